@@ -82,13 +82,15 @@ struct SceneEntry {
     uint64_t hash = 0;
     uint64_t last_use = 0;
     SceneDev sc{};
-    DevBuf lam_tab, dir_tab, slot, nlay, pupil_xy;
+    DevBuf lam_tab, dir_tab, slot, nlay, pupil_xy, dirs, dir_n;
     std::vector<int32_t> h_nlay;
     void release()
     {
-        for (DevBuf* b : { &lam_tab, &dir_tab, &slot, &nlay, &pupil_xy }) b->release();
+        for (DevBuf* b : { &lam_tab, &dir_tab, &slot, &nlay, &pupil_xy, &dirs, &dir_n }) b->release();
     }
 };
+// Largest direction table of a scene (1 GiB, 87381 points).
+constexpr int64_t kDirTableMaxDoubles = (int64_t)1 << 27;
 // Scenes kept per context (least recently used evicted), so that calls
 // that alternate between a few scenes (a batch traced in chunks of designs)
 // rebuild nothing, and can be captured in one graph once each was built.
@@ -486,6 +488,16 @@ int build_scene(gwg_ctx* c, const gwg_slab* sl, const gwg_prma* pr, const gwg_ma
     s.slot = (const uint8_t*)ent->slot.p;
     s.nlay = (const int32_t*)ent->nlay.p;
     s.pupil_xy = (const double*)ent->pupil_xy.p;
+    // direction states of collimated beams (12 KB a point; scenes of very
+    // many points walk in general)
+    if (s.fov_mode == 0 && dir_table_doubles(s) <= kDirTableMaxDoubles) {
+        HIP_CHECK(c, ent->dirs.ensure(sizeof(double) * (size_t)dir_table_doubles(s)), "alloc direction states");
+        HIP_CHECK(c, ent->dir_n.ensure(sizeof(int32_t) * (size_t)s.n_lsel * s.F), "alloc direction counts");
+        HIP_CHECK(c, launch_dir_states(s, (double*)ent->dirs.p, (int32_t*)ent->dir_n.p, stream), "direction states kernel");
+        HIP_CHECK(c, hipStreamSynchronize(stream), "direction states");
+        s.dirs = (const double*)ent->dirs.p;
+        s.dir_n = (const int32_t*)ent->dir_n.p;
+    }
     ent->h_nlay.assign(st->n_layers, st->n_layers + DM);
     ent->hash = h;
     ent->last_use = ++c->scene_clock;
@@ -500,7 +512,7 @@ int pick_fwd_wg(gwg_ctx* c, const SceneDev& s, bool lds_bins)
 {
     if (c->tune.block_threads) return c->tune.block_threads;
     for (int wg : { 256, 128, 64 })
-        if (fwd_smem_bytes(s, wg, lds_bins) <= 65536) return wg;
+        if (fwd_scene_bytes(s, wg, lds_bins) <= 65536) return wg;
     return 64;
 }
 
@@ -782,18 +794,17 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
     sc.tab_scale = nullptr;
     sc.tab_acc = nullptr;
     int wg = pick_fwd_wg(c, sc, lds_bins);
-    if (sc.memo && fwd_smem_bytes(sc, wg, lds_bins) > 65536) {
+    if (sc.memo && fwd_scene_bytes(sc, wg, lds_bins) > 65536) {
         sc.memo = 0;                                   // per-hit solves (their own slot table size)
         wg = pick_fwd_wg(c, sc, lds_bins);
     }
     set_tiles(sc, c->tune.rays_per_block, wg, c->n_cu);
-    if (fwd_smem_bytes(sc, wg, lds_bins) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
+    if (fwd_scene_bytes(sc, wg, lds_bins) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     if (sc.n_items > 0x7fffffff) return fail(c, GWG_E_INVAL, "too many work items; raise rays_per_block");
     const int64_t nbins = (int64_t)sc.D * sc.n_lsel * sc.F * B;
     const bool table = (flags & GWG_FWD_TABLE) != 0;
-    // per-hit solves take a wave's rays in pools of rounds (all of an item's
-    // rounds, up to kPoolMax); the memoized and table forwards round by round
-    sc.pool = (sc.memo || table) ? 1 : (int32_t)std::min<int64_t>(kPoolMax, (sc.rays_per_tile + wg - 1) / wg);
+    // a wave takes its rays in pools of rounds: all of an item's rounds, up to kPoolMax
+    sc.pool = (int32_t)std::min<int64_t>(kPoolMax, (sc.rays_per_tile + wg - 1) / wg);
     if (table) {
         const int n = c->tune.table_nodes ? c->tune.table_nodes : kTableNodesDefault;
         const size_t tab_b = sizeof(double) * 8 * (size_t)sc.D * sc.n_lsel * sc.M * 2 * (size_t)n;
@@ -1233,7 +1244,7 @@ int gwg_autotune(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, const g
     // forward candidates: block size x ray tile; bins must not depend on them
     std::vector<gwg_tuning> cands;
     for (int wg : { 256, 128 }) {
-        if (fwd_smem_bytes(sc0, wg, lds_bins) > 65536) continue;
+        if (fwd_scene_bytes(sc0, wg, lds_bins) > 65536) continue;
         SceneDev t = sc0;
         set_tiles(t, 0, wg, c->n_cu);
         std::vector<int64_t> seen;

@@ -43,10 +43,13 @@ __device__ inline void q_put(const Queue& q, int pos, double kappa, cd Gs, cd Gp
 
 // Adjoint thin-film solve of one mirror hit (one per lane): kappa, the
 // scaled cotangents and meta = mirror | front << 8 | reflected << 9.
-// LOSSLESS: the scene has no absorbing slot (compiled without the general path).
+// KIND: the scene has no absorbing slot (ADJ_LOSSLESS), has one (ADJ_ABSORBING),
+// or either (ADJ_ANY): the entry kernels are compiled for one of them, so that
+// each keeps within the 64 KB instruction cache.
 // stored: chk is the entry's checkpoint block written by the forward solve
 // (lossless stacks; the sweep is not run again).
-template <bool LOSSLESS = false>
+enum { ADJ_ANY = 0, ADJ_LOSSLESS = 1, ADJ_ABSORBING = 2 };
+template <int KIND = ADJ_ANY>
 __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const double* s_thk,
                                    const uint8_t* s_slot, const LaneSlots3& sl, double* gw, double kappa, cd Gs,
                                    cd Gp, int meta, double* chk, int64_t cstride, bool stored = false)
@@ -62,7 +65,7 @@ __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const
     }
     const double z0 = pl.ng * pl.ng - kappa * kappa;
     const double q0 = sqrt(z0 > kTinyZ ? z0 : kTinyZ);
-    if (LOSSLESS || sc.slot_complex == 0u) {
+    if (KIND == ADJ_LOSSLESS || (KIND == ADJ_ANY && sc.slot_complex == 0u)) {
         // waves whose lanes all see circular layers take the sweep without
         // the hyperbolic case (same results).  A sweep the forward stored
         // has its hit's checkpoint interval; a sweep run here takes one
@@ -80,7 +83,7 @@ __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const
                                        pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, stored,
                                        kseg);
     }
-    else if (!LOSSLESS)
+    else if (KIND != ADJ_LOSSLESS)
         tmm_adjoint(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, sc.slot_complex,
                     pl.k0, kappa * kappa, q0, pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk,
                     cstride);
@@ -209,7 +212,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
                 if constexpr (TAB)
                     walk_ray<true, true>(sc, *pl, r, o, NoHit{}, TabCoef{ tab_dl, sc.table_n, pl->ng, sc.nx, sc.nz }, tape, &nt);
                 else
-                    walk_ray<true, true>(sc, *pl, r, o, NoHit{}, GetCoef{ hq, own, nullptr }, tape, &nt);
+                    walk_ray<true, true>(sc, *pl, r, o, NoHit{}, GetCoef{ hq, own }, tape, &nt);
                 c_rays += 1;
                 c_ev += (unsigned long long)r.nev;
                 c_hits += (unsigned long long)r.nprma;
@@ -391,7 +394,7 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                     // the forward stored this entry's sweep (lossless FP64 stacks)
                     const bool stored = LOSSLESS && st.ck && k < st.ck_cap;
                     double* c = stored ? st.ck + ((item * st.waves + rr) * st.ck_cap + k) * 8 : chk;
-                    adjoint_hit<LOSSLESS>(sc, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, c,
+                    adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, c,
                                           stored ? 8 * st.ck_total : nthreads, stored);
                     c_ahits += 1;
                     c_alay += (unsigned long long)pl->nlay[mm & 255];

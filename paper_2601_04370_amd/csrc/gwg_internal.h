@@ -71,10 +71,10 @@ enum StatWord { ST_RAYS = 0, ST_EVENTS = 1, ST_PRMA = 2, ST_FP64 = 3, ST_SAT = 4
 // cnt[item * waves + wave] = entries of that region; ovf[item] != 0 when a
 // region of the item overflowed (the backward then regenerates that item).
 constexpr int kEntFields = 6;
-constexpr int kFwdMemoKeys = 128;      // largest key table per wave of the memoized forward
+constexpr int kFwdMemoKeys = 128;      // largest key table of a work item of the keyed forwards
 constexpr int kTableNodesDefault = 8192;
 constexpr int kCkEntriesPerRay = 4;        // sweep checkpoints kept per ray (entry regions)
-constexpr int kPoolMax = 8;                // per-hit forward: rounds of 64 rays per wave pool, at most
+constexpr int kPoolMax = 8;                // forward: rounds of 64 rays per wave pool, at most
 constexpr double kCkBudgetBytes = 128.0 * (1ull << 30);
 constexpr int kTableNodesMax = 1 << 20;
 struct AdjStore {
@@ -127,6 +127,10 @@ struct SceneDev {
     const double* lam_tab;            // [n_lsel][LT_STRIDE]
     int32_t fov_mode, F;
     const double* dir_tab;            // [n_lsel][F][4]
+    // direction states of the points (collimated beams; null: rays walk in
+    // general), kDirMax per point, and their counts
+    const double* dirs;               // [n_lsel][F][kDirMax][kDirWords]
+    const int32_t* dir_n;             // [n_lsel][F]
     double fov_x0, fov_x1, fov_y0, fov_y1;  // random mode bounds, degrees
     int64_t N;                        // rays per point
     int64_t id_base;                  // added to a ray's id in its random stream (first_design n_lsel F N)
@@ -136,8 +140,8 @@ struct SceneDev {
     uint32_t seed_hi, step_host;      // with step_dev: key1 = seed_hi ^ (step_host + *step_dev)
     const uint32_t* step_dev;         // optional device step counter (graph replays)
     int32_t precision;
-    int32_t memo;                     // forward: key table capacity per wave (0: solve every hit)
-    int32_t pool;                     // forward: rounds of 64 rays per pool of a wave (per-hit solves; else 1)
+    int32_t memo;                     // forward: key table capacity per work item (0: solve every hit)
+    int32_t pool;                     // forward: rounds of 64 rays per pool of a wave
     // angle table (table_n = 0: exact per-hit thin film)
     const double* table;              // [D][n_lsel][M][2 sides][table_n][8]
     int32_t table_n;

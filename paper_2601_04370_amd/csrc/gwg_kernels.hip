@@ -59,7 +59,7 @@ __host__ __device__ inline SmemLayout smem_layout(int M, int Lmax, int n_slots, 
 
 // Stage one point's uniform data and its design's stacks into LDS: as
 // thickness and slot arrays (s_thk, s_slot) or as layer records (s_rec, for
-// slot tables of `per` values per slot).
+// slot tables of `per` values per slot); neither: no stacks.
 __device__ inline void stage_point(const SceneDev& sc, int d, int l, int f, PointLds* pl,
                                    double* s_thk, uint8_t* s_slot, LayerRec* s_rec = nullptr, int per = 0)
 {
@@ -102,7 +102,7 @@ __device__ inline void stage_point(const SceneDev& sc, int d, int l, int f, Poin
     const uint8_t* gslot = sc.slot + (int64_t)d * n;
     if (s_rec)
         stage_recs(s_rec, gthk, gslot, sc.M, sc.Lmax, per);
-    else
+    else if (s_thk)
         for (int i = tid; i < n; i += nt) { s_thk[i] = gthk[i]; s_slot[i] = gslot[i]; }
 }
 
@@ -137,6 +137,7 @@ __device__ inline int64_t draw_item(unsigned long long* ctr)
 }
 
 #include "gwg_table.h"
+#include "gwg_dirs.h"
 #include "gwg_fwd_kernel.h"
 #include "gwg_bwd_kernel.h"
 #include "gwg_memo_kernel.h"
@@ -454,11 +455,23 @@ hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s)
     return hipGetLastError();
 }
 
+// LDS of the scene's layout by which a scene is accepted (64 KB) and a
+// workgroup size picked: point data, stacks, slot tables, bins and, memoized,
+// 3 KB of keys per wave.  The launch takes the direction and key tables and
+// the statistics' columns on top (at most 25 KB): a workgroup may use 160 KB
+// on gfx950, and two of the usual scenes' fit a CU.
+size_t fwd_scene_bytes(const SceneDev& sc, int wg, bool lds_bins)
+{
+    return (size_t)smem_layout(sc.M, sc.Lmax, sc.n_slots, wg, sc.bins_x * sc.bins_y, lds_bins, 0,
+                               sc.memo ? LaneSlots3::kPer : LaneSlots3x::kPer, true).total
+           + (sc.memo ? (size_t)(wg / 64) * (24 * kFwdMemoKeys) : 0);
+}
 size_t fwd_smem_bytes(const SceneDev& sc, int wg, bool lds_bins)
 {
     return (size_t)smem_layout(sc.M, sc.Lmax, sc.n_slots, wg, sc.bins_x * sc.bins_y, lds_bins, 0,
                                sc.memo ? LaneSlots3::kPer : LaneSlots3x::kPer, true).total
-           + (sc.memo ? (size_t)(wg / 64) * fwd_memo_wave_bytes() : 0);
+           + (NCAT + 2) * kStatCols * 8 + (size_t)dir_smem_bytes(sc)
+           + (sc.memo || sc.table ? (size_t)key_smem_bytes(sc.M) : 0);
 }
 size_t bwd_smem_bytes(const SceneDev& sc, int wg)
 {
@@ -679,6 +692,13 @@ hipError_t launch_table_reduce(const double* partial, const SceneDev& sc, double
                        sc.Lmax, sc.nlay, grad);
     return hipGetLastError();
 }
+
+hipError_t launch_dir_states(const SceneDev& sc, double* dirs, int32_t* dir_n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_dir_states, dim3((unsigned)(sc.n_lsel * sc.F)), dim3(64), 0, s, sc, dirs, dir_n);
+    return hipGetLastError();
+}
+int64_t dir_table_doubles(const SceneDev& sc) { return (int64_t)sc.n_lsel * sc.F * kDirMax * kDirWords; }
 
 hipError_t launch_omega_grad(const SceneDev& sc, int grid_blocks, int wg, const double* W, const uint32_t* counts,
                              double* partial, double* grad, hipStream_t s)

@@ -11,7 +11,10 @@ hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s);
 
+size_t fwd_scene_bytes(const SceneDev& sc, int wg, bool lds_bins);
 size_t fwd_smem_bytes(const SceneDev& sc, int wg, bool lds_bins);
+hipError_t launch_dir_states(const SceneDev& sc, double* dirs, int32_t* dir_n, hipStream_t s);
+int64_t dir_table_doubles(const SceneDev& sc);
 size_t bwd_smem_bytes(const SceneDev& sc, int wg);
 size_t tmm_smem_bytes(int L, int n_slots, int wg);
 int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);

@@ -213,7 +213,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves, 2) k_adj_memo(SceneDev sc, co
                             const cd Gs = cscale(mk(st.ent[1 * st.total + e], st.ent[2 * st.total + e]), gscale);
                             const cd Gp = cscale(mk(st.ent[3 * st.total + e], st.ent[4 * st.total + e]), gscale);
                             const int mm = (int)(meta & 1023);
-                            adjoint_hit<LOSSLESS>(sc, *pl, s_thk, s_slot, sl, gw, st.ent[e], Gs, Gp, mm, chk, nthreads);
+                            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, st.ent[e], Gs, Gp, mm, chk, nthreads);
                             c_keys += 1;
                             c_lay += (unsigned long long)pl->nlay[mm & 255];
                         }
@@ -227,7 +227,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves, 2) k_adj_memo(SceneDev sc, co
                         const cd Gs = mk(m0.gsum[k], m0.gsum[kMemoKeys + k]);
                         const cd Gp = mk(m0.gsum[2 * kMemoKeys + k], m0.gsum[3 * kMemoKeys + k]);
                         const int mm = m0.kmeta[k];
-                        adjoint_hit<LOSSLESS>(sc, *pl, s_thk, s_slot, sl, gw,
+                        adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw,
                                               __longlong_as_double((long long)m0.kbits[k]), Gs, Gp, mm, chk, nthreads);
                         c_keys += 1;
                         c_lay += (unsigned long long)pl->nlay[mm & 255];

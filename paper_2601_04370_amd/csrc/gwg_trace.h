@@ -246,13 +246,11 @@ __device__ inline FaceCoef face_coeffs(double ng, double na, double dx, double d
     return f;
 }
 
-// Eyebox bin of a ray leaving the top face at (px, py) along air direction
-// a: the grid cell of its crossing of the eyebox plane, or, with eye pupils,
-// the pupil whose circle holds the crossing (pupils do not overlap).
-__device__ inline int eyebox_bin(const SceneDev& sc, const PointLds& pl, double px, double py, const double* a)
+// Eyebox bin of a ray that crosses the eyebox plane at (xe, ye): the grid
+// cell, or, with eye pupils, the pupil whose circle holds the crossing
+// (pupils do not overlap).
+__device__ inline int eyebox_cell(const SceneDev& sc, const PointLds& pl, double xe, double ye)
 {
-    double xe = px + pl.ER * (a[0] / a[2]);
-    double ye = py + pl.ER * (a[1] / a[2]);
     if (sc.n_pupils > 0) {
         for (int q = 0; q < sc.n_pupils; ++q) {
             const double dx = xe - sc.pupil_xy[2 * q];
@@ -266,6 +264,12 @@ __device__ inline int eyebox_bin(const SceneDev& sc, const PointLds& pl, double 
     if (!(fx >= 0.0 && fx < (double)pl.bins_x && fy >= 0.0 && fy < (double)pl.bins_y)) return -1;
     int bx = (int)fx, by = (int)fy;
     return by * pl.bins_x + bx;
+}
+
+// ... of a ray leaving the top face at (px, py) along air direction a.
+__device__ inline int eyebox_bin(const SceneDev& sc, const PointLds& pl, double px, double py, const double* a)
+{
+    return eyebox_cell(sc, pl, px + pl.ER * (a[0] / a[2]), py + pl.ER * (a[1] / a[2]));
 }
 
 __device__ inline void exit_direction(double ng, double na, const Ray& r, double st2, double* a)
@@ -321,13 +325,12 @@ __device__ inline int wave_max_int(int x)
 }
 
 // ------------------------------------------------------------ hit queue
-// Mirror hits of one wave's current round of rays: entry p holds the hit's
-// kappa and meta (mirror | front << 8), after the solve its four
-// coefficients, and (field 10) the checkpoint slot of its adjoint entry or
-// -1.  Field f of entry p at base[f * cap + p].
-// A wave's hit queue holds up to Kmax hits per lane; hit h of lane l is in
-// slot h * 64 + l, so the lanes' h-th hits share 512 contiguous bytes per
-// field (the walks touch the lanes' hits in step).
+// Mirror hits of one wave's rays: entry p holds the hit's kappa and meta
+// (mirror | front << 8 | reflected << 9), and after the solve its
+// coefficients.  Field f of entry p at base[f * cap + p].
+// The regenerating backward's queue holds up to Kmax hits per lane; hit h of
+// lane l is in slot h * 64 + l, so the lanes' h-th hits share 512 contiguous
+// bytes per field (the walks touch the lanes' hits in step).
 __device__ inline int hq_slot(int lane, int h) { return h * 64 + lane; }
 
 struct HitQueue {
@@ -355,9 +358,7 @@ struct HitQueue {
         return c;
     }
 };
-// Field 11 (non-memoized forward): the solve order, the slot of the wave's
-// p-th solved hit at position p.
-constexpr int kHitFields = 12;
+constexpr int kHitFields = 10;
 
 // ------------------------------------------------------------ tape
 // Field-changing events of one ray, for the reverse field sweep.  Event k
