@@ -183,14 +183,19 @@ int ensure_buf(gwg_ctx* c, DevBuf& b, size_t n, bool capturing, const char* what
     return GWG_OK;
 }
 
-int occupancy(gwg_ctx* c, int kind, int precision, int wg, size_t smem)
+template <class Query>
+int occupancy(gwg_ctx* c, int kind, int precision, int wg, size_t smem, Query query)
 {
     const auto key = std::make_tuple(kind, precision, wg, smem);
     auto it = c->occ.find(key);
     if (it != c->occ.end()) return it->second;
-    const int n = trace_blocks_per_cu(kind, precision, wg, smem);
+    const int n = query();
     c->occ[key] = n;
     return n;
+}
+int occupancy(gwg_ctx* c, int kind, int precision, int wg, size_t smem)
+{
+    return occupancy(c, kind, precision, wg, smem, [&]() { return trace_blocks_per_cu(kind, precision, wg, smem); });
 }
 
 struct DeviceGuard {
@@ -787,8 +792,8 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
     sc.precision = precision;
     const int B = sc.bins_x * sc.bins_y;
     const bool lds_bins = B <= 2048;
-    // memoized solves need collimated beams (shared hit keys) and room for the key tables
-    sc.memo = ((flags & GWG_FWD_MEMO) && sc.fov_mode == 0) ? (c->tune.memo_keys ? c->tune.memo_keys : kFwdMemoKeys) : 0;
+    // memoized solves need collimated beams (keys by direction state) and room for the key tables
+    sc.memo = ((flags & GWG_FWD_MEMO) && sc.dirs) ? (c->tune.memo_keys ? c->tune.memo_keys : kFwdMemoKeys) : 0;
     sc.table = nullptr;
     sc.table_n = 0;
     sc.tab_scale = nullptr;
@@ -851,7 +856,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
             HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items, 0u, s), "zero overflow flags");
-            c->adj = AdjStore{ (double*)c->adj_ent.p, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, cap_w, total, waves,
+            c->adj = AdjStore{ (double*)c->adj_ent.p, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, cap_w, waves,
                                nullptr, 0, 0, nullptr };
             adj = true;
             // The FP64 solve can keep the adjoint's sweep checkpoints of the
@@ -890,14 +895,15 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
-            c->adj = AdjStore{ nullptr, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, 0, 0, waves, nullptr, 0, 0, nullptr };
+            c->adj = AdjStore{ nullptr, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, 0, waves, nullptr, 0, 0, nullptr };
         }
         adj_sweep = adj || table;
     }
     // persistent grid: as many workgroups as fit on the device at once
-    const int kind_f = adj_sweep ? (table ? KIND_FWD_ADJ_TAB : sc.memo ? KIND_FWD_ADJ_MEMO : KIND_FWD_ADJ)
-                                 : (table ? KIND_FWD_TAB : sc.memo ? KIND_FWD_MEMO : KIND_FWD);
-    const int per_cu = occupancy(c, kind_f, precision, wg, fwd_smem_bytes(sc, wg, lds_bins));
+    const int kind_f = KIND_FWD + (adj_sweep ? 1 : 0) + (table ? 2 : 0) + (sc.memo ? 4 : 0) + (sc.dirs ? 8 : 0);
+    const size_t smem_f = fwd_smem_bytes(sc, wg, lds_bins);
+    const int per_cu = occupancy(c, kind_f, precision, wg, smem_f,
+                                 [&]() { return fwd_blocks_per_cu(sc, adj_sweep, wg, smem_f); });
     const int64_t grid = std::min<int64_t>(sc.n_items, (int64_t)std::max(c->n_cu, 1) * per_cu);
     rc = ensure_buf(c, c->fwd_scratch, sizeof(double) * (size_t)fwd_scratch_doubles(sc, grid, wg), cap, "alloc hit queues");
     if (rc) return rc;

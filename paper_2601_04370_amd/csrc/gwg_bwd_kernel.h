@@ -25,6 +25,13 @@
 
 constexpr int kQFields = 6;      // kappa, Gs.re, Gs.im, Gp.re, Gp.im, meta
 
+__device__ inline AdjEntry load_entry(const AdjStore& st, int64_t e)
+{
+    const double2* p = (const double2*)(st.ent + e * kEntFields);
+    const double2 a = p[0], b = p[1], c = p[2];
+    return { a.x, a.y, b.x, b.y, c.x, (int64_t)c.y };
+}
+
 struct Queue {
     double* base;      // this wave's queue, field f of slot p at base[f * cap + p]
     int cap;
@@ -371,7 +378,7 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                 if (c < total) {
                     int rr = 0, k = c;
                     while (k >= cnt[rr]) { k -= cnt[rr]; ++rr; }
-                    const double kap = st.ent[(item * st.waves + rr) * st.cap_w + k];
+                    const double kap = st.ent[((item * st.waves + rr) * st.cap_w + k) * kEntFields];
                     ev = kap * kap > pl->kap2_evan;
                 }
                 qc.add(c < total && !ev, c, lane);
@@ -383,13 +390,14 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                 int rr = 0, k = v;
                 while (k >= cnt[rr]) { k -= cnt[rr]; ++rr; }
                 const int64_t e = (item * st.waves + rr) * st.cap_w + k;
-                const double kappa = st.ent[e];
-                const int64_t meta = (int64_t)st.ent[5 * st.total + e];
+                const AdjEntry en = load_entry(st, e);
+                const double kappa = en.kappa;
+                const int64_t meta = en.meta;
                 const int bin = (int)(meta >> 10);
                 const double gscale = g_bins[bin] / (double)sc.N;
                 if (gscale != 0.0) {
-                    const cd Gs = cscale(mk(st.ent[1 * st.total + e], st.ent[2 * st.total + e]), gscale);
-                    const cd Gp = cscale(mk(st.ent[3 * st.total + e], st.ent[4 * st.total + e]), gscale);
+                    const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
+                    const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
                     const int mm = (int)(meta & 1023);
                     // the forward stored this entry's sweep (lossless FP64 stacks)
                     const bool stored = LOSSLESS && st.ck && k < st.ck_cap;

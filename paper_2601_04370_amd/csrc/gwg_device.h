@@ -75,8 +75,11 @@ __device__ inline u32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t
 {
 #pragma unroll
     for (int i = 0; i < 10; ++i) {
-        uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+        // one wide multiply each for the low and high words (integer
+        // multiplies issue at a quarter of the rate)
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+        uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
         uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
         k0 += 0x9E3779B9u;
@@ -735,14 +738,25 @@ __device__ inline void renorm(V2<T>& v, int& e)
 // Coefficients (Eq. 3 convention) from the chain result.
 struct Coef4 { cd rs, rp, ts, tp; };
 
-template <typename T>
+// TAKEN: only the reflected (refl) or the transmitted pair, returned as
+// both: the same divisions of the selected numerators, half as many.
+template <typename T, bool TAKEN = false>
 __device__ inline Coef4 finish_coeffs(const V2<T>& vs, const V2<T>& vp, int es, int ep,
-                                      double eta0s, double eta0p, cd tp_factor)
+                                      double eta0s, double eta0p, cd tp_factor, bool refl = false)
 {
     cd Bs = mk((double)vs.br, (double)vs.bi), Cs = mk((double)vs.cr, (double)vs.ci);
     cd Bp = mk((double)vp.br, (double)vp.bi), Cp = mk((double)vp.cr, (double)vp.ci);
     cd dens = cadd(cscale(Bs, eta0s), Cs), denp = cadd(cscale(Bp, eta0p), Cp);
     Coef4 o;
+    if constexpr (TAKEN) {
+        const cd rn = csub(cscale(Bs, eta0s), Cs), rm = csub(cscale(Bp, eta0p), Cp);
+        const cd s = cdiv(refl ? rn : mk(2.0 * eta0s, 0.0), dens);
+        const cd p = cdiv(refl ? rm : mk(2.0 * eta0p, 0.0), denp);
+        const cd ts = cscale(s, ldexp(1.0, -es)), tp = cscale(cmul(p, tp_factor), ldexp(1.0, -ep));
+        o.rs = o.ts = refl ? s : ts;
+        o.rp = o.tp = refl ? mk(-p.re, -p.im) : tp;
+        return o;
+    }
     o.rs = cdiv(csub(cscale(Bs, eta0s), Cs), dens);
     cd rpm = cdiv(csub(cscale(Bp, eta0p), Cp), denp);
     o.rp = mk(-rpm.re, -rpm.im);
@@ -859,23 +873,24 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
 // hyperbolic case; the results are the same).  ck (lossless FP64 stacks):
 // the entry's checkpoint blocks for the adjoint's sweep (block g at ck + g
 // ckb, one every kseg layers), or null.
-template <typename T, class SL, class Stk>
+// TAKEN: finish_coeffs's.
+template <typename T, bool TAKEN = false, class SL, class Stk>
 __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk, int L,
                                   bool front, const SL& sl, uint32_t cplx_mask, double k0d, double eta0s,
                                   double eta0p, cd etaEs, cd etaEp, cd tp_factor, bool circ = false,
-                                  double* ck = nullptr, int64_t ckb = 8, int kseg = kSegL)
+                                  double* ck = nullptr, int64_t ckb = 8, int kseg = kSegL, bool refl = false)
 {
     const T k0 = (T)k0d;
     V2<T> vs = { (T)1, (T)0, (T)etaEs.re, (T)etaEs.im };
     V2<T> vp = { (T)1, (T)0, (T)etaEp.re, (T)etaEp.im };
     int es = 0, ep = 0;
-    if (L <= 0) return finish_coeffs(vs, vp, es, ep, eta0s, eta0p, tp_factor);
+    if (L <= 0) return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
     if (cplx_mask == 0u) {
         if (circ)
             lossless_sweep<T, false>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg);
         else
             lossless_sweep<T, true>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg);
-        return finish_coeffs(vs, vp, es, ep, eta0s, eta0p, tp_factor);
+        return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
     }
     auto cur = stk.cursor(L, front);
     for (int j = 0; j < L; ++j, cur.next()) {
@@ -900,7 +915,7 @@ __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk,
         }
         if (sizeof(T) == 4 && (j & 7) == 7) { renorm(vs, es); renorm(vp, ep); }
     }
-    return finish_coeffs(vs, vp, es, ep, eta0s, eta0p, tp_factor);
+    return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
 }
 
 }  // namespace gwg

@@ -29,9 +29,12 @@
 // event and wave for the geometry, 1600 with the field and the tape: three
 // divisions, two square roots, two bases and four 3-vectors an event).
 // Forward kernel before and after, 6 mirrors, 3 x 441 points: 8192 rays a
-// point, 200 layers, gradient flag 29.3 -> 25.6 ms, memoized 14.5 -> 5.4 ms,
-// angle table 12.4 -> 7.0 ms; 65536 rays a point, 40 layers, no gradient
-// 93.1 -> 68.9 ms.
+// point, 200 layers, gradient flag 29.3 -> 23.1 ms, memoized 14.5 -> 3.4 ms,
+// angle table 12.4 -> 3.4 ms; 65536 rays a point, 40 layers, no gradient
+// 93.1 -> 55.5 ms.  The walk's loop keeps its state's quantities in registers
+// (read from LDS at every event instead: 17.4 ms of geometry for 8.3e8
+// events; so: 13.1 ms); what is left of it is issue and LDS latency at two
+// waves per SIMD.
 
 constexpr int kDirMax = 64;           // directions kept per point
 constexpr int kDirGeo = 12;           // doubles of a state's geometry part
@@ -48,7 +51,7 @@ enum { DF_RS = 0, DF_RP = 2, DF_ROT = 4, DF_XS = 8, DF_XP = 9, DF_EX = 10, DF_EY
 // flag word: child states (state << 1 | dz < 0) after a reflection at dz > 0
 // (bits 0-7) and dz < 0 (bits 8-15), total reflection at the faces (bit 16),
 // mirror basis defined at dz > 0 and dz < 0 (bits 17, 18)
-constexpr unsigned long long kDirTir = 1ull << 16;
+constexpr uint32_t kDirTir = 1u << 16;
 
 // n / d for finite operands from r = 1 / d correctly rounded: one fused
 // correction of n r gives the correctly rounded quotient (Markstein, 1990).
@@ -114,7 +117,7 @@ __global__ void __launch_bounds__(64) k_dir_states(SceneDev sc, double* __restri
     double* g = out + (pt * kDirMax + lane) * kDirWords;
     double* f = g + kDirGeo;
     const FaceCoef fc = face_coeffs(ng, na, ex, dy, ez);
-    unsigned long long flags = (unsigned long long)s_child[lane][0] | (unsigned long long)s_child[lane][1] << 8;
+    uint32_t flags = (uint32_t)s_child[lane][0] | (uint32_t)s_child[lane][1] << 8;
     if (fc.tir) flags |= kDirTir;
     g[DG_ADZ] = ez; g[DG_RDZ] = 1.0 / ez;
     g[DG_DX] = ex; g[DG_RDX] = 1.0 / ex;
@@ -150,9 +153,7 @@ __global__ void __launch_bounds__(64) k_dir_states(SceneDev sc, double* __restri
     g[11] = 0.0;
 }
 
-// LDS of a workgroup's direction table: the geometry parts, then the field parts.
-__host__ __device__ inline int dir_smem_bytes(const SceneDev& sc) { return sc.dirs ? kDirMax * kDirWords * 8 : 0; }
-
+// A workgroup's direction table in LDS: the geometry parts, then the field parts.
 struct DirLds {
     const double* g;                  // [kDirMax][kDirGeo]
     const double* f;                  // [kDirMax][kDirFld]
@@ -198,7 +199,7 @@ struct DirFate {
 
 // Geometry and branch decisions of one ray of the point: walk_ray<false>'s
 // operations on positions, with the direction's quantities from the table.
-// Every mirror hit h calls on_hit(h, kappa, word) and on_hit.branch(m, refl).
+// Every mirror hit h calls on_hit(h, &kappa, word) and on_hit.branch(m, refl).
 // The random words of the first eight hits are drawn before the loop, where
 // every lane needs them, rather than in the iteration in which some lane of
 // the wave reaches its first or fifth hit.
@@ -216,76 +217,73 @@ __device__ inline void dir_walk(const SceneDev& sc, const PointLds& pl, const Di
     double py = u24(w.y) * sc.ph - 0.5 * sc.ph;
     double pz = pl.T;
     const double nx = pl.nx, nz = pl.nz, T = pl.T, dy = dt.dy;
-    const int M = pl.M;
+    const int M = pl.M, Kmax = pl.Kmax;
     int e = 0, neg = dt.root, cell = 0, last = SURF_TOP, nev = 0, nh = 0, nt = 0;
     o.pol = (int)(w.x & 1u);
     o.bin = -1;
     o.off = neg == kDirOff;
     o.cat = CAT_LOST;
+    o.e = 0;
     if (o.off) return;
-    for (;;) {
-        if (nev >= pl.Kmax) { o.cat = CAT_TRUNC; break; }
+    // the state's quantities stay in registers between reflections
+    double adz, rdz, dx, dnp, rdnp, dnn, rdnn;
+    uint32_t fl;
+    auto load = [&]() {
         const double* g = dt.g + e * kDirGeo;
-        const double adz = g[DG_ADZ], dx = g[DG_DX];
-        const double dn = g[DG_DN + 2 * neg], rdn = g[DG_DN + 2 * neg + 1];
-        const double dz = neg ? -adz : adz;
-        // candidates in next_surface's order: the face ahead, the left side
-        // (end face 0 or mirror cell-1), the right side (end face 1 or mirror cell)
-        double best = dir_quot(neg ? pz : T - pz, adz, g[DG_RDZ]);
-        const int face = neg ? SURF_BOTTOM : SURF_TOP;
+        adz = g[DG_ADZ]; rdz = g[DG_RDZ]; dx = g[DG_DX];
+        dnp = g[DG_DN]; rdnp = g[DG_DN + 1]; dnn = g[DG_DN + 2]; rdnn = g[DG_DN + 3];
+        fl = (uint32_t)__double_as_longlong(g[DG_FLAGS]);
+    };
+    load();
+    while (nev < Kmax) {
+        const bool up = neg == 0;
+        const double dn = up ? dnp : dnn, rdn = up ? rdnp : rdnn;
+        // candidates in next_surface's order: the face ahead, end face 0, the
+        // mirror ahead (the cell's left one for n.d > 0, else its right one),
+        // end face 1; an earlier one keeps a tie
+        const int mm = dn > 0.0 ? cell - 1 : cell;
+        const bool hm = (unsigned)mm < (unsigned)M && last != mm && dn != 0.0;
+        const double hp = pl.h[hm ? mm : 0];
+        double best = dir_quot(up ? T - pz : pz, adz, rdz);
+        const int face = up ? SURF_TOP : SURF_BOTTOM;
         int hit = last != face ? face : -1;
-        const double pn = nx * px + nz * pz;
-        const bool ml = cell != 0 && dn > 0.0 && last != cell - 1;
-        const bool mr = cell != M && dn < 0.0 && last != cell;
-        const int mm = ml ? cell - 1 : cell;
-        double tm = 0.0;
-        if (ml || mr) tm = dir_quot(pl.h[mm] - pn, dn, rdn);
-        const bool e0 = cell == 0 && dx < 0.0 && last != SURF_END0;
-        const bool e1 = cell == M && dx > 0.0 && last != SURF_END1;
-        double te = 0.0;
-        if (e0 || e1) te = dir_quot((e0 ? 0.0 : pl.Lx) - px, dx, g[DG_RDX]);
-        if (e0) {
+        const double tm = dir_quot(hp - (nx * px + nz * pz), dn, rdn);
+        if (cell == 0 && dx < 0.0 && last != SURF_END0) {
+            const double te = dir_quot(0.0 - px, dx, dt.g[e * kDirGeo + DG_RDX]);
             if (hit < 0 || te < best) { best = te; hit = SURF_END0; }
-        } else if (ml) {
-            if (hit < 0 || tm < best) { best = tm; hit = mm; }
         }
-        if (e1) {
+        if (hm && (hit < 0 || tm < best)) { best = tm; hit = mm; }
+        if (cell == M && dx > 0.0 && last != SURF_END1) {
+            const double te = dir_quot(pl.Lx - px, dx, dt.g[e * kDirGeo + DG_RDX]);
             if (hit < 0 || te < best) { best = te; hit = SURF_END1; }
-        } else if (mr) {
-            if (hit < 0 || tm < best) { best = tm; hit = mm; }
         }
-        if (hit < 0) break;                              // CAT_LOST
+        if (hit < 0 || hit >= SURF_END0) {
+            if (hit >= 0) { o.cat = CAT_END; ++nev; }    // else CAT_LOST
+            break;
+        }
         px = px + best * dx;
         py = py + best * dy;
-        pz = pz + best * dz;
+        pz = pz + best * (up ? adz : -adz);
         ++nev;
-        const unsigned long long fl = (unsigned long long)__double_as_longlong(g[DG_FLAGS]);
+        last = hit;
         if (hit >= SURF_TOP) {
-            if (hit >= SURF_END0) { o.cat = CAT_END; break; }
-            pz = neg ? 0.0 : T;
+            pz = up ? T : 0.0;
             if (!(fl & kDirTir)) {
-                if (!neg) {
-                    const double* f = dt.f + e * kDirFld;
-                    o.bin = eyebox_cell(sc, pl, px + f[DF_EX], py + f[DF_EY]);
-                    o.cat = o.bin >= 0 ? CAT_EYEBOX : CAT_MISS;
-                } else {
-                    o.cat = CAT_LEAK;
-                }
+                o.cat = up ? CAT_EYEBOX : CAT_LEAK;      // the bin decides below
                 break;
             }
             neg ^= 1;
             ++nt;
-            last = hit;
         } else {
-            if (!((fl >> (17 + neg)) & 1ull)) { o.off = true; break; }
+            if (!((fl >> (17 + neg)) & 1u)) { o.off = true; break; }
             const int k = nh & 3;
-            if (k == 0) {
+            if (k == 0 && nh >= 4) {
                 if (nh == 4) wa = wb;
-                if (nh >= 8) wa = philox10(id0, id1, (uint32_t)(nh >> 2), 1u, sc.key0, key1);
+                else wa = philox10(id0, id1, (uint32_t)(nh >> 2), 1u, sc.key0, key1);
             }
-            const uint32_t word = k == 0 ? wa.x : k == 1 ? wa.y : k == 2 ? wa.z : wa.w;
+            const uint32_t word = (k & 2) ? ((k & 1) ? wa.w : wa.z) : ((k & 1) ? wa.y : wa.x);
             const int refl = word < pl.thr[hit] ? 1 : 0;
-            on_hit(nh, g[DG_KAP + neg], hit_word(hit, dn < 0.0 ? 1 : 0, refl, neg, e, nt));
+            on_hit(nh, dt.g + e * kDirGeo + DG_KAP + neg, hit_word(hit, dn < 0.0 ? 1 : 0, refl, neg, e, nt));
             on_hit.branch(hit, refl != 0);
             nt = 0;
             ++nh;
@@ -294,11 +292,17 @@ __device__ inline void dir_walk(const SceneDev& sc, const PointLds& pl, const Di
                 if (c == kDirOff) { o.off = true; break; }
                 e = c >> 1;
                 neg = c & 1;
+                load();
             } else {
                 cell += hit == cell ? 1 : -1;
             }
-            last = hit;
         }
+    }
+    if (o.cat == CAT_LOST && nev >= Kmax && !o.off) o.cat = CAT_TRUNC;
+    if (o.cat == CAT_EYEBOX) {
+        const double* f = dt.f + e * kDirFld;
+        o.bin = eyebox_cell(sc, pl, px + f[DF_EX], py + f[DF_EY]);
+        if (o.bin < 0) o.cat = CAT_MISS;
     }
     o.nev = nev; o.nh = nh; o.e = e; o.neg = neg; o.nt = nt;
 }

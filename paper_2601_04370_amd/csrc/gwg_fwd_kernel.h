@@ -29,18 +29,19 @@
 // direction table, take the general walks instead (walk_ray, with the tape
 // of every event and reverse_sweep): the same paths, branches and bins.
 
-// Thin-film coefficients of one hit for this lane (fills the lane's slot table).
-template <int MODE, class SL, class Stks>
-__device__ inline Coef4 hit_solve(const SceneDev& sc, const PointLds& pl, const Stks& stks,
+// Thin-film coefficients of one hit for this lane (fills the lane's slot
+// table).  TAKEN: only the taken pair (refl), returned as both.
+template <int MODE, bool TAKEN = false, class SL, class Stks>
+__device__ inline Coef4 hit_solve(int n_slots, uint32_t cplx, const PointLds& pl, const Stks& stks,
                                   const SL& sl, int m, bool front, double kappa,
-                                  bool* used_fp64, double* ck = nullptr, int64_t ckb = 8)
+                                  bool* used_fp64, double* ck = nullptr, int64_t ckb = 8, bool refl = false)
 {
     bool hyp = false;                       // an evanescent lossless slot at this kappa
-    for (int s = 0; s < sc.n_slots; ++s) {
+    for (int s = 0; s < n_slots; ++s) {
         double P[NPF];
         slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], kappa, pl.k0, P);
         sl.put(s, P);
-        hyp |= !((sc.slot_complex >> s) & 1u) && P[0] < 0.0;
+        hyp |= !((cplx >> s) & 1u) && P[0] < 0.0;
     }
     const bool circ = __ballot(hyp) == 0ull;
     const double z0 = pl.ng * pl.ng - kappa * kappa;
@@ -48,14 +49,14 @@ __device__ inline Coef4 hit_solve(const SceneDev& sc, const PointLds& pl, const 
     const double eta0s = q0, eta0p = pl.ng * pl.ng / q0;
     const int L = pl.nlay[m];
     const auto stk = stks.mirror(m);
-    const bool fp64 = (MODE == GWG_FP64) || (MODE == GWG_FP32_MIXED && near_critical(pl, sc.n_slots, kappa));
+    const bool fp64 = (MODE == GWG_FP64) || (MODE == GWG_FP32_MIXED && near_critical(pl, n_slots, kappa));
     *used_fp64 = fp64;
     if (fp64)
-        return tmm_solve<double>(stk, L, front, sl, sc.slot_complex, pl.k0, eta0s, eta0p,
+        return tmm_solve<double, TAKEN>(stk, L, front, sl, cplx, pl.k0, eta0s, eta0p,
                                  mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ, MODE == GWG_FP64 ? ck : nullptr,
-                                 ckb, ck_interval(hyp));
-    return tmm_solve<float>(stk, L, front, sl, sc.slot_complex, pl.k0, eta0s, eta0p,
-                            mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ);
+                                 ckb, ck_interval(hyp), refl);
+    return tmm_solve<float, TAKEN>(stk, L, front, sl, cplx, pl.k0, eta0s, eta0p,
+                            mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ, nullptr, 8, kSegL, refl);
 }
 
 // Dense hit p (the wave's hits in ray order) belongs to the largest lane
@@ -90,7 +91,7 @@ __device__ inline void solve_hits(const SceneDev& sc, const PointLds& pl, const 
             const int meta = hq.meta(q);
             const int m = meta & 255;
             bool u64 = false;
-            const Coef4 c = hit_solve<MODE>(sc, pl, stks, sl, m, (meta >> 8) & 1, kappa, &u64);
+            const Coef4 c = hit_solve<MODE>(sc.n_slots, sc.slot_complex, pl, stks, sl, m, (meta >> 8) & 1, kappa, &u64);
             hq.put_coef(q, c);
             *n_fp64 += u64 ? 1ull : 0ull;
             *n_lay += (unsigned long long)pl.nlay[m];
@@ -136,53 +137,106 @@ __device__ inline void wave_lds_sync()
 
 // ----------------------------------------------------- pooled rounds
 // A wave's queue holds the hits of a pool of rounds: ncol = 64 sc.pool
-// columns (one per ray) of Kmax slots, hit h of column col in slot
-// h * ncol + col of each field.  The geometry walk writes fields 0 (kappa)
-// and 1 (word), the per-hit solves read them in the order of field 8 and
-// write each hit's taken coefficients (c_s, c_p: fields 2-5) and word (field
-// 6) in the slot of the ray's place in the field-pass order (column pos), so
-// that the lanes of a field pass read adjacent slots.  Field 7: the
-// checkpoint slot of the hit's adjoint entry, or -1.
-constexpr int kPoolFields = 9;
+// columns (one per ray) of Kmax slots.  The geometry walk writes hit h of
+// column col to slot h * ncol + col of kap (kappa) and word (its word); the
+// per-hit solves read them in the order of ord (h << 16 | col), the
+// checkpoint slot of the hit's adjoint entry (relative to the wave's region,
+// or -1) from ck, and write the hit's taken coefficients and word at the
+// ray's place pos in the field-pass order: word to slot h * ncol + pos of
+// tword, (c_s, c_p) as two 16-byte words to tcoef, the 64 lanes of a field
+// pass side by side, so that its loads are whole cache lines.
+struct PoolQueue {
+    double* kap;
+    double2* tcoef;              // [Kmax][pool][2][64]
+    int32_t *word, *tword, *ord, *ck;
+    int64_t* info;               // [ncol] adjoint entry position << 16 | length class << 1 | bound for the eyebox
+    int64_t* fate;               // [ncol] see fate_word
+    int32_t *bin, *pos, *at;     // [ncol] bin, place of a column, column at a place
+    int ncol, cap;               // cap: slots (ncol Kmax)
+    __device__ double2* coef(int h, int place) const
+    {
+        return tcoef + ((int64_t)h * (ncol >> 6) + (place >> 6)) * 128 + (place & 63);
+    }
+    // a hit's taken coefficients and word to the slots of its ray's place
+    __device__ void put_taken(int h, int place, const Coef4& c, int w) const
+    {
+        const bool rf = (w >> 9) & 1;
+        const cd cs = rf ? c.rs : c.ts, cp = rf ? c.rp : c.tp;
+        double2* o = coef(h, place);
+        o[0] = make_double2(cs.re, cs.im);
+        o[64] = make_double2(cp.re, cp.im);
+        tword[h * ncol + place] = w;
+    }
+};
 constexpr int kSortBins = 128;                      // field-pass length classes
 constexpr int kStatCols = 16;                       // columns of the statistics' LDS counters
 
-// doubles of global scratch per wave: the hit queue, then per column two
-// 64-bit words (carried data, fate) and three 32-bit words (bin, place in
-// the order, column at each place)
+// doubles of global scratch per wave: per slot kappa, the coefficients and
+// four 32-bit words, per column two 64-bit and three 32-bit words
 __host__ __device__ inline int64_t fwd_wave_doubles(const SceneDev& sc)
 {
-    return (int64_t)kPoolFields * 64 * sc.pool * sc.Kmax + 4 * 64 * sc.pool;
+    return (int64_t)7 * 64 * sc.pool * sc.Kmax + 4 * 64 * sc.pool;
+}
+__device__ inline PoolQueue pool_queue(double* mem, int pool, int Kmax)
+{
+    PoolQueue q;
+    q.ncol = 64 * pool;
+    q.cap = q.ncol * Kmax;
+    const int64_t n = q.cap;
+    q.tcoef = (double2*)mem;
+    q.kap = mem + 4 * n;
+    q.word = (int32_t*)(q.kap + n);
+    q.tword = q.word + n;
+    q.ord = q.tword + n;
+    q.ck = q.ord + n;
+    q.info = (int64_t*)(q.ck + n);
+    q.fate = q.info + q.ncol;
+    q.bin = (int32_t*)(q.fate + q.ncol);
+    q.pos = q.bin + q.ncol;
+    q.at = q.pos + q.ncol;
+    return q;
+}
+
+// A ray's fate: category (3 bits), walked in general (1), first field along
+// p (1), mirror hits (9), events (9), final state (8), total reflections
+// since the last hit (9).
+__device__ inline int64_t fate_word(const DirFate& o)
+{
+    return (int64_t)(o.cat | (o.off ? 8 : 0) | o.pol << 4 | o.nh << 5 | o.nev << 14) | (int64_t)o.e << 23 |
+           (int64_t)o.nt << 31;
 }
 
 // Writes the ray's hits to its column.  Also counts the hits whose kappa^2
 // exceeds kap2 (they may meet an evanescent layer) in *ne and marks hits
 // h < 64 of them in bit h of *evm.
 struct PutHitP {
-    HitQueue q;
-    int col, ncol;
+    PoolQueue q;
+    int col;
     double kap2;
     int* ne;
     unsigned long long* evm;
     __device__ void operator()(int h, double kappa, int word) const
     {
-        q.put(h * ncol + col, kappa, word);
+        q.kap[h * q.ncol + col] = kappa;
+        q.word[h * q.ncol + col] = word;
         if (kappa * kappa > kap2) {
             ++*ne;
             if (h < 64) *evm |= 1ull << h;
         }
     }
+    __device__ void operator()(int h, const double* kappa, int word) const { (*this)(h, *kappa, word); }
     __device__ void branch(int, bool) const {}
 };
-// Keyed forwards: writes the hits and marks their keys in the item's LDS
-// bit set (the read first: most hits find their key marked).
+// Keyed forwards: writes the words (kappa follows from the state) and marks
+// their keys in the item's LDS bit set (the read first: most hits find their
+// key marked).
 struct PutHitK {
-    HitQueue q;
-    int col, ncol, M;
+    PoolQueue q;
+    int col, M;
     uint32_t* used;
-    __device__ void operator()(int h, double kappa, int word) const
+    __device__ void operator()(int h, const double*, int word) const
     {
-        q.put(h * ncol + col, kappa, word);
+        q.word[h * q.ncol + col] = word;
         const int key = hit_key(word, M);
         if (!((used[key >> 5] >> (key & 31)) & 1u)) atomicOr(&used[key >> 5], 1u << (key & 31));
     }
@@ -192,67 +246,98 @@ struct PutHitK {
 // order: the taken pair (c_s, c_p) returned as both the reflected and the
 // transmitted one, and the branch.
 struct GetCoefP {
-    HitQueue q;
-    int pos, ncol;
+    PoolQueue q;
+    int pos;
     static constexpr bool kStoredBranch = true;
-    __device__ bool refl(int h) const { return ((int)q.base[6 * (int64_t)q.cap + h * ncol + pos] >> 9) & 1; }
+    __device__ bool refl(int h) const { return (q.tword[h * q.ncol + pos] >> 9) & 1; }
     __device__ Coef4 operator()(int h, double, double, double, int, bool) const
     {
-        const double* b = q.base + 2 * (int64_t)q.cap + h * ncol + pos;
-        const int64_t c = q.cap;
+        const double2* b = q.coef(h, pos);
+        const double2 s = b[0], p = b[64];
         Coef4 o;
-        o.rs = o.ts = mk(b[0], b[c]);
-        o.rp = o.tp = mk(b[2 * c], b[3 * c]);
+        o.rs = o.ts = mk(s.x, s.y);
+        o.rp = o.tp = mk(p.x, p.y);
         return o;
     }
 };
 
-// A hit's taken coefficients and word to the slot of its ray's place.
-__device__ inline void put_taken(const HitQueue& hq, int slot, const Coef4& c, int word)
-{
-    const bool rf = (word >> 9) & 1;
-    double* o = hq.base + 2 * (int64_t)hq.cap + slot;
-    const int64_t cc = hq.cap;
-    const cd cs = rf ? c.rs : c.ts, cp = rf ? c.rp : c.tp;
-    o[0] = cs.re; o[cc] = cs.im; o[2 * cc] = cp.re; o[3 * cc] = cp.im;
-    o[4 * cc] = (double)word;
-}
+// LDS pointers as the out-of-line solves take them: their address space is
+// part of the type, or their loads would be flat ones.
+typedef __attribute__((address_space(3))) void* LdsPtr;
+__device__ inline LdsPtr lds_ptr(const void* p) { return (LdsPtr)p; }
 
-// Solve a pool's ne + nc queued hits in batches of 64 (one per lane): field
-// 8 lists the possibly evanescent hits' slots from its front (positions
-// 0 .. ne-1) and the others' from its back (cap-1 down to cap-nc), so the
-// batches of the second kind take the circular-only sweep.  colpos[col]:
-// the place of column col in the field-pass order, where the hit's taken
-// coefficients go.  ck (non-null): the checkpoint store; a hit whose field
-// 7 holds a slot c >= 0 stores its sweep checkpoints there.
-template <int MODE, class SL, class Stks>
-__device__ inline void solve_pool(const SceneDev& sc, const PointLds& pl, const Stks& stks, const SL& sl,
-                                  const HitQueue& hq, int ncol, const int32_t* colpos, int ne, int nc,
-                                  unsigned long long* n_fp64, unsigned long long* n_lay, double* ck, int64_t ck_total)
+// What the solves of one item read, and where they count.
+struct SolveCtx {
+    LdsPtr pl, rec, sp, st;      // PointLds, the stacks' records, this lane's slot table, statistics
+    int Lmax, n_slots;
+    uint32_t cplx;               // absorbing slots
+};
+
+// Solve a pool's ne + nc queued hits in batches of 64 (one per lane): ord
+// lists the possibly evanescent hits from its front (positions 0 .. ne-1)
+// and the others from its back (cap-1 down to cap-nc), so the batches of the
+// second kind take the circular-only sweep.  ck (non-null): the checkpoint
+// store of the wave's region; a hit whose slot c >= 0 stores its sweep
+// checkpoints there.
+// Out of line: the layer loop needs some 50 scalar registers for its
+// polynomials, and inlined among the walks it had 20 of them reloaded from
+// vector lanes in every four layers (211 vector instructions where 188 are
+// needed; 6 mirrors of 200 layers, 1.1e10 layer steps: 19.9 -> 18.8 ms).
+template <int MODE, class SL>
+__device__ __attribute__((noinline)) void solve_pool(SolveCtx cx, double* mem, int pool, int Kmax, int ne, int nc,
+                                                     double* ck, int64_t ck_total)
 {
+    const PointLds& pl = *(const PointLds*)cx.pl;
+    const RecStacks stks = { (const LayerRec*)cx.rec, cx.Lmax };
+    const SL sl = { (double*)cx.sp, pl.nsq, pl.pxy };
+    unsigned long long* st = (unsigned long long*)cx.st;
+    const int n_slots = __builtin_amdgcn_readfirstlane(cx.n_slots);
+    const uint32_t cplx = (uint32_t)__builtin_amdgcn_readfirstlane((int)cx.cplx);
+    const PoolQueue q = pool_queue(mem, pool, Kmax);
     const int lane = wave_lane();
-    const int total = ne + nc;
-    const double* ord = hq.base + 8 * (int64_t)hq.cap;
+    const int total = __builtin_amdgcn_readfirstlane(ne + nc);
+    unsigned long long n_fp64 = 0, n_lay = 0;
     for (int b = 0; b < total; b += 64) {
         const int p = b + lane;
         if (p < total) {
-            const int q = (int)ord[p < ne ? p : hq.cap - 1 - (p - ne)];
-            const double kappa = hq.kappa(q);
-            const int word = hq.meta(q);
+            const int hc = q.ord[p < ne ? p : q.cap - 1 - (p - ne)], h = hc >> 16, col = hc & 0xffff;
+            const int slot = h * q.ncol + col;
+            const double kappa = q.kap[slot];
+            const int word = q.word[slot];
+            const int place = q.pos[col];
             const int m = word & 255;
             bool u64 = false;
             double* ckp = nullptr;
             if (ck) {
-                const double c = hq.base[7 * (int64_t)hq.cap + q];
-                if (c >= 0.0) ckp = ck + (int64_t)c * 8;
+                const int c = q.ck[slot];
+                if (c >= 0) ckp = ck + (int64_t)c * 8;
             }
-            const Coef4 c = hit_solve<MODE>(sc, pl, stks, sl, m, (word >> 8) & 1, kappa, &u64, ckp, 8 * ck_total);
-            const int h = q / ncol, col = q - h * ncol;
-            put_taken(hq, h * ncol + colpos[col], c, word);
-            *n_fp64 += u64 ? 1ull : 0ull;
-            *n_lay += (unsigned long long)pl.nlay[m];
+            const Coef4 c = hit_solve<MODE, true>(n_slots, cplx, pl, stks, sl, m, (word >> 8) & 1, kappa, &u64, ckp,
+                                                  8 * ck_total, (word >> 9) & 1);
+            q.put_taken(h, place, c, word);
+            n_fp64 += u64 ? 1ull : 0ull;
+            n_lay += (unsigned long long)pl.nlay[m];
         }
     }
+    if (n_fp64) atomicAdd(&st[ST_FP64], n_fp64);
+    if (n_lay) atomicAdd(&st[ST_LAYERS], n_lay);
+}
+
+// One hit (one per lane), out of line for the keyed forwards.
+template <int MODE, class SL>
+__device__ __attribute__((noinline)) Coef4 solve_one(SolveCtx cx, double kappa, int m, bool front)
+{
+    const PointLds& pl = *(const PointLds*)cx.pl;
+    const RecStacks stks = { (const LayerRec*)cx.rec, cx.Lmax };
+    const SL sl = { (double*)cx.sp, pl.nsq, pl.pxy };
+    unsigned long long* st = (unsigned long long*)cx.st;
+    bool u64 = false;
+    const Coef4 c = hit_solve<MODE>(__builtin_amdgcn_readfirstlane(cx.n_slots),
+                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)cx.cplx), pl, stks, sl, m, front, kappa,
+                                    &u64);
+    if (u64) atomicAdd(&st[ST_FP64], 1ull);
+    atomicAdd(&st[ST_LAYERS], (unsigned long long)pl.nlay[m]);
+    return c;
 }
 
 // ------------------------------------------------------- keyed coefficients
@@ -333,38 +418,38 @@ __device__ inline bool key_resolve(const KeyLds& kl, const DirLds& dt, int M, in
 }
 
 // ------------------------------------------------------------ field passes
-// The taken coefficients of a table ray's hit h, in two steps so that the
-// loads of the next hit run ahead: word(h), then coef(h, word, ...).
-struct HitCoefs {                      // per-hit solves: the queue's slots at place pos
-    HitQueue q;
-    int pos, ncol;
-    __device__ int word(int h) const { return (int)q.base[6 * (int64_t)q.cap + h * ncol + pos]; }
-    __device__ void coef(int h, int, cd& cs, cd& cp) const
+// One hit of a table ray as the field passes read it.
+struct HitRec { int word; double2 cs, cp; };
+// Per-hit solves: the queue's slots at place pos.
+struct HitCoefs {
+    PoolQueue q;
+    int pos;
+    __device__ HitRec operator()(int h) const
     {
-        const double* b = q.base + 2 * (int64_t)q.cap + h * ncol + pos;
-        const int64_t c = q.cap;
-        cs = mk(b[0], b[c]);
-        cp = mk(b[2 * c], b[3 * c]);
+        const double2* b = q.coef(h, pos);
+        return { q.tword[h * q.ncol + pos], b[0], b[64] };
     }
 };
-struct KeyCoefs {                      // keyed: the word in the ray's column, the key's coefficients in LDS
-    HitQueue q;
-    int col, ncol, M;
+// Keyed: the word in the ray's column, the key's coefficients in LDS.
+struct KeyCoefs {
+    PoolQueue q;
+    int col, M;
     const uint8_t* slot;
     const double* kc;
-    __device__ int word(int h) const { return q.meta(h * ncol + col); }
-    __device__ void coef(int, int word, cd& cs, cd& cp) const
+    __device__ HitRec operator()(int h) const
     {
-        const double* b = kc + 8 * slot[hit_key(word, M)] + (((word >> 9) & 1) ? 0 : 4);
-        cs = mk(b[0], b[1]);
-        cp = mk(b[2], b[3]);
+        const int w = q.word[h * q.ncol + col];
+        const double2* b = (const double2*)(kc + 8 * slot[hit_key(w, M)] + (((w >> 9) & 1) ? 0 : 4));
+        return { w, b[0], b[1] };
     }
 };
 
-// Field of one ray of the table from its birth to its end, over its nh hits
-// (lanes without a ray: nh = 0).  Writes the incoming field's mirror
-// components of hit h to the tape where tape.mr is set; returns the field at
-// the ray's last state, before an exit.
+// Field of one ray of the table from its birth to its end, over its nh hits.
+// Hits are requested three ahead of their use: their coefficients come from
+// HBM (a pool's hits are more than the L2), a latency of several hits' work
+// (requested one ahead, 8-byte words: 11.7 ms for 4.3e8 hits; so: 6.1 ms).
+// Writes the incoming field's mirror components of hit h to the tape where
+// tape.mr is set; returns the field at the ray's last state, before an exit.
 template <class Coefs>
 __device__ inline FaceSp dir_field(const PointLds& pl, const DirLds& dt, int pol, int nh, int e_end, int nt_end,
                                    const Coefs& src, const TapeRef& tape)
@@ -376,25 +461,26 @@ __device__ inline FaceSp dir_field(const PointLds& pl, const DirLds& dt, int pol
         const cd rs = mk(f[DF_RS], f[DF_RS + 1]), rp = mk(f[DF_RP], f[DF_RP + 1]);
         for (int k = 0; k < n; ++k) { a.s = cmul_f(rs, a.s); a.p = cmul_f(rp, a.p); }
     };
-    int wd = 0, wn = 0;
-    cd cs, cp, ns, np;
-    cs = cp = ns = np = mk(0.0, 0.0);
-    if (nh > 0) { wn = src.word(0); src.coef(0, wn, ns, np); }
+    HitRec n1{}, n2{}, n3{};
+    if (nh > 0) n1 = src(0);
+    if (nh > 1) n2 = src(1);
+    if (nh > 2) n3 = src(2);
     for (int h = 0; h < nh; ++h) {
-        wd = wn; cs = ns; cp = np;
-        if (h + 1 < nh) { wn = src.word(h + 1); src.coef(h + 1, wn, ns, np); }
-        const int e = (wd >> 11) & 255, neg = (wd >> 10) & 1, m = wd & 255;
-        const bool rf = (wd >> 9) & 1;
+        const HitRec r = n1;
+        n1 = n2; n2 = n3;
+        if (h + 3 < nh) n3 = src(h + 3);
+        const int e = (r.word >> 11) & 255, neg = (r.word >> 10) & 1, m = r.word & 255;
+        const bool rf = (r.word >> 9) & 1;
         const double* f = dt.f + e * kDirFld;
-        tir(f, wd >> 19);
+        tir(f, r.word >> 19);
         double c = f[DF_ROT + 2 * neg], d = f[DF_ROT + 2 * neg + 1];
         FaceSp b = to_mirror(a, c, d);
         if (tape.mr) tape_put_mirror(tape, h, b.s, b.p);
         const double scale = rf ? pl.sc_r[m] : pl.sc_t[m];
-        b.s = cscale(cmul_f(cs, b.s), scale);
-        b.p = cscale(cmul_f(cp, b.p), scale);
+        b.s = cscale(cmul_f(mk(r.cs.x, r.cs.y), b.s), scale);
+        b.p = cscale(cmul_f(mk(r.cp.x, r.cp.y), b.p), scale);
         if (rf) {
-            const unsigned long long fl = (unsigned long long)__double_as_longlong(dt.g[e * kDirGeo + DG_FLAGS]);
+            const uint32_t fl = (uint32_t)__double_as_longlong(dt.g[e * kDirGeo + DG_FLAGS]);
             const int ch = (int)(fl >> (8 * neg)) & 255;
             const double* fc = dt.f + (ch >> 1) * kDirFld + DF_ROT + 2 * (ch & 1);
             c = fc[0]; d = fc[1];
@@ -408,10 +494,13 @@ __device__ inline FaceSp dir_field(const PointLds& pl, const DirLds& dt, int pol
 // Reverse field sweep of one ray of the table that left through the exit
 // (the adjoint of dir_field and the exit for w = |E|^2): a is the field
 // after the exit.  Calls emit(kappa, G_s, G_p, word) for every mirror hit,
-// last to first, with the cotangents of reverse_sweep.
+// last to first, with the cotangents of reverse_sweep.  As in that sweep the
+// lanes step a common hit index down from nhw - 1, the longest of the
+// calling lanes' (nh = 0: none), so that they read the same tape record
+// together.
 template <class Coefs, class Emit>
-__device__ inline void dir_reverse(const PointLds& pl, const DirLds& dt, FaceSp a, int nh, int e_end, int nt_end,
-                                   const Coefs& src, const TapeRef& tape, Emit emit)
+__device__ inline void dir_reverse(const PointLds& pl, const DirLds& dt, FaceSp a, int nh, int nhw, int e_end,
+                                   int nt_end, const Coefs& src, const TapeRef& tape, Emit emit)
 {
     auto tir = [&](const double* f, int n) {
         const cd rs = mk(f[DF_RS], -f[DF_RS + 1]), rp = mk(f[DF_RP], -f[DF_RP + 1]);
@@ -421,29 +510,32 @@ __device__ inline void dir_reverse(const PointLds& pl, const DirLds& dt, FaceSp 
     a.s = cscale(a.s, fx[DF_XS]);
     a.p = cscale(a.p, fx[DF_XP]);
     tir(fx, nt_end);
-    struct Next { int wd; cd cs, cp; double2 t0, t1; } nx;
-    nx.wd = 0;
-    nx.cs = nx.cp = mk(0.0, 0.0);
-    nx.t0 = nx.t1 = make_double2(0.0, 0.0);
+    struct Rec { HitRec r; double2 t0, t1; };
     auto fetch = [&](int h) {
-        nx.wd = src.word(h);
-        src.coef(h, nx.wd, nx.cs, nx.cp);
-        const double2* p = (const double2*)(tape.mr + (int64_t)h * (tape.ks / 2));
-        nx.t0 = p[0];
-        nx.t1 = p[64];
+        Rec x{};
+        if (h >= 0 && h < nh) {
+            x.r = src(h);
+            const double2* p = (const double2*)(tape.mr + (int64_t)h * (tape.ks / 2));
+            x.t0 = p[0];
+            x.t1 = p[64];
+        }
+        return x;
     };
-    if (nh > 0) fetch(nh - 1);
-    for (int h = nh - 1; h >= 0; --h) {
-        const Next ev = nx;
-        if (h > 0) fetch(h - 1);
-        const int e = (ev.wd >> 11) & 255, neg = (ev.wd >> 10) & 1, m = ev.wd & 255;
-        const bool rf = (ev.wd >> 9) & 1;
+    Rec n1 = fetch(nhw - 1), n2 = fetch(nhw - 2);
+    for (int h = nhw - 1; h >= 0; --h) {
+        const Rec ev = n1;
+        n1 = n2;
+        n2 = fetch(h - 2);
+        if (h >= nh) continue;                          // this lane has fewer hits
+        const int wd = ev.r.word;
+        const int e = (wd >> 11) & 255, neg = (wd >> 10) & 1, m = wd & 255;
+        const bool rf = (wd >> 9) & 1;
         const double* g = dt.g + e * kDirGeo;
         const double* f = dt.f + e * kDirFld;
         const double c = f[DF_ROT + 2 * neg], d = f[DF_ROT + 2 * neg + 1];
         double co = c, so = d;
         if (rf) {
-            const int ch = (int)((unsigned long long)__double_as_longlong(g[DG_FLAGS]) >> (8 * neg)) & 255;
+            const int ch = (int)((uint32_t)__double_as_longlong(g[DG_FLAGS]) >> (8 * neg)) & 255;
             const double* fc = dt.f + (ch >> 1) * kDirFld + DF_ROT + 2 * (ch & 1);
             co = fc[0]; so = fc[1];
         }
@@ -451,20 +543,132 @@ __device__ inline void dir_reverse(const PointLds& pl, const DirLds& dt, FaceSp 
         FaceSp b = to_mirror(a, co, so);
         const cd Gs = cscale(cmul_f(cconj(b.s), mk(ev.t0.x, ev.t0.y)), scale);
         const cd Gp = cscale(cmul_f(cconj(b.p), mk(ev.t1.x, ev.t1.y)), scale);
-        emit(g[DG_KAP + neg], Gs, Gp, ev.wd & 1023);
-        b.s = cscale(cmul_f(cconj(ev.cs), b.s), scale);
-        b.p = cscale(cmul_f(cconj(ev.cp), b.p), scale);
+        emit(g[DG_KAP + neg], Gs, Gp, wd & 1023);
+        b.s = cscale(cmul_f(mk(ev.r.cs.x, -ev.r.cs.y), b.s), scale);
+        b.p = cscale(cmul_f(mk(ev.r.cp.x, -ev.r.cp.y), b.p), scale);
         a = to_face(b, c, d);
-        tir(f, ev.wd >> 19);
+        tir(f, wd >> 19);
     }
+}
+
+// ------------------------------------------------------------ general walks
+// Where a forward's adjoint entries of one wave and item go.
+struct EntryOut {
+    double* ent;                 // the region's first entry
+    int64_t cap_w;
+    double gmax;                 // largest cotangent component (angle table)
+    unsigned long long n;        // entries emitted
+    __device__ void put(int64_t k, double kappa, cd Gs, cd Gp, int64_t meta, bool track)
+    {
+        if (track) {
+            const double a = fmax(fmax(fabs(Gs.re), fabs(Gs.im)), fmax(fabs(Gp.re), fabs(Gp.im)));
+            gmax = a > gmax ? a : gmax;
+            ++n;
+        }
+        if (k < cap_w) {
+            double2* e = (double2*)(ent + k * kEntFields);
+            e[0] = make_double2(kappa, Gs.re);
+            e[1] = make_double2(Gs.im, Gp.re);
+            e[2] = make_double2(Gp.im, (double)meta);
+        }
+    }
+};
+
+// Geometry walk of one ray (this lane's, if mine): hits to its column.
+__device__ inline void general_geometry(const SceneDev& sc, const PointLds& pl, int64_t id, const PoolQueue& q,
+                                        int col, DirFate& o, int& ne, unsigned long long& evm)
+{
+    Ray r;
+    Outcome oc;
+    TapeRef none = { nullptr, nullptr, 0 };
+    ne = 0;
+    evm = 0ull;
+    ray_birth(sc, pl, id, r);
+    walk_ray<false, false>(sc, pl, r, oc, PutHitP{ q, col, pl.kap2_evan, &ne, &evm }, NoCoef{}, none, nullptr);
+    o.cat = oc.cat; o.bin = oc.bin; o.nev = r.nev; o.nh = r.nprma;
+    o.off = true;
+}
+
+// Field walk of the rays at places pos (lanes with mine), with the tape of
+// every event and, where eye, the reverse sweep and its entries.  All lanes
+// of the wave call.
+template <bool ADJ>
+__device__ inline void general_field(const SceneDev& sc, const PointLds& pl, int64_t id, const PoolQueue& q, int pos,
+                                     bool mine, bool eye, const TapeRef& tape, int64_t kent, int64_t meta_bin,
+                                     bool track, EntryOut& out, double& w, double& w_in)
+{
+    Ray r;
+    Outcome o;
+    int nt = 0;
+    if (mine) {
+        ray_birth(sc, pl, id, r);
+        const TapeRef rt = { ADJ && eye ? tape.ev : nullptr, tape.mr, tape.ks };
+        walk_ray<true, ADJ>(sc, pl, r, o, NoHit{}, GetCoefP{ q, pos }, rt, &nt);
+        w = o.w; w_in = o.w_in;
+    }
+    if constexpr (ADJ) {
+        const int ntw = wave_max_int(mine && eye ? nt : 0);
+        if (mine && eye) {
+            int64_t k = kent;
+            reverse_sweep(sc, pl, r.e, tape, nt, ntw, [&](double kappa, cd Gs, cd Gp, int meta) {
+                out.put(k++, kappa, Gs, Gp, meta_bin | (int64_t)meta, track);
+            });
+        }
+    }
+}
+
+// The same for the few rays of a collimated item that leave its direction
+// table, out of line (sc in LDS): inlined, their registers cost the kernel's
+// own loops spills.
+template <bool TAB>
+__device__ __attribute__((noinline)) void off_geometry(const SceneDev& sc, const PointLds& pl, int64_t id,
+                                                       const PoolQueue& q, int col, DirFate& o, int& ne,
+                                                       unsigned long long& evm)
+{
+    general_geometry(sc, pl, id, q, col, o, ne, evm);
+}
+template <bool ADJ, bool TAB>
+__device__ __attribute__((noinline)) void off_field(const SceneDev& sc, const PointLds& pl, int64_t id,
+                                                    const PoolQueue& q, int pos, bool mine, bool eye,
+                                                    const TapeRef& tape, int64_t kent, int64_t meta_bin, bool track,
+                                                    EntryOut& out, double& w, double& w_in)
+{
+    general_field<ADJ>(sc, pl, id, q, pos, mine, eye, tape, kent, meta_bin, track, out, w, w_in);
+}
+
+// ------------------------------------------------------------------- LDS
+// The table forward solves nothing: no stacks, and only the counting sort's
+// class counts in place of the slot tables.
+struct FwdLayout { int off_pl, off_rec, off_sp, off_q, off_c, off_st, off_col, off_sc, off_dir, off_key, total; };
+
+__host__ __device__ inline FwdLayout fwd_layout(const SceneDev& sc, int wg, bool lds_bins, bool dirs, bool tab, bool memo)
+{
+    const int B = sc.bins_x * sc.bins_y, waves = (wg + 63) / 64;
+    FwdLayout s;
+    int o = 0;
+    s.off_pl = o; o = align16(o + (int)sizeof(PointLds));
+    s.off_rec = o; o = align16(o + (tab ? 0 : (int)sizeof(LayerRec) * sc.M * rec_stride(sc.Lmax)));
+    s.off_sp = o;
+    o = align16(o + (tab ? 4 * kSortBins * waves
+                         : 8 * sc.n_slots * (memo ? LaneSlots3::kPer : LaneSlots3x::kPer) * 64 * waves));
+    s.off_q = o; o = align16(o + (lds_bins ? 8 * B : 0));
+    s.off_c = o; o = align16(o + (lds_bins ? 4 * B : 0));
+    s.off_st = o; o = align16(o + 8 * ST_WORDS);
+    s.off_col = o; o = align16(o + (NCAT + 2) * kStatCols * 8);
+    s.off_sc = o; o = align16(o + (dirs ? (int)sizeof(SceneDev) : 0));
+    s.off_dir = o; o = align16(o + (dirs ? kDirMax * kDirWords * 8 : 0));
+    s.off_key = o; o = align16(o + (dirs && (tab || memo) ? key_smem_bytes(sc.M) : 0));
+    s.total = o;
+    return s;
 }
 
 // Persistent workgroups draw work items; each wave handles a strided share
 // of the item's rays.  Eyebox bins of the current point accumulate in LDS
 // (integer atomics) and are flushed per item with integer global atomics:
-// the result does not depend on scheduling.
-template <int MODE, bool ADJ, bool TAB, bool MEMO>
-__global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __restrict__ q_out,
+// the result does not depend on scheduling.  DIRS: collimated beams with a
+// direction table (else every ray walks in general).
+template <int MODE, bool ADJ, bool TAB, bool MEMO, bool DIRS>
+__global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_fwd(SceneDev sc, uint64_t* __restrict__ q_out,
                                                    uint32_t* __restrict__ c_out,
                                                    unsigned long long* __restrict__ stats,
                                                    gwg_ray_record* __restrict__ rec, int64_t rec_stride,
@@ -475,39 +679,39 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
     const int B = sc.bins_x * sc.bins_y;
     const int WG = blockDim.x;
     const int n_waves = WG / 64;
-    constexpr bool KEYED = TAB || MEMO;
+    constexpr bool KEYED = DIRS && (TAB || MEMO);
     // slot table: all five values per lane, except with the keyed
     // coefficients, which solve few hits and keep their table in LDS
     using SlotTable = typename std::conditional<MEMO, LaneSlots3, LaneSlots3x>::type;
-    const SmemLayout lay = smem_layout(sc.M, sc.Lmax, sc.n_slots, WG, B, lds_bins != 0, 0, SlotTable::kPer, true);
+    const FwdLayout lay = fwd_layout(sc, WG, lds_bins != 0, DIRS, TAB, MEMO);
     PointLds* pl = (PointLds*)(smem + lay.off_pl);
-    LayerRec* s_rec = (LayerRec*)(smem + lay.off_thk);
-    const RecStacks stks = { s_rec, sc.Lmax };
+    LayerRec* s_rec = (LayerRec*)(smem + lay.off_rec);
     double* s_sp = (double*)(smem + lay.off_sp);
     unsigned long long* s_q = (unsigned long long*)(smem + lay.off_q);
     uint32_t* s_c = (uint32_t*)(smem + lay.off_c);
     unsigned long long* s_st = (unsigned long long*)(smem + lay.off_st);
     // statistics: per-ray sums in kStatCols columns per word, so that the
     // lanes of a wave add to different addresses
-    unsigned long long* s_col = (unsigned long long*)(smem + lay.total);        // power, events, mirror hits
-    double* s_dir = (double*)(s_col + (NCAT + 2) * kStatCols);
-    unsigned char* s_key = (unsigned char*)s_dir + dir_smem_bytes(sc);
-    const bool dirs = sc.dirs != nullptr;
+    unsigned long long* s_col = (unsigned long long*)(smem + lay.off_col);      // power, events, mirror hits
     const int tid = threadIdx.x, wave = tid / 64, lane = wave_lane();
+    // the ordering's class counts: in this wave's slot tables (at least 1.5
+    // KB), which only the solves use, or in LDS of their own
+    uint32_t* s_hist = (uint32_t*)(smem + lay.off_sp + wave * (TAB ? 4 * kSortBins : sc.n_slots * SlotTable::kPer * kSlotLanes * 8));
     const int64_t gwave = (int64_t)blockIdx.x * n_waves + wave;
-    const int cap = 64 * sc.pool * sc.Kmax;                // queue slots of a wave (a pool of rounds)
-    const HitQueue hq = { scratch + gwave * fwd_wave_doubles(sc), cap };
-    const SlotTable sl = { slot_lane_base(s_sp, sc.n_slots, SlotTable::kPer, tid), pl->nsq, pl->pxy };
+    double* pmem = scratch + gwave * fwd_wave_doubles(sc);
+    const PoolQueue pq = pool_queue(pmem, sc.pool, sc.Kmax);
+    const SolveCtx cx = { lds_ptr(pl), lds_ptr(s_rec), lds_ptr(slot_lane_base(s_sp, sc.n_slots, SlotTable::kPer, tid)),
+                          lds_ptr(s_st), sc.Lmax, sc.n_slots, sc.slot_complex };
     const double wscale = ldexp(1.0, sc.fp_shift), wcap = ldexp(1.0, 40), pscale = 16777216.0;
     for (int k = tid; k < ST_WORDS; k += WG) s_st[k] = 0ull;
     for (int k = tid; k < (NCAT + 2) * kStatCols; k += WG) s_col[k] = 0ull;
-    unsigned long long n_fp64 = 0, n_lay = 0;
+    SceneDev* s_sc = (SceneDev*)(smem + lay.off_sc);
+    if (DIRS && tid == 0) *s_sc = sc;                     // for the rays off the table
     const TapeRef tape = tape_lane(tape_scratch, sc.Kmax, (int64_t)gridDim.x * n_waves, gwave, lane);
     KeyLds kl{};
-    if constexpr (KEYED) kl = key_lds(s_key, sc.M);
+    if constexpr (KEYED) kl = key_lds(smem + lay.off_key, sc.M);
     const int key_cap = MEMO ? sc.memo : kFwdMemoKeys;
-    double t_gmax = 0.0;                                 // largest cotangent component (angle table)
-    unsigned long long t_ne = 0;                         // cotangent pairs emitted (angle table)
+    EntryOut out = { nullptr, st.cap_w, 0.0, 0ull };
 
     for (int64_t it = draw_item(stats + ST_NEXT0); it < sc.n_items; it = draw_item(stats + ST_NEXT0)) {
         const int64_t item = sc.fwd_order ? (int64_t)sc.fwd_order[it] : it;
@@ -516,7 +720,7 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
         decode_item(sc, item, &point, &d, &l, &f, &i0, &i1);
         stage_point(sc, d, l, f, pl, nullptr, nullptr, TAB ? nullptr : s_rec, SlotTable::kPer);
         DirLds dt{};
-        if (dirs) dt = stage_dirs(sc, (int64_t)l * sc.F + f, s_dir);
+        if constexpr (DIRS) dt = stage_dirs(sc, (int64_t)l * sc.F + f, (double*)(smem + lay.off_dir));
         int64_t n_work = 0;                               // this wave's mirror hits in this item (uniform)
         if (lds_bins)
             for (int k = tid; k < B; k += WG) { s_q[k] = 0ull; s_c[k] = 0u; }
@@ -529,19 +733,16 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
         uint64_t* gq = q_out + point * B;
         uint32_t* gc = c_out + point * B;
         int64_t n_ent = 0;                                // this wave's entries in this item (uniform)
-        bool keyed = KEYED && dirs;                       // the item's hits take their keys' coefficients (uniform)
-        const int64_t ent0 = (item * st.waves + wave) * st.cap_w;
+        bool keyed = KEYED;                               // the item's hits take their keys' coefficients (uniform)
+        const int64_t region = item * st.waves + wave;
+        out.ent = st.ent + region * st.cap_w * kEntFields;
         const double* tab_dl = TAB ? sc.table + (int64_t)(d * sc.n_lsel + l) * sc.M * 2 * sc.table_n * 8 : nullptr;
         // coefficients of one hit (one per lane)
         auto one_hit = [&](double kappa, int m, bool front) {
             if constexpr (TAB) {
                 return table_coef(tab_dl, sc.table_n, m, front, kappa, pl->ng);
             } else {
-                bool u64 = false;
-                const Coef4 c = hit_solve<MODE>(sc, *pl, stks, sl, m, front, kappa, &u64);
-                n_fp64 += u64 ? 1ull : 0ull;
-                n_lay += (unsigned long long)pl->nlay[m];
-                return c;
+                return solve_one<MODE, SlotTable>(cx, kappa, m, front);
             }
         };
         // Weight, eyebox scatter, statistics and record of a ray that ended
@@ -578,40 +779,14 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
                 if (n && lane == c) atomicAdd(&s_st[ST_CAT + c], (unsigned long long)n);
             }
         };
-        // one adjoint entry at position k of the wave's region
-        auto put_entry = [&](int64_t k, double kappa, cd Gs, cd Gp, int64_t meta) {
-            if constexpr (TAB) {
-                const double a = fmax(fmax(fabs(Gs.re), fabs(Gs.im)), fmax(fabs(Gp.re), fabs(Gp.im)));
-                t_gmax = a > t_gmax ? a : t_gmax;
-                ++t_ne;
-            }
-            if (k < st.cap_w) {
-                const int64_t e = ent0 + k;
-                st.ent[e] = kappa;
-                st.ent[1 * st.total + e] = Gs.re;
-                st.ent[2 * st.total + e] = Gs.im;
-                st.ent[3 * st.total + e] = Gp.re;
-                st.ent[4 * st.total + e] = Gp.im;
-                st.ent[5 * st.total + e] = (double)meta;
-            }
-        };
-        const int ncol = 64 * sc.pool;
         const int64_t first = i0 + (int64_t)wave * 64;
         const int n_rounds = first < i1 ? (int)((i1 - first + WG - 1) / WG) : 0;      // uniform
         const int n_rounds0 = (int)((i1 - i0 + WG - 1) / WG);                          // wave 0's, the most
-        // the ordering's class counts sit in this wave's slot tables, which
-        // only the solves use (each hit's solve fills its lane's table first)
-        uint32_t* s_hist = (uint32_t*)(s_sp + (int64_t)wave * sc.n_slots * SlotTable::kPer * kSlotLanes);
-        int64_t* colinfo = (int64_t*)(hq.base + (int64_t)kPoolFields * cap);        // [ncol] carried data
-        int64_t* colfate = colinfo + ncol;                                          // [ncol] fate
-        int32_t* colbin = (int32_t*)(colfate + ncol);                               // [ncol] bin
-        int32_t* colpos = colbin + ncol;                                            // [ncol] place of a column
-        int32_t* colord = colpos + ncol;                                            // [ncol] column at a place
-        const bool cks = ADJ && !KEYED && MODE == GWG_FP64 && st.ck != nullptr;
+        const bool cks = ADJ && !TAB && !MEMO && MODE == GWG_FP64 && st.ck != nullptr;
         for (int r0 = 0; r0 < (KEYED ? n_rounds0 : n_rounds); r0 += sc.pool) {
             const int nr = max(0, n_rounds - r0 < sc.pool ? n_rounds - r0 : sc.pool);
             int n_e = 0, n_c = 0;                         // the pool's possibly evanescent / other hits (uniform)
-            bool any_off = false;                         // some ray of the pool walks in general (uniform)
+            bool any_off = !DIRS;                         // some ray of the pool walks in general (uniform)
             for (int rr = 0; rr < nr; ++rr) {
                 const int col = rr * 64 + lane;
                 const int64_t i = first + (int64_t)(r0 + rr) * WG + lane;
@@ -621,31 +796,34 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
                 o.off = false;
                 int ne = 0;
                 unsigned long long evm = 0ull;             // bit h: hit h may meet an evanescent layer
-                if (active) {
-                    if (dirs) {
-                        if constexpr (KEYED) dir_walk(sc, *pl, dt, base + i, PutHitK{ hq, col, ncol, sc.M, kl.used }, o);
-                        else dir_walk(sc, *pl, dt, base + i, PutHitP{ hq, col, ncol, pl->kap2_evan, &ne, &evm }, o);
-                    } else {
-                        o.off = true;
+                if constexpr (DIRS) {
+                    if (active) {
+                        if constexpr (KEYED) dir_walk(sc, *pl, dt, base + i, PutHitK{ pq, col, sc.M, kl.used }, o);
+                        else dir_walk(sc, *pl, dt, base + i, PutHitP{ pq, col, pl->kap2_evan, &ne, &evm }, o);
                     }
-                    if (o.off) {
-                        Ray r;
-                        Outcome oc;
-                        TapeRef none = { nullptr, nullptr, 0 };
-                        ne = 0;
-                        evm = 0ull;
-                        ray_birth(sc, *pl, base + i, r);
-                        walk_ray<false, false>(sc, *pl, r, oc, PutHitP{ hq, col, ncol, pl->kap2_evan, &ne, &evm },
-                                               NoCoef{}, none, nullptr);
-                        o.cat = oc.cat; o.bin = oc.bin; o.nev = r.nev; o.nh = r.nprma;
+                    if (__ballot(o.off) != 0ull) {
+                        any_off = true;
+                        if (o.off) {
+                            // copies: only these go through memory
+                            const PoolQueue pq2 = pq;
+                            DirFate o2 = o;
+                            int ne2;
+                            unsigned long long evm2;
+                            off_geometry<TAB>(*s_sc, *pl, base + i, pq2, col, o2, ne2, evm2);
+                            o = o2; ne = ne2; evm = evm2;
+                        }
                     }
+                } else {
+                    if (active) general_geometry(sc, *pl, base + i, pq, col, o, ne, evm);
                 }
-                any_off |= __ballot(o.off) != 0ull;
                 const int nh = o.nh;
                 const bool to_eyebox = active && o.cat == CAT_EYEBOX;              // fixed by geometry alone
-                int total;
-                (void)wave_excl_scan(nh, &total);
-                n_work += total;
+                // offsets of this ray's possibly evanescent (low half) and
+                // other hits in the round's
+                int t2;
+                const int e2 = wave_excl_scan(ne | (nh - ne) << 16, &t2);
+                const int te = t2 & 0xffff, tc = t2 >> 16;
+                n_work += te + tc;
                 // the ray's adjoint entries (rays bound for the eyebox) start
                 // at kent of the wave's region; with a checkpoint store its
                 // hits learn their entries' checkpoint slots
@@ -654,33 +832,26 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
                     int etot;
                     const int eoff = wave_excl_scan(to_eyebox ? nh : 0, &etot);
                     kent = n_ent + eoff;
-                    if (cks)
-                        for (int h = 0; h < nh; ++h) {
-                            const int64_t k = kent + (nh - 1 - h);
-                            double c = -1.0;
-                            if (to_eyebox && k < st.ck_cap) c = (double)((item * st.waves + wave) * st.ck_cap + k);
-                            hq.base[7 * (int64_t)cap + h * ncol + col] = c;
-                        }
                     n_ent += etot;
                 }
-                if constexpr (!KEYED) {
+                if constexpr (!TAB && !KEYED) {
                     // solve order: the hits that may meet an evanescent layer
-                    // from the front of field 8, the others from its back
-                    int te, tc;
-                    const int eo = wave_excl_scan(ne, &te);
-                    const int co = wave_excl_scan(nh - ne, &tc);
-                    int pe = n_e + eo, pc = n_c + co;
+                    // from the front of ord, the others from its back
+                    int pe = n_e + (e2 & 0xffff), pc = n_c + (e2 >> 16);
                     for (int h = 0; h < nh; ++h) {
-                        const int q = h * ncol + col;
                         bool ev;
                         if (h < 64) {
                             ev = (evm >> h) & 1ull;
                         } else {
-                            const double k = hq.kappa(q);
+                            const double k = pq.kap[h * pq.ncol + col];
                             ev = k * k > pl->kap2_evan;
                         }
-                        const int pos = ev ? pe++ : cap - 1 - pc++;
-                        hq.base[8 * (int64_t)cap + pos] = (double)q;
+                        const int at = ev ? pe++ : pq.cap - 1 - pc++;
+                        pq.ord[at] = h << 16 | col;
+                        if (cks) {
+                            const int64_t k = kent + (nh - 1 - h);
+                            pq.ck[h * pq.ncol + col] = to_eyebox && k < st.ck_cap ? (int32_t)k : -1;
+                        }
                     }
                     n_e += te;
                     n_c += tc;
@@ -690,10 +861,9 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
                 const int len = o.off ? o.nev : nh;
                 const int cost = len + (to_eyebox ? len : 0);
                 const int key = active ? 1 + (cost < kSortBins - 2 ? cost : kSortBins - 2) : 0;
-                colinfo[col] = (kent << 16) | (int64_t)(key << 1) | (to_eyebox ? 1 : 0);
-                colfate[col] = (int64_t)o.cat | (int64_t)(o.off ? 1 : 0) << 3 | (int64_t)o.pol << 4 | (int64_t)nh << 5 |
-                               (int64_t)o.nev << 14 | (int64_t)o.e << 23 | (int64_t)o.nt << 31;
-                colbin[col] = o.bin;
+                pq.info[col] = (kent << 16) | (int64_t)(key << 1) | (to_eyebox ? 1 : 0);
+                pq.fate[col] = fate_word(o);
+                pq.bin[col] = o.bin;
             }
             __threadfence_block();
             // the field-pass order: the pool's columns by length class,
@@ -701,7 +871,7 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
             for (int k = lane; k < kSortBins; k += 64) s_hist[k] = 0u;
             wave_lds_sync();
             for (int rr = 0; rr < nr; ++rr) {
-                const int key = (int)((colinfo[rr * 64 + lane] >> 1) & 255);
+                const int key = (int)((pq.info[rr * 64 + lane] >> 1) & 255);
                 atomicAdd(&s_hist[key], 1u);
             }
             wave_lds_sync();
@@ -717,102 +887,104 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
             wave_lds_sync();
             for (int rr = 0; rr < nr; ++rr) {
                 const int col = rr * 64 + lane;
-                const int key = (int)((colinfo[col] >> 1) & 255);
+                const int key = (int)((pq.info[col] >> 1) & 255);
                 const int pos = (int)atomicAdd(&s_hist[key], 1u);
-                colpos[col] = pos;
-                colord[pos] = col;
+                pq.pos[col] = pos;
+                pq.at[pos] = col;
             }
-            wave_lds_sync();                              // the slot tables are the solves' again
+            wave_lds_sync();                              // s_hist is the solves' LDS again
             __threadfence_block();
-            if constexpr (KEYED) {
-                if (keyed) keyed = key_resolve(kl, dt, sc.M, key_cap, one_hit);
+            if constexpr (TAB || MEMO) {
+                if constexpr (KEYED) {
+                    if (keyed) keyed = key_resolve(kl, dt, sc.M, key_cap, one_hit);
+                }
                 if (!keyed || any_off) {
                     // hit by hit, each lane its own column's (rays off the
                     // direction table, or every ray without keys)
                     for (int rr = 0; rr < nr; ++rr) {
                         const int col = rr * 64 + lane;
-                        const int64_t fate = colfate[col];
-                        const int nh = (!keyed || ((fate >> 3) & 1)) ? (int)(fate >> 5) & 511 : 0;
-                        const int pos = colpos[col];
+                        const int64_t fate = pq.fate[col];
+                        const bool off = (fate >> 3) & 1;
+                        const int nh = !keyed || off ? (int)(fate >> 5) & 511 : 0;
+                        const int pos = pq.pos[col];
                         for (int h = 0; h < nh; ++h) {
-                            const int word = hq.meta(h * ncol + col);
-                            const Coef4 c = one_hit(hq.kappa(h * ncol + col), word & 255, (word >> 8) & 1);
-                            put_taken(hq, h * ncol + pos, c, word);
+                            const int word = pq.word[h * pq.ncol + col];
+                            const double kappa = off ? pq.kap[h * pq.ncol + col]
+                                                     : dt.g[((word >> 11) & 255) * kDirGeo + DG_KAP + ((word >> 10) & 1)];
+                            const Coef4 c = one_hit(kappa, word & 255, (word >> 8) & 1);
+                            pq.put_taken(h, pos, c, word);
                         }
                     }
                     __threadfence_block();
                 }
             } else {
-                solve_pool<MODE>(sc, *pl, stks, sl, hq, ncol, colpos, n_e, n_c, &n_fp64, &n_lay,
-                                 cks ? st.ck : nullptr, st.ck_total);
+                solve_pool<MODE, SlotTable>(cx, pmem, sc.pool, sc.Kmax, n_e, n_c,
+                                            cks ? st.ck + region * st.ck_cap * 8 : nullptr, st.ck_total);
                 __threadfence_block();
             }
             for (int s2 = 0; s2 < nr; ++s2) {
                 const int pos = s2 * 64 + lane;
-                const int col = colord[pos];
-                const int64_t info = colinfo[col], fate = colfate[col];
+                const int col = pq.at[pos];
+                const int64_t info = pq.info[col], fate = pq.fate[col];
                 const int64_t i = first + (int64_t)(r0 + col / 64) * WG + (col & 63);
                 const int64_t id = base + i;
                 const bool active = ((info >> 1) & 255) != 0, eye = (info & 1) != 0, off = (fate >> 3) & 1;
                 const int64_t kent = info >> 16;
-                int cat = (int)(fate & 7), bin = colbin[col], nev = (int)(fate >> 14) & 511, nh = (int)(fate >> 5) & 511;
+                const int cat = (int)(fate & 7), bin = pq.bin[col];
+                const int nev = (int)(fate >> 14) & 511, nh = (int)(fate >> 5) & 511;
                 const int64_t meta_bin = (int64_t)bin << 10;
                 double w = 0.0, w_in = 0.0;
-                const int e_end = (int)(fate >> 23) & 255, nt_end = (int)(fate >> 31) & 511;
-                auto table_ray = [&](const auto& src) {
-                    const TapeRef rt = { nullptr, ADJ && eye ? tape.mr : nullptr, tape.ks };
-                    FaceSp a = dir_field(*pl, dt, (int)(fate >> 4) & 1, nh, e_end, nt_end, src, rt);
-                    w = w_in = sp_norm2(a);
-                    if (cat == CAT_EYEBOX || cat == CAT_MISS) {
-                        const double* fx = dt.f + e_end * kDirFld;
-                        a.s = cscale(a.s, fx[DF_XS]);
-                        a.p = cscale(a.p, fx[DF_XP]);
-                        w = sp_norm2(a);
-                    }
-                    if (ADJ && eye) {
-                        int64_t k = kent;
-                        dir_reverse(*pl, dt, a, nh, e_end, nt_end, src, tape, [&](double kappa, cd Gs, cd Gp, int meta) {
-                            put_entry(k++, kappa, Gs, Gp, meta_bin | (int64_t)meta);
-                        });
-                    }
-                };
-                if (active && !off) {
-                    if constexpr (KEYED) {
-                        if (keyed) table_ray(KeyCoefs{ hq, col, ncol, sc.M, kl.slot, kl.coef });
-                        else table_ray(HitCoefs{ hq, pos, ncol });
-                    } else {
-                        table_ray(HitCoefs{ hq, pos, ncol });
-                    }
-                }
-                if (__ballot(active && off) != 0ull) {
-                    // general field walk, tape of every event and reverse sweep
-                    Ray r;
-                    Outcome o;
-                    o.cat = CAT_LOST;
-                    int nt = 0;
-                    const bool mine = active && off;
-                    if (mine) {
-                        ray_birth(sc, *pl, id, r);
-                        const TapeRef rt = { ADJ && eye ? tape.ev : nullptr, tape.mr, tape.ks };
-                        walk_ray<true, ADJ>(sc, *pl, r, o, NoHit{}, GetCoefP{ hq, pos, ncol }, rt, &nt);
-                        w = o.w; w_in = o.w_in;
-                    }
-                    if constexpr (ADJ) {
-                        const int ntw = wave_max_int(mine && eye ? nt : 0);
-                        if (mine && eye) {
-                            int64_t k = kent;
-                            reverse_sweep(sc, *pl, r.e, tape, nt, ntw, [&](double kappa, cd Gs, cd Gp, int meta) {
-                                put_entry(k++, kappa, Gs, Gp, meta_bin | (int64_t)meta);
-                            });
+                if constexpr (DIRS) {
+                    const int e_end = (int)(fate >> 23) & 255, nt_end = (int)(fate >> 31) & 511;
+                    const bool mine = active && !off;
+                    auto table_rays = [&](const auto& src) {
+                        const TapeRef rt = { nullptr, ADJ && eye ? tape.mr : nullptr, tape.ks };
+                        FaceSp a{};
+                        if (mine) {
+                            a = dir_field(*pl, dt, (int)(fate >> 4) & 1, nh, e_end, nt_end, src, rt);
+                            w = w_in = sp_norm2(a);
+                            if (cat == CAT_EYEBOX || cat == CAT_MISS) {
+                                const double* fx = dt.f + e_end * kDirFld;
+                                a.s = cscale(a.s, fx[DF_XS]);
+                                a.p = cscale(a.p, fx[DF_XP]);
+                                w = sp_norm2(a);
+                            }
                         }
+                        if constexpr (ADJ) {
+                            const int nhw = wave_max_int(mine && eye ? nh : 0);
+                            if (mine && eye) {
+                                int64_t k = kent;
+                                dir_reverse(*pl, dt, a, nh, nhw, e_end, nt_end, src, tape,
+                                            [&](double kappa, cd Gs, cd Gp, int meta) {
+                                                out.put(k++, kappa, Gs, Gp, meta_bin | (int64_t)meta, TAB);
+                                            });
+                            }
+                        }
+                    };
+                    if constexpr (KEYED) {
+                        if (keyed) table_rays(KeyCoefs{ pq, col, sc.M, kl.slot, kl.coef });
+                        else table_rays(HitCoefs{ pq, pos });
+                    } else {
+                        table_rays(HitCoefs{ pq, pos });
                     }
+                    if (any_off && __ballot(active && off) != 0ull) {
+                        const PoolQueue pq2 = pq;
+                        const TapeRef tp2 = tape;
+                        EntryOut out2 = out;
+                        double w2 = 0.0, wi2 = 0.0;
+                        off_field<ADJ, TAB>(*s_sc, *pl, id, pq2, pos, active && off, eye, tp2, kent, meta_bin, TAB, out2, w2, wi2);
+                        out = out2;
+                        if (active && off) { w = w2; w_in = wi2; }
+                    }
+                } else {
+                    general_field<ADJ>(sc, *pl, id, pq, pos, active, eye, tape, kent, meta_bin, TAB, out, w, w_in);
                 }
                 finish(active, id, cat, bin, nev, nh, w, w_in);
             }
             __threadfence_block();                        // the next pool's solves rewrite the queue
         }
         if (ADJ && lane == 0) {
-            st.cnt[item * st.waves + wave] = (int32_t)(n_ent < st.cap_w ? n_ent : st.cap_w);
+            st.cnt[region] = (int32_t)(n_ent < st.cap_w ? n_ent : st.cap_w);
             if (n_ent > st.cap_w) st.ovf[item] = 1;
         }
         if (sc.item_work && lane == 0) sc.item_work[item * n_waves + wave] = (int32_t)n_work;
@@ -826,13 +998,11 @@ __global__ void __launch_bounds__(256, 2) k_trace_fwd(SceneDev sc, uint64_t* __r
             }
         }
     }
-    if (n_fp64) atomicAdd(&s_st[ST_FP64], n_fp64);
-    if (n_lay) atomicAdd(&s_st[ST_LAYERS], n_lay);
     if constexpr (ADJ && TAB) {
         // nonnegative doubles order like their bit patterns
-        const double gm = wave_max(t_gmax);
+        const double gm = wave_max(out.gmax);
         if (lane == 0 && gm > 0.0) atomicMax(&sc.tab_scale[0], (unsigned long long)__double_as_longlong(gm));
-        if (t_ne) atomicAdd(&sc.tab_scale[1], t_ne);
+        if (out.n) atomicAdd(&sc.tab_scale[1], out.n);
     }
     __syncthreads();
     for (int k = tid; k < NCAT + 3; k += WG) {

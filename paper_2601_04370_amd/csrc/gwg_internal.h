@@ -64,10 +64,11 @@ enum StatWord { ST_RAYS = 0, ST_EVENTS = 1, ST_PRMA = 2, ST_FP64 = 3, ST_SAT = 4
                 ST_WORDS = 28 };
 
 // Adjoint entries recorded by the forward trace for the backward: per
-// (work item, forward wave) a region of cap_w entries, field f of entry e at
-// ent[f * total + e], e = (item * waves + wave) * cap_w + k.  Fields: kappa,
-// G_s (re, im), G_p (re, im) without the dL/dI factor, meta = mirror |
-// front << 8 | reflected << 9 | bin << 10 (an exact integer in a double).
+// (work item, forward wave) a region of cap_w entries of kEntFields doubles,
+// entry e = (item * waves + wave) * cap_w + k at ent + e * kEntFields, written
+// and read as three 16-byte words.  Fields: kappa, G_s (re, im), G_p (re, im)
+// without the dL/dI factor, meta = mirror | front << 8 | reflected << 9 |
+// bin << 10 (an exact integer in a double).
 // cnt[item * waves + wave] = entries of that region; ovf[item] != 0 when a
 // region of the item overflowed (the backward then regenerates that item).
 constexpr int kEntFields = 6;
@@ -77,12 +78,12 @@ constexpr int kCkEntriesPerRay = 4;        // sweep checkpoints kept per ray (en
 constexpr int kPoolMax = 8;                // forward: rounds of 64 rays per wave pool, at most
 constexpr double kCkBudgetBytes = 128.0 * (1ull << 30);
 constexpr int kTableNodesMax = 1 << 20;
+struct AdjEntry { double kappa; double gs_re, gs_im, gp_re, gp_im; int64_t meta; };
 struct AdjStore {
     double* ent;
     int32_t* cnt;
     int32_t* ovf;
     int64_t cap_w;
-    int64_t total;
     int32_t waves;
     // Sweep checkpoints of the first ck_cap entries of every region, stored
     // by the FP64 forward solve (null: the adjoint recomputes them).  Entry

@@ -468,10 +468,7 @@ size_t fwd_scene_bytes(const SceneDev& sc, int wg, bool lds_bins)
 }
 size_t fwd_smem_bytes(const SceneDev& sc, int wg, bool lds_bins)
 {
-    return (size_t)smem_layout(sc.M, sc.Lmax, sc.n_slots, wg, sc.bins_x * sc.bins_y, lds_bins, 0,
-                               sc.memo ? LaneSlots3::kPer : LaneSlots3x::kPer, true).total
-           + (NCAT + 2) * kStatCols * 8 + (size_t)dir_smem_bytes(sc)
-           + (sc.memo || sc.table ? (size_t)key_smem_bytes(sc.M) : 0);
+    return (size_t)fwd_layout(sc, wg, lds_bins, sc.dirs != nullptr, sc.table != nullptr, sc.memo != 0).total;
 }
 size_t bwd_smem_bytes(const SceneDev& sc, int wg)
 {
@@ -486,12 +483,29 @@ static int blocks_per_cu(K kernel, int wg, size_t smem)
     return n;
 }
 
-template <bool ADJ, bool TAB, bool MEMO = false>
-static int fwd_blocks_per_cu(int precision, int wg, size_t smem)
+// The forward kernel of a kind: memoized solves need the direction table, and
+// the table forward solves nothing, so its precision does not matter.
+using FwdKernel = void (*)(SceneDev, uint64_t*, uint32_t*, unsigned long long*, gwg_ray_record*, int64_t, int, double*,
+                           AdjStore, double*);
+template <int MODE, bool ADJ>
+static FwdKernel fwd_kernel_mode(bool tab, bool memo, bool dirs)
 {
-    if (precision == GWG_FP64) return blocks_per_cu(k_trace_fwd<GWG_FP64, ADJ, TAB, MEMO>, wg, smem);
-    if (precision == GWG_FP32_MIXED) return blocks_per_cu(k_trace_fwd<GWG_FP32_MIXED, ADJ, TAB, MEMO>, wg, smem);
-    return blocks_per_cu(k_trace_fwd<GWG_FP32, ADJ, TAB, MEMO>, wg, smem);
+    if (tab) return dirs ? k_trace_fwd<GWG_FP64, ADJ, true, false, true> : k_trace_fwd<GWG_FP64, ADJ, true, false, false>;
+    if (memo) return k_trace_fwd<MODE, ADJ, false, true, true>;
+    return dirs ? k_trace_fwd<MODE, ADJ, false, false, true> : k_trace_fwd<MODE, ADJ, false, false, false>;
+}
+static FwdKernel fwd_kernel(int precision, bool adj, bool tab, bool memo, bool dirs)
+{
+    switch (precision) {
+    case GWG_FP64: return adj ? fwd_kernel_mode<GWG_FP64, true>(tab, memo, dirs) : fwd_kernel_mode<GWG_FP64, false>(tab, memo, dirs);
+    case GWG_FP32_MIXED:
+        return adj ? fwd_kernel_mode<GWG_FP32_MIXED, true>(tab, memo, dirs) : fwd_kernel_mode<GWG_FP32_MIXED, false>(tab, memo, dirs);
+    default: return adj ? fwd_kernel_mode<GWG_FP32, true>(tab, memo, dirs) : fwd_kernel_mode<GWG_FP32, false>(tab, memo, dirs);
+    }
+}
+int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem)
+{
+    return blocks_per_cu(fwd_kernel(sc.precision, adj, sc.table != nullptr, sc.memo != 0, sc.dirs != nullptr), wg, smem);
 }
 
 template <bool TAB>
@@ -505,12 +519,6 @@ static int bwd_blocks_per_cu(int precision, int wg, size_t smem)
 int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
 {
     switch (kind) {
-    case KIND_FWD: return fwd_blocks_per_cu<false, false>(precision, wg, smem);
-    case KIND_FWD_ADJ: return fwd_blocks_per_cu<true, false>(precision, wg, smem);
-    case KIND_FWD_TAB: return fwd_blocks_per_cu<false, true>(precision, wg, smem);
-    case KIND_FWD_ADJ_TAB: return fwd_blocks_per_cu<true, true>(precision, wg, smem);
-    case KIND_FWD_MEMO: return fwd_blocks_per_cu<false, false, true>(precision, wg, smem);
-    case KIND_FWD_ADJ_MEMO: return fwd_blocks_per_cu<true, false, true>(precision, wg, smem);
     case KIND_BWD_REGEN: return bwd_blocks_per_cu<false>(precision, wg, smem);
     case KIND_BWD_REGEN_TAB: return bwd_blocks_per_cu<true>(precision, wg, smem);
     case KIND_ADJ_LOSSLESS:
@@ -528,49 +536,14 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
     }
 }
 
-template <int MODE>
-static void launch_fwd_mode(const SceneDev& sc, dim3 grid, dim3 block, size_t sm, bool lds_bins, uint64_t* q,
-                            uint32_t* c, unsigned long long* stats, gwg_ray_record* rec, int64_t rec_stride,
-                            double* scratch, const AdjStore* adj, double* tape, hipStream_t s)
-{
-    const bool tab = sc.table != nullptr, memo = sc.memo != 0;
-    if (adj && tab)
-        hipLaunchKernelGGL((k_trace_fwd<MODE, true, true, false>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, *adj, tape);
-    else if (adj && memo)
-        hipLaunchKernelGGL((k_trace_fwd<MODE, true, false, true>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, *adj, tape);
-    else if (adj)
-        hipLaunchKernelGGL((k_trace_fwd<MODE, true, false, false>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, *adj, tape);
-    else if (tab)
-        hipLaunchKernelGGL((k_trace_fwd<MODE, false, true, false>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, AdjStore{}, (double*)nullptr);
-    else if (memo)
-        hipLaunchKernelGGL((k_trace_fwd<MODE, false, false, true>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, AdjStore{}, (double*)nullptr);
-    else
-        hipLaunchKernelGGL((k_trace_fwd<MODE, false, false, false>), grid, block, sm, s, sc, q, c, stats, rec, rec_stride,
-                           (int)lds_bins, scratch, AdjStore{}, (double*)nullptr);
-}
-
 hipError_t launch_trace_fwd(const SceneDev& sc, int wg, int grid_blocks, bool lds_bins, uint64_t* q, uint32_t* c,
                             unsigned long long* stats, gwg_ray_record* rec, int64_t rec_stride, double* scratch,
                             const AdjStore* adj, double* tape, hipStream_t s)
 {
-    size_t sm = fwd_smem_bytes(sc, wg, lds_bins);
-    dim3 grid((unsigned)grid_blocks), block(wg);
-    switch (sc.precision) {
-    case GWG_FP64:
-        launch_fwd_mode<GWG_FP64>(sc, grid, block, sm, lds_bins, q, c, stats, rec, rec_stride, scratch, adj, tape, s);
-        break;
-    case GWG_FP32_MIXED:
-        launch_fwd_mode<GWG_FP32_MIXED>(sc, grid, block, sm, lds_bins, q, c, stats, rec, rec_stride, scratch, adj, tape, s);
-        break;
-    default:
-        launch_fwd_mode<GWG_FP32>(sc, grid, block, sm, lds_bins, q, c, stats, rec, rec_stride, scratch, adj, tape, s);
-        break;
-    }
+    const size_t sm = fwd_smem_bytes(sc, wg, lds_bins);
+    FwdKernel k = fwd_kernel(sc.precision, adj != nullptr, sc.table != nullptr, sc.memo != 0, sc.dirs != nullptr);
+    hipLaunchKernelGGL(k, dim3((unsigned)grid_blocks), dim3(wg), sm, s, sc, q, c, stats, rec, rec_stride, (int)lds_bins,
+                       scratch, adj ? *adj : AdjStore{}, adj ? tape : nullptr);
     return hipGetLastError();
 }
 

@@ -19,9 +19,10 @@ size_t bwd_smem_bytes(const SceneDev& sc, int wg);
 size_t tmm_smem_bytes(int L, int n_slots, int wg);
 int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
 
-enum { KIND_FWD = 0, KIND_FWD_ADJ = 1, KIND_BWD_REGEN = 2, KIND_ADJ_ENTRIES = 3, KIND_ADJ_LOSSLESS = 4,
-       KIND_ADJ_MEMO = 5, KIND_ADJ_MEMO_LOSSLESS = 6, KIND_TABLE_ACCUM = 7, KIND_FWD_TAB = 8, KIND_FWD_ADJ_TAB = 9,
-       KIND_BWD_REGEN_TAB = 10, KIND_OMEGA = 11, KIND_FWD_MEMO = 12, KIND_FWD_ADJ_MEMO = 13 };
+// KIND_FWD and up: forward kernels, KIND_FWD + gradient + 2 table + 4 memoized + 8 direction table
+enum { KIND_BWD_REGEN = 0, KIND_ADJ_ENTRIES = 1, KIND_ADJ_LOSSLESS = 2, KIND_ADJ_MEMO = 3, KIND_ADJ_MEMO_LOSSLESS = 4,
+       KIND_TABLE_ACCUM = 5, KIND_BWD_REGEN_TAB = 6, KIND_OMEGA = 7, KIND_FWD = 8 };
+int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem);
 int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem);
 int64_t fwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
 int64_t adj_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);

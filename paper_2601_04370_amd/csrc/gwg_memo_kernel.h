@@ -65,9 +65,10 @@ __device__ inline int memo_collect(const SceneDev& sc, const AdjStore& st, int64
         nmeta = -1;
         if (v < v1) {
             const int64_t e = entry_index(st, item, cnt, v);
-            nk = st.ent[e];
-            nmeta = (int64_t)st.ent[5 * st.total + e];
-            for (int q = 0; q < 4; ++q) ng[q] = st.ent[(1 + q) * st.total + e];
+            const AdjEntry en = load_entry(st, e);
+            nk = en.kappa;
+            nmeta = en.meta;
+            ng[0] = en.gs_re; ng[1] = en.gs_im; ng[2] = en.gp_re; ng[3] = en.gp_im;
         }
     };
     fetch(v0);
@@ -207,13 +208,14 @@ __global__ void __launch_bounds__(64 * kMemoWaves, 2) k_adj_memo(SceneDev sc, co
                     const int v = c + lane;
                     if (v < total) {
                         const int64_t e = entry_index(st, item, cnt, v);
-                        const int64_t meta = (int64_t)st.ent[5 * st.total + e];
+                        const AdjEntry en = load_entry(st, e);
+                        const int64_t meta = en.meta;
                         const double gscale = g_bins[(int)(meta >> 10)] * invN;
                         if (gscale != 0.0) {
-                            const cd Gs = cscale(mk(st.ent[1 * st.total + e], st.ent[2 * st.total + e]), gscale);
-                            const cd Gp = cscale(mk(st.ent[3 * st.total + e], st.ent[4 * st.total + e]), gscale);
+                            const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
+                            const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
                             const int mm = (int)(meta & 1023);
-                            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, st.ent[e], Gs, Gp, mm, chk, nthreads);
+                            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, en.kappa, Gs, Gp, mm, chk, nthreads);
                             c_keys += 1;
                             c_lay += (unsigned long long)pl->nlay[mm & 255];
                         }

@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(256) k_table_build(SceneDev sc, double* __rest
         const int ms = (int)(q / n);
         const int m = ms >> 1;
         bool u64 = false;
-        const Coef4 c = hit_solve<MODE>(sc, *pl, RecStacks{ s_rec, sc.Lmax }, sl, m, (ms & 1) == 0, table_kappa(pl->ng, j, n), &u64);
+        const Coef4 c = hit_solve<MODE>(sc.n_slots, sc.slot_complex, *pl, RecStacks{ s_rec, sc.Lmax }, sl, m, (ms & 1) == 0, table_kappa(pl->ng, j, n), &u64);
         double* o = out + q * 8;
         o[0] = c.rs.re; o[1] = c.rs.im; o[2] = c.rp.re; o[3] = c.rp.im;
         o[4] = c.ts.re; o[5] = c.ts.im; o[6] = c.tp.re; o[7] = c.tp.im;
@@ -110,12 +110,13 @@ __global__ void __launch_bounds__(64 * kMemoWaves) k_table_accum(SceneDev sc, co
                     const int v = c + lane;
                     if (v < total) {
                         const int64_t e = entry_index(st, item, cnt, v);
-                        const int64_t meta = (int64_t)st.ent[5 * st.total + e];
+                        const AdjEntry en = load_entry(st, e);
+                        const int64_t meta = en.meta;
                         const double gscale = g_bins[(int)(meta >> 10)] * invN;
                         if (gscale != 0.0) {
-                            const cd Gs = cscale(mk(st.ent[1 * st.total + e], st.ent[2 * st.total + e]), gscale);
-                            const cd Gp = cscale(mk(st.ent[3 * st.total + e], st.ent[4 * st.total + e]), gscale);
-                            table_emit(acc_dl, n, ng, st.ent[e], Gs, Gp, (int)(meta & 1023), fx);
+                            const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
+                            const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
+                            table_emit(acc_dl, n, ng, en.kappa, Gs, Gp, (int)(meta & 1023), fx);
                         }
                     }
                 }
