@@ -1135,7 +1135,7 @@ int gwg_omega_gradient(gwg_ctx* c, const double* d_W, const uint32_t* d_counts, 
     const SceneDev sc = c->fwd;                    // the forward's items, seeds and decisions
     const int wg = 256;
     const size_t smem = omega_smem_bytes(sc, wg);
-    if (smem > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
+    if (omega_scene_bytes(sc, wg) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     const int64_t n_cu = std::max(c->n_cu, 1);
     const int64_t grid = std::min<int64_t>(sc.n_items, n_cu * occupancy(c, KIND_OMEGA, sc.precision, wg, smem));
     int rc = ensure_buf(c, c->partial, sizeof(double) * (size_t)sc.n_items * sc.M, cap, "alloc partial gradients");

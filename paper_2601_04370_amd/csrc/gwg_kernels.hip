@@ -530,7 +530,7 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
     case KIND_TABLE_ACCUM:
         return blocks_per_cu(k_table_accum, 64 * kMemoWaves, smem);
     case KIND_OMEGA:
-        return blocks_per_cu(k_omega_grad, wg, smem);
+        return std::min(blocks_per_cu(k_omega_grad<true>, wg, smem), blocks_per_cu(k_omega_grad<false>, wg, smem));
     default:
         return blocks_per_cu(k_adj_entries<false>, wg, smem);
     }
@@ -676,9 +676,13 @@ int64_t dir_table_doubles(const SceneDev& sc) { return (int64_t)sc.n_lsel * sc.F
 hipError_t launch_omega_grad(const SceneDev& sc, int grid_blocks, int wg, const double* W, const uint32_t* counts,
                              double* partial, double* grad, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_omega_grad, dim3((unsigned)grid_blocks), dim3(wg), omega_smem_bytes(sc, wg), s, sc, W, counts,
-                       partial);
-    hipLaunchKernelGGL(k_omega_reduce, dim3(1), dim3(64), 0, s, (const double*)partial, sc.n_items, sc.M, grad);
+    if (sc.dirs)
+        hipLaunchKernelGGL(k_omega_grad<true>, dim3((unsigned)grid_blocks), dim3(wg), omega_smem_bytes(sc, wg), s, sc, W,
+                           counts, partial);
+    else
+        hipLaunchKernelGGL(k_omega_grad<false>, dim3((unsigned)grid_blocks), dim3(wg), omega_smem_bytes(sc, wg), s, sc, W,
+                           counts, partial);
+    hipLaunchKernelGGL(k_omega_reduce, dim3((unsigned)sc.M), dim3(256), 0, s, (const double*)partial, sc.n_items, sc.M, grad);
     return hipGetLastError();
 }
 

@@ -47,6 +47,7 @@ size_t table_adj_smem_bytes(const SceneDev& sc);
 hipError_t launch_table_adj(const SceneDev& sc, double* partial, double* scratch, unsigned long long* stats,
                             hipStream_t s);
 hipError_t launch_table_reduce(const double* partial, const SceneDev& sc, double* grad, hipStream_t s);
+size_t omega_scene_bytes(const SceneDev& sc, int wg);
 size_t omega_smem_bytes(const SceneDev& sc, int wg);
 hipError_t launch_omega_grad(const SceneDev& sc, int grid_blocks, int wg, const double* W, const uint32_t* counts,
                              double* partial, double* grad, hipStream_t s);
