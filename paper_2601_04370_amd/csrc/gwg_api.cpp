@@ -513,9 +513,17 @@ int build_scene(gwg_ctx* c, const gwg_slab* sl, const gwg_prma* pr, const gwg_ma
     return GWG_OK;
 }
 
+// Waves of 64 rays a launch has (points are traced separately).
+int64_t ray_waves(const SceneDev& s) { return (int64_t)s.D * s.n_lsel * s.F * ((s.N + 63) / 64); }
+
 int pick_fwd_wg(gwg_ctx* c, const SceneDev& s, bool lds_bins)
 {
     if (c->tune.block_threads) return c->tune.block_threads;
+    // A launch of at most one wave per SIMD: workgroups of one wave spread
+    // over the CUs and wait for no other wave's barriers.  (27 points x 2048
+    // rays, 200 layers, gradient: 0.76 ms a step against 1.11 ms at 256
+    // threads; 100,000 rays of one point, 1563 waves: 0.16 against 0.14 ms.)
+    if (ray_waves(s) <= 4 * (int64_t)std::max(c->n_cu, 1)) return 64;
     for (int wg : { 256, 128, 64 })
         if (fwd_scene_bytes(s, wg, lds_bins) <= 65536) return wg;
     return 64;
@@ -529,7 +537,9 @@ int pick_bwd_wg(gwg_ctx* c, const SceneDev& s)
     return 64;
 }
 
-void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu)
+// grad: an adjoint follows, which takes the forward's items; per_hit: the
+// forward solves every hit (its passes are long enough for their fit to count).
+void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu, bool grad, bool per_hit)
 {
     const int64_t points = (int64_t)s.D * s.n_lsel * s.F;
     int64_t rpt = rays_per_tile;
@@ -539,10 +549,31 @@ void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu)
         // most about one item, costs little); otherwise split every point
         // into equal tiles of at least 4 rays per lane.  Memoized solves
         // share keys within an item, and take half as many, larger items.
-        const int64_t target = (int64_t)std::max(n_cu, 1) * (s.memo ? 16 : 32);
+        const int64_t cu = std::max(n_cu, 1);
+        const int64_t target = cu * (s.memo ? 16 : 32);
         const int64_t tiles = points >= target ? 1 : (target + points - 1) / points;
         rpt = (s.N + tiles - 1) / tiles;
-        rpt = std::max<int64_t>(rpt, (int64_t)wg * 4);
+        // 4 rays per lane make fuller solve batches and field passes, but
+        // not at the price of idle CUs: fewer while the launch has under 4
+        // items per CU (8 with an adjoint, which runs 8 waves a CU and two
+        // to an item; 2 memoized, whose items solve their keys each).  75
+        // points x 8192 rays, 200 layers, gradient: 2.94 ms a step at one
+        // ray per lane, 4.95 at four; memoized 1.74 and 1.31 ms.  100,000
+        // rays of one point, 8 layers, forward: 0.14 and 0.30 ms; 1,000,000
+        // rays 0.83 and 0.75 ms.
+        const int64_t fill = cu * (s.memo ? 2 : grad ? 8 : 4) * (wg / 64);
+        int64_t rounds = std::min<int64_t>(4, std::max<int64_t>(1, ray_waves(s) / fill));
+        // per hit, of 1 to that many the one whose items fill whole passes of two
+        // workgroups per CU best (1,000,000 rays of one point: 1302 items
+        // of three rounds take 0.84 ms, 977 of four 0.75)
+        int64_t best = -1, pick = rounds;
+        for (int64_t r = rounds; per_hit && r >= 1; --r) {
+            const int64_t items = points * ((s.N + wg * r - 1) / (wg * r));
+            const int64_t cost = (items + 2 * cu - 1) / (2 * cu) * r;
+            if (best < 0 || cost < best) { best = cost; pick = r; }
+        }
+        rounds = pick;
+        rpt = std::max<int64_t>(rpt, (int64_t)wg * rounds);
         rpt = ((rpt + wg - 1) / wg) * wg;
     }
     if (rpt > s.N) rpt = s.N;
@@ -803,7 +834,8 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         sc.memo = 0;                                   // per-hit solves (their own slot table size)
         wg = pick_fwd_wg(c, sc, lds_bins);
     }
-    set_tiles(sc, c->tune.rays_per_block, wg, c->n_cu);
+    set_tiles(sc, c->tune.rays_per_block, wg, c->n_cu, (flags & GWG_FWD_GRAD) != 0,
+              (flags & (GWG_FWD_MEMO | GWG_FWD_TABLE)) == 0);
     if (fwd_scene_bytes(sc, wg, lds_bins) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     if (sc.n_items > 0x7fffffff) return fail(c, GWG_E_INVAL, "too many work items; raise rays_per_block");
     const int64_t nbins = (int64_t)sc.D * sc.n_lsel * sc.F * B;
@@ -988,7 +1020,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     // items: the entry kernel covers items whose regions fit, the
     // regenerating kernel the rest.  Otherwise every item is regenerated.
     const bool entries = c->adj_valid && sample_stride == 1;
-    if (!entries) set_tiles(sc, c->tune.bwd_rays_per_block, wg, c->n_cu);
+    if (!entries) set_tiles(sc, c->tune.bwd_rays_per_block, wg, c->n_cu, true, true);
     if (bwd_smem_bytes(sc, wg) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     // persistent grids: as many workgroups as fit on the device at once
     const size_t smem = bwd_smem_bytes(sc, wg);
@@ -1252,11 +1284,11 @@ int gwg_autotune(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, const g
     for (int wg : { 256, 128 }) {
         if (fwd_scene_bytes(sc0, wg, lds_bins) > 65536) continue;
         SceneDev t = sc0;
-        set_tiles(t, 0, wg, c->n_cu);
+        set_tiles(t, 0, wg, c->n_cu, with_bwd, (flags & GWG_FWD_MEMO) == 0);
         std::vector<int64_t> seen;
         for (int shift : { 0, -1, 1, -2, 2 }) {
             int64_t rpt = shift >= 0 ? t.rays_per_tile << shift : t.rays_per_tile >> -shift;
-            rpt = std::max<int64_t>(rpt, (int64_t)wg * 4);
+            rpt = std::max<int64_t>(rpt, (int64_t)wg);
             rpt = std::min<int64_t>(((rpt + wg - 1) / wg) * wg, sc0.N);
             if (std::find(seen.begin(), seen.end(), rpt) != seen.end()) continue;
             seen.push_back(rpt);

@@ -22,7 +22,7 @@
 // by a fixed tree per mirror: the gradient is deterministic.
 //
 // Bound by the geometry walks (instruction issue and LDS latency).  On the
-// direction table, 4 workgroups a CU instead of 3, one butterfly per item
+// direction table, with one butterfly per item
 // instead of one per 64 rays, and 256 threads per mirror summing the items
 // instead of one: 6 mirrors, 3 x 441 points x 8192 rays, 2.63 -> 1.28 ms; the sum over
 // the items 1.16 -> 0.01 ms.
