@@ -115,7 +115,7 @@ struct gwg_ctx {
     bool have_forward = false;
     SceneDev fwd{};
     // adjoint entries recorded by the last forward (GWG_FWD_GRAD)
-    DevBuf adj_ent, adj_cnt, adj_ovf, fwd_tape, adj_ck, adj_order;
+    DevBuf adj_ent, adj_cnt, adj_ovf, fwd_tape, adj_ck, adj_order, adj_keys, key_sum;
     // per-(item, wave) mirror hits of the last forward, and the order the
     // next forward of the same decomposition takes its items in
     DevBuf item_work, fwd_order;
@@ -181,6 +181,16 @@ int ensure_buf(gwg_ctx* c, DevBuf& b, size_t n, bool capturing, const char* what
         return fail(c, GWG_E_STATE, "%s would allocate during stream capture; make the same call once before capturing", what);
     HIP_CHECK(c, b.ensure(n), what);
     return GWG_OK;
+}
+
+// A buffer that a call can do without: whether it is there (or could be
+// allocated) with n bytes.
+bool room_for(gwg_ctx* c, DevBuf& b, size_t n, bool capturing)
+{
+    if (ensure_buf(c, b, n, capturing, "optional buffer") == GWG_OK) return true;
+    c->err.clear();
+    (void)hipGetLastError();
+    return false;
 }
 
 template <class Query>
@@ -652,7 +662,7 @@ int gwg_destroy(gwg_ctx* c)
         for (DevBuf* b : { &c->stats, &c->partial, &c->scratch, &c->fwd_scratch,
                            &c->loss_work, &c->tmm_tab, &c->tmm_slot, &c->adj_ent, &c->adj_cnt, &c->adj_ovf, &c->fwd_tape,
                            &c->tab, &c->tab_scale, &c->tab_acc, &c->tune_q, &c->tune_c, &c->tune_g, &c->tune_grad,
-                           &c->adj_ck, &c->grad_tmp, &c->adj_order, &c->item_work, &c->fwd_order })
+                           &c->adj_ck, &c->adj_keys, &c->key_sum, &c->grad_tmp, &c->adj_order, &c->item_work, &c->fwd_order })
             b->release();
         for (KernelTimer& t : c->timer) t.destroy();
     }
@@ -869,7 +879,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         const int64_t total = sc.n_items * waves * cap_w;
         const size_t ent_b = sizeof(double) * (size_t)(total * kEntFields);
         const size_t cnt_b = sizeof(int32_t) * (size_t)(sc.n_items * waves);
-        const size_t ovf_b = sizeof(int32_t) * (size_t)sc.n_items;
+        const size_t ovf_b = sizeof(int32_t) * (2 * (size_t)sc.n_items + 1);   // flags, then the list of overflowed items
         bool fits;
         if (cap) {
             // nothing may be allocated: use the entries if the buffers already hold them
@@ -887,9 +897,9 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
-            HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items, 0u, s), "zero overflow flags");
+            HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items + 1, 0u, s), "zero overflow flags");
             c->adj = AdjStore{ (double*)c->adj_ent.p, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, cap_w, waves,
-                               nullptr, 0, 0, nullptr };
+                               nullptr, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
             adj = true;
             // The FP64 solve can keep the adjoint's sweep checkpoints of the
             // first ck_cap entries of every region (kCkEntriesPerRay per ray,
@@ -927,9 +937,23 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
-            c->adj = AdjStore{ nullptr, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, 0, waves, nullptr, 0, 0, nullptr };
+            HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items + 1, 0u, s), "zero overflow flags");
+            c->adj = AdjStore{ nullptr, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, 0, waves,
+                               nullptr, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
         }
         adj_sweep = adj || table;
+        if (adj && sc.dirs && (sc.memo || table)) {
+            // the items' keys: number of items with entries without keys, their list, the
+            // items' key counts, then kFwdMemoKeys 16-bit keys an item.  No
+            // room: the backward searches the entries for their keys.
+            const size_t n4 = sizeof(int32_t) * (2 * (size_t)sc.n_items + 2);
+            if (room_for(c, c->adj_keys, n4 + sizeof(uint16_t) * kFwdMemoKeys * (size_t)sc.n_items, cap)) {
+                c->adj.unkeyed = (int32_t*)c->adj_keys.p;
+                c->adj.n_keys = c->adj.unkeyed + 1 + sc.n_items;
+                c->adj.keys = (uint16_t*)((char*)c->adj_keys.p + n4);
+                HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj.unkeyed, 1, 0u, s), "zero item list");
+            }
+        }
     }
     // persistent grid: as many workgroups as fit on the device at once
     const int kind_f = KIND_FWD + (adj_sweep ? 1 : 0) + (table ? 2 : 0) + (sc.memo ? 4 : 0) + (sc.dirs ? 8 : 0);
@@ -1034,10 +1058,18 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     const int ML = sc.M * sc.Lmax;
     int64_t scratch_d = std::max(bwd_scratch_doubles(sc, grid, wg), entries ? adj_scratch_doubles(sc, grid_e, wg) : 0);
     if (entries && c->memo) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_m, 64));
-    if (sc.table) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, table_adj_blocks(sc), 128));
+    // memoized entries with keys: summed per item, then one adjoint per key of a point
+    const bool keyed = entries && c->memo && c->adj.n_keys &&
+                       room_for(c, c->key_sum, sizeof(double) * (size_t)key_sum_doubles(sc), cap);
+    const int kind_k = sc.slot_complex == 0u ? KIND_KEY_ADJ_LOSSLESS : KIND_KEY_ADJ;
+    const int64_t grid_k = keyed ? std::min<int64_t>(key_adj_blocks(sc), n_cu * occupancy(c, kind_k, sc.precision, 64,
+                                                                                          key_adj_smem_bytes(sc))) : 0;
+    if (keyed) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_k, 64));
+    const int64_t grid_ta = std::min<int64_t>(table_adj_rows(sc), 4 * n_cu);
+    if (sc.table) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_ta, 128));
     rc = ensure_buf(c, c->scratch, sizeof(double) * (size_t)scratch_d, cap, "alloc adjoint scratch");
     if (rc) return rc;
-    const int64_t partial_d = sc.table ? table_adj_blocks(sc) * sc.Lmax : sc.n_items * (int64_t)ML;
+    const int64_t partial_d = sc.table ? table_adj_rows(sc) * sc.Lmax : sc.n_items * (int64_t)ML;
     rc = ensure_buf(c, c->partial, sizeof(double) * (size_t)partial_d, cap, "alloc partial gradients");
     if (rc) return rc;
     rc = ensure_buf(c, c->stats, sizeof(uint64_t) * ST_WORDS, cap, "alloc stats");
@@ -1046,7 +1078,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     if (sc.table) {
         // angle table: cotangents of the table entries, then one adjoint per entry
         if (table_adj_smem_bytes(sc) > 65536) return fail(c, GWG_E_INVAL, "scene too large for the table adjoint's LDS");
-        const int64_t n_acc = table_adj_blocks(sc) * (int64_t)sc.table_n * 4;
+        const int64_t n_acc = table_acc_words(sc);
         rc = ensure_buf(c, c->tab_acc, sizeof(int64_t) * (size_t)n_acc, cap, "alloc table cotangents");
         if (rc) return rc;
         sc.tab_acc = (long long*)c->tab_acc.p;
@@ -1057,11 +1089,13 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         HIP_CHECK(c, launch_fill_u64((uint64_t*)(sc.tab_scale + 2), 1, 0, s), "zero dL/dI bound");
         HIP_CHECK(c, launch_absmax(d_dL_dI, nbins, sc.tab_scale + 2, s), "dL/dI bound");
         if (c->timing && !cap) HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].begin(), s), "timing event");
+        if (entries && c->adj.n_keys)
+            HIP_CHECK(c, launch_table_keys(sc, d_dL_dI, c->adj, s), "keyed table cotangent kernel");
         if (entries) HIP_CHECK(c, launch_table_accum(sc, (int)grid_t, d_dL_dI, c->adj, s), "table cotangent kernel");
         HIP_CHECK(c, launch_trace_bwd(sc, wg, (int)grid, d_dL_dI, (unsigned long long*)c->stats.p, (double*)c->partial.p,
-                                      (double*)c->scratch.p, sample_stride, entries ? c->adj.ovf : nullptr, s),
+                                      (double*)c->scratch.p, sample_stride, entries ? c->adj.left : nullptr, s),
                   "adjoint kernel");
-        HIP_CHECK(c, launch_table_adj(sc, (double*)c->partial.p, (double*)c->scratch.p, (unsigned long long*)c->stats.p, s),
+        HIP_CHECK(c, launch_table_adj(sc, (int)grid_ta, (double*)c->partial.p, (double*)c->scratch.p, (unsigned long long*)c->stats.p, s),
                   "table adjoint kernel");
         if (c->timing && !cap) {
             HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].end(), s), "timing event");
@@ -1072,11 +1106,17 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         return GWG_OK;
     }
     if (c->timing && !cap) HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].begin(), s), "timing event");
-    if (entries && c->memo)
+    if (entries && c->memo) {
+        AdjStore st = c->adj;
+        if (!keyed) st.n_keys = nullptr;                                     // every item's keys are searched for
+        if (keyed)
+            HIP_CHECK(c, launch_key_adj(sc, (int)grid_k, d_dL_dI, (unsigned long long*)c->stats.p, (double*)c->partial.p,
+                                        st, (double*)c->key_sum.p, (double*)c->scratch.p, s),
+                      "keyed adjoint kernels");
         HIP_CHECK(c, launch_adj_memo(sc, (int)grid_m, d_dL_dI, (unsigned long long*)c->stats.p, (double*)c->partial.p,
-                                     c->adj, (double*)c->scratch.p, s),
+                                     st, (double*)c->scratch.p, s),
                   "memoized adjoint kernel");
-    else if (entries) {
+    } else if (entries) {
         // the entry kernel takes items largest first (entry counts from the
         // forward), so its workgroups finish together
         rc = ensure_buf(c, c->adj_order, sizeof(int32_t) * (size_t)sc.n_items, cap, "alloc item order");
@@ -1091,7 +1131,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
                   "adjoint entry kernel");
     }
     HIP_CHECK(c, launch_trace_bwd(sc, wg, (int)grid, d_dL_dI, (unsigned long long*)c->stats.p, (double*)c->partial.p,
-                                  (double*)c->scratch.p, sample_stride, entries ? c->adj.ovf : nullptr, s),
+                                  (double*)c->scratch.p, sample_stride, entries ? c->adj.left : nullptr, s),
               "adjoint kernel");
     if (c->timing && !cap) {
         HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].end(), s), "timing event");

@@ -163,9 +163,10 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
     constexpr bool tabm = TAB;
     const double fx = tabm ? table_fx_scale(sc) : 0.0;
 
-    for (int64_t item = draw_item(stats + ST_NEXT1); item < sc.n_items; item = draw_item(stats + ST_NEXT1)) {
-        // regen (optional): only items whose stored entries overflowed
-        if (regen && regen[item] == 0) continue;
+    // regen (optional): only the listed items, whose stored entries overflowed
+    const int64_t n_it = regen ? (int64_t)regen[0] : sc.n_items;
+    for (int64_t it = draw_item(stats + ST_NEXT1); it < n_it; it = draw_item(stats + ST_NEXT1)) {
+        const int64_t item = regen ? (int64_t)regen[1 + it] : it;
         int64_t point, i0, i1;
         int d, l, f;
         decode_item(sc, item, &point, &d, &l, &f, &i0, &i1);
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                 const AdjEntry en = load_entry(st, e);
                 const double kappa = en.kappa;
                 const int64_t meta = en.meta;
-                const int bin = (int)(meta >> 10);
+                const int bin = ent_bin(meta);
                 const double gscale = g_bins[bin] / (double)sc.N;
                 if (gscale != 0.0) {
                     const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);

@@ -351,7 +351,7 @@ struct KeyLds {
     uint32_t* have;              // [key_words] keys with coefficients
     uint8_t* slot;               // [2 kDirMax M] a key's slot
     uint16_t* key;               // [kFwdMemoKeys] the slots' keys
-    int* n;                      // slots in use; [1]: the table overflowed
+    int* n;                      // slots in use; [1]: the table overflowed; [2]: a ray left the direction table
     double* coef;                // [kFwdMemoKeys][8] r_s, r_p, t_s, t_p
 };
 
@@ -429,6 +429,7 @@ struct HitCoefs {
         const double2* b = q.coef(h, pos);
         return { q.tword[h * q.ncol + pos], b[0], b[64] };
     }
+    __device__ int64_t tag(int) const { return 0; }
 };
 // Keyed: the word in the ray's column, the key's coefficients in LDS.
 struct KeyCoefs {
@@ -442,6 +443,7 @@ struct KeyCoefs {
         const double2* b = (const double2*)(kc + 8 * slot[hit_key(w, M)] + (((w >> 9) & 1) ? 0 : 4));
         return { w, b[0], b[1] };
     }
+    __device__ int64_t tag(int w) const { return (int64_t)slot[hit_key(w, M)] << kEntSlotShift; }
 };
 
 // Field of one ray of the table from its birth to its end, over its nh hits.
@@ -543,7 +545,7 @@ __device__ inline void dir_reverse(const PointLds& pl, const DirLds& dt, FaceSp 
         FaceSp b = to_mirror(a, co, so);
         const cd Gs = cscale(cmul_f(cconj(b.s), mk(ev.t0.x, ev.t0.y)), scale);
         const cd Gp = cscale(cmul_f(cconj(b.p), mk(ev.t1.x, ev.t1.y)), scale);
-        emit(g[DG_KAP + neg], Gs, Gp, wd & 1023);
+        emit(g[DG_KAP + neg], Gs, Gp, (int64_t)(wd & 1023) | src.tag(wd));
         b.s = cscale(cmul_f(mk(ev.r.cs.x, -ev.r.cs.y), b.s), scale);
         b.p = cscale(cmul_f(mk(ev.r.cp.x, -ev.r.cp.y), b.p), scale);
         a = to_face(b, c, d);
@@ -726,7 +728,7 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
             for (int k = tid; k < B; k += WG) { s_q[k] = 0ull; s_c[k] = 0u; }
         if constexpr (KEYED) {
             for (int k = tid; k < 2 * key_words(sc.M); k += WG) kl.used[k] = 0u;
-            if (tid < 2) kl.n[tid] = 0;
+            if (tid < 3) kl.n[tid] = 0;
         }
         __syncthreads();
         const int64_t base = point * sc.N;
@@ -803,6 +805,7 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                     }
                     if (__ballot(o.off) != 0ull) {
                         any_off = true;
+                        if (KEYED && lane == 0) kl.n[2] = 1;
                         if (o.off) {
                             // copies: only these go through memory
                             const PoolQueue pq2 = pq;
@@ -932,7 +935,7 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                 const int64_t kent = info >> 16;
                 const int cat = (int)(fate & 7), bin = pq.bin[col];
                 const int nev = (int)(fate >> 14) & 511, nh = (int)(fate >> 5) & 511;
-                const int64_t meta_bin = (int64_t)bin << 10;
+                const int64_t meta_bin = (int64_t)(bin & 0xffffff) << 10;
                 double w = 0.0, w_in = 0.0;
                 if constexpr (DIRS) {
                     const int e_end = (int)(fate >> 23) & 255, nt_end = (int)(fate >> 31) & 511;
@@ -955,8 +958,8 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                             if (mine && eye) {
                                 int64_t k = kent;
                                 dir_reverse(*pl, dt, a, nh, nhw, e_end, nt_end, src, tape,
-                                            [&](double kappa, cd Gs, cd Gp, int meta) {
-                                                out.put(k++, kappa, Gs, Gp, meta_bin | (int64_t)meta, TAB);
+                                            [&](double kappa, cd Gs, cd Gp, int64_t meta) {
+                                                out.put(k++, kappa, Gs, Gp, meta_bin | meta, TAB);
                                             });
                             }
                         }
@@ -972,7 +975,8 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                         const TapeRef tp2 = tape;
                         EntryOut out2 = out;
                         double w2 = 0.0, wi2 = 0.0;
-                        off_field<ADJ, TAB>(*s_sc, *pl, id, pq2, pos, active && off, eye, tp2, kent, meta_bin, TAB, out2, w2, wi2);
+                        off_field<ADJ, TAB>(*s_sc, *pl, id, pq2, pos, active && off, eye, tp2, kent,
+                                            meta_bin | (int64_t)kNoSlot << kEntSlotShift, TAB, out2, w2, wi2);
                         out = out2;
                         if (active && off) { w = w2; w_in = wi2; }
                     }
@@ -985,10 +989,20 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
         }
         if (ADJ && lane == 0) {
             st.cnt[region] = (int32_t)(n_ent < st.cap_w ? n_ent : st.cap_w);
-            if (n_ent > st.cap_w) st.ovf[item] = 1;
+            if (n_ent > st.cap_w && atomicExch(&st.ovf[item], 1) == 0) st.left[1 + atomicAdd(st.left, 1)] = (int32_t)item;
         }
         if (sc.item_work && lane == 0) sc.item_work[item * n_waves + wave] = (int32_t)n_work;
         __syncthreads();
+        if constexpr (ADJ && KEYED) {
+            const int n = keyed ? kl.n[0] : -1;
+            if (st.n_keys) {
+                if (tid == 0) {
+                    st.n_keys[item] = n;
+                    if (n < 0 || kl.n[2] != 0) st.unkeyed[1 + atomicAdd(st.unkeyed, 1)] = (int32_t)item;
+                }
+                for (int k = tid; k < n; k += WG) st.keys[item * kFwdMemoKeys + k] = kl.key[k];
+            }
+        }
         if (lds_bins) {
             for (int k = tid; k < B; k += WG) {
                 if (s_c[k]) {

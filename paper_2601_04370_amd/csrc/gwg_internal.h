@@ -98,7 +98,20 @@ struct AdjStore {
     // Order in which the entry kernel takes items (null: item order); set by
     // the backward, largest entry regions first.
     const int32_t* order;
+    // Keyed forwards (memoized, angle table): the item's keys (hit_key
+    // values) and their number, -1 where the item overflowed its key table.
+    // Otherwise an entry's meta also holds its key's slot << kEntSlotShift
+    // (kNoSlot: of a ray that left the direction table).
+    uint16_t* keys;                       // [n_items][kFwdMemoKeys]
+    int32_t* n_keys;                      // [n_items] (null: no keys)
+    // Lists of items, written by the forward: [0] their number, then the
+    // items, in no particular order (outputs are indexed by item).
+    int32_t* left;                        // items that overflowed (ovf != 0)
+    int32_t* unkeyed;                     // items with entries without keys
 };
+constexpr int kNoSlot = 255;
+constexpr int kEntSlotShift = 34;         // meta: bin in bits 10..33, key slot above
+__host__ __device__ inline int ent_bin(int64_t meta) { return (int)((meta >> 10) & 0xffffff); }
 
 struct SceneDev {
     // slab

@@ -527,6 +527,10 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
         return blocks_per_cu(k_adj_memo<false>, 64 * kMemoWaves, smem);
     case KIND_ADJ_MEMO_LOSSLESS:
         return blocks_per_cu(k_adj_memo<true>, 64 * kMemoWaves, smem);
+    case KIND_KEY_ADJ:
+        return blocks_per_cu(k_key_adj<false>, 64, smem);
+    case KIND_KEY_ADJ_LOSSLESS:
+        return blocks_per_cu(k_key_adj<true>, 64, smem);
     case KIND_TABLE_ACCUM:
         return blocks_per_cu(k_table_accum, 64 * kMemoWaves, smem);
     case KIND_OMEGA:
@@ -646,10 +650,34 @@ hipError_t launch_table_accum(const SceneDev& sc, int grid_blocks, const double*
     return hipGetLastError();
 }
 
-hipError_t launch_table_adj(const SceneDev& sc, double* partial, double* scratch, unsigned long long* stats,
+hipError_t launch_key_adj(const SceneDev& sc, int grid_blocks, const double* dLdI, unsigned long long* stats,
+                          double* partial, const AdjStore& st, double* sum, double* scratch, hipStream_t s)
+{
+    unsigned long long* seen = (unsigned long long*)(sum + sc.n_items * (int64_t)(kKeyIndex * 4));
+    hipLaunchKernelGGL(k_key_sums, dim3((unsigned)std::min<int64_t>(sc.n_items, 1 << 20)), dim3(64 * kMemoWaves), 0, s, sc,
+                       dLdI, st, sum, seen);
+    const size_t sm = key_adj_smem_bytes(sc);
+    if (sc.slot_complex == 0u)
+        hipLaunchKernelGGL(k_key_adj<true>, dim3((unsigned)grid_blocks), dim3(64), sm, s, sc, st, (const double*)sum,
+                           (const unsigned long long*)seen, partial, scratch, stats);
+    else
+        hipLaunchKernelGGL(k_key_adj<false>, dim3((unsigned)grid_blocks), dim3(64), sm, s, sc, st, (const double*)sum,
+                           (const unsigned long long*)seen, partial, scratch, stats);
+    return hipGetLastError();
+}
+
+hipError_t launch_table_keys(const SceneDev& sc, const double* dLdI, const AdjStore& st, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_table_keys, dim3((unsigned)std::min<int64_t>(sc.n_items, 1 << 20)), dim3(64 * kMemoWaves), 0, s, sc,
+                       dLdI, st);
+    return hipGetLastError();
+}
+int64_t table_acc_words(const SceneDev& sc) { return (int64_t)sc.D * sc.n_lsel * sc.M * 4 * sc.table_n * 4; }
+
+hipError_t launch_table_adj(const SceneDev& sc, int grid_blocks, double* partial, double* scratch, unsigned long long* stats,
                             hipStream_t s)
 {
-    const dim3 grid((unsigned)(table_adj_blocks(sc))), block(128);
+    const dim3 grid((unsigned)grid_blocks), block(128);
     const size_t sm = table_adj_smem_bytes(sc);
     if (sc.slot_complex == 0u)
         hipLaunchKernelGGL(k_table_adj<true>, grid, block, sm, s, sc, partial, scratch, stats);

@@ -21,7 +21,8 @@ int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
 
 // KIND_FWD and up: forward kernels, KIND_FWD + gradient + 2 table + 4 memoized + 8 direction table
 enum { KIND_BWD_REGEN = 0, KIND_ADJ_ENTRIES = 1, KIND_ADJ_LOSSLESS = 2, KIND_ADJ_MEMO = 3, KIND_ADJ_MEMO_LOSSLESS = 4,
-       KIND_TABLE_ACCUM = 5, KIND_BWD_REGEN_TAB = 6, KIND_OMEGA = 7, KIND_FWD = 8 };
+       KIND_TABLE_ACCUM = 5, KIND_BWD_REGEN_TAB = 6, KIND_OMEGA = 7, KIND_FWD = 8,
+       KIND_KEY_ADJ = 64, KIND_KEY_ADJ_LOSSLESS = 65 };
 int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem);
 int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem);
 int64_t fwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
@@ -42,9 +43,16 @@ hipError_t launch_table_build(const SceneDev& sc, double* tab, int n_cu, unsigne
 hipError_t launch_absmax(const double* x, int64_t n, unsigned long long* out, hipStream_t s);
 size_t table_accum_smem_bytes();
 hipError_t launch_table_accum(const SceneDev& sc, int grid_blocks, const double* dLdI, const AdjStore& st, hipStream_t s);
-int64_t table_adj_blocks(const SceneDev& sc);
+int64_t table_adj_rows(const SceneDev& sc);          // partial gradient rows (Lmax each) of the table adjoint
+int64_t table_acc_words(const SceneDev& sc);         // its accumulators
+size_t key_adj_smem_bytes(const SceneDev& sc);
+int64_t key_adj_blocks(const SceneDev& sc);          // units of work of the keyed adjoint
+int64_t key_sum_doubles(const SceneDev& sc);
 size_t table_adj_smem_bytes(const SceneDev& sc);
-hipError_t launch_table_adj(const SceneDev& sc, double* partial, double* scratch, unsigned long long* stats,
+hipError_t launch_key_adj(const SceneDev& sc, int grid_blocks, const double* dLdI, unsigned long long* stats,
+                          double* partial, const AdjStore& st, double* sum, double* scratch, hipStream_t s);
+hipError_t launch_table_keys(const SceneDev& sc, const double* dLdI, const AdjStore& st, hipStream_t s);
+hipError_t launch_table_adj(const SceneDev& sc, int grid_blocks, double* partial, double* scratch, unsigned long long* stats,
                             hipStream_t s);
 hipError_t launch_table_reduce(const double* partial, const SceneDev& sc, double* grad, hipStream_t s);
 size_t omega_scene_bytes(const SceneDev& sc, int wg);

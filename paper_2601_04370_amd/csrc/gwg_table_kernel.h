@@ -84,8 +84,11 @@ __global__ void __launch_bounds__(64 * kMemoWaves) k_table_accum(SceneDev sc, co
     const double fx = table_fx_scale(sc);
     const int n = sc.table_n;
 
-    for (int64_t item = blockIdx.x; item < sc.n_items; item += gridDim.x) {
+    const int64_t n_it = st.n_keys ? (int64_t)st.unkeyed[0] : sc.n_items;    // only the items with entries without keys
+    for (int64_t it = blockIdx.x; it < n_it; it += gridDim.x) {
+        const int64_t item = st.n_keys ? (int64_t)st.unkeyed[1 + it] : it;
         if (st.ovf[item] != 0) continue;
+        const bool rest = st.n_keys && st.n_keys[item] >= 0;
         int64_t point, i0, i1;
         int d, l, f;
         decode_item(sc, item, &point, &d, &l, &f, &i0, &i1);
@@ -98,7 +101,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves) k_table_accum(SceneDev sc, co
         const int per = (total + kMemoWaves - 1) / kMemoWaves;
         const int v0 = min(wave * per, total), v1 = min(v0 + per, total);
         __syncthreads();
-        const int nk = memo_collect(sc, st, item, cnt, g_bins, v0, v1, mt);
+        const int nk = memo_collect(sc, st, item, cnt, g_bins, v0, v1, rest, mt);
         if (lane == 0) s_nkeys[wave] = nk;
         __syncthreads();
         if (wave == 0) {
@@ -112,7 +115,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves) k_table_accum(SceneDev sc, co
                         const int64_t e = entry_index(st, item, cnt, v);
                         const AdjEntry en = load_entry(st, e);
                         const int64_t meta = en.meta;
-                        const double gscale = g_bins[(int)(meta >> 10)] * invN;
+                        const double gscale = ent_searched(meta, rest) ? g_bins[ent_bin(meta)] * invN : 0.0;
                         if (gscale != 0.0) {
                             const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
                             const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
@@ -140,8 +143,41 @@ size_t table_accum_smem_bytes()
     return (size_t)(kMemoWaves * memo_wave_bytes() + 16);
 }
 
-// One workgroup (two waves) per (design, wavelength, mirror, side, branch):
-// block b covers accumulators [b n, (b + 1) n) and writes partial row b.
+// Items with keys: one workgroup per item, its keys' sums (key_sums) to the
+// table accumulators.
+__global__ void __launch_bounds__(64 * kMemoWaves, 4) k_table_keys(SceneDev sc, const double* __restrict__ dLdI, AdjStore st)
+{
+    const double fx = table_fx_scale(sc);
+    const int n = sc.table_n;
+    for (int64_t item = blockIdx.x; item < sc.n_items; item += gridDim.x) {
+        if (st.ovf[item] != 0 || st.n_keys[item] < 0) continue;
+        int64_t point, i0, i1;
+        int d, l, f;
+        decode_item(sc, item, &point, &d, &l, &f, &i0, &i1);
+        double s[4];
+        if (key_sums(sc, st, item, dLdI + point * (sc.bins_x * sc.bins_y), s)) {
+            const int i = threadIdx.x;
+            double kappa;
+            int mm;
+            key_hit(sc, (int64_t)l * sc.F + f, st.keys[item * kFwdMemoKeys + (i >> 1)], i & 1, &kappa, &mm);
+            table_emit(sc.tab_acc + ((int64_t)d * sc.n_lsel + l) * sc.M * 4 * n * 4, n,
+                       sc.lam_tab[(int64_t)l * LT_STRIDE + LT_NG], kappa, mk(s[0], s[1]), mk(s[2], s[3]), mm, fx);
+        }
+        __syncthreads();
+    }
+}
+
+// kTableParts workgroups (two waves each) per (design, wavelength, mirror,
+// side, branch) row r: unit r kTableParts + p covers a share of the row's n
+// accumulators and writes partial row r kTableParts + p.  One workgroup per
+// row left the chip idle: 108 rows on 256 CUs, and tens of adjoints of 200
+// layers one after another in each wave (8192 nodes: 1.24 ms; eight contiguous
+// parts 0.60 ms; eight interleaved ones 0.37 ms).
+constexpr int kTableParts = 8;
+__host__ __device__ inline int64_t table_adj_units(const SceneDev& sc)
+{
+    return (int64_t)sc.D * sc.n_lsel * sc.M * 4 * kTableParts;
+}
 template <bool LOSSLESS>
 __global__ void __launch_bounds__(128, 2) k_table_adj(SceneDev sc, double* __restrict__ partial,
                                                  double* __restrict__ scratch,
@@ -164,82 +200,82 @@ __global__ void __launch_bounds__(128, 2) k_table_adj(SceneDev sc, double* __res
     const LaneSlots3 sl = { slot_lane_base(s_sp, sc.n_slots, LaneSlots3::kPer, tid), pl->nsq, pl->pxy };
     double* chk = scratch + (int64_t)blockIdx.x * WG + tid;
     const int64_t cstride = (int64_t)gridDim.x * WG;
-    const int64_t b = blockIdx.x;
-    const int sb = (int)(b % 4);
-    const int m = (int)((b / 4) % sc.M);
-    const int64_t dl = b / 4 / sc.M;
-    const int d = (int)(dl / sc.n_lsel), l = (int)(dl % sc.n_lsel);
-    stage_point(sc, d, l, 0, pl, s_thk, s_slot);
-    for (int k = tid; k < n_waves * ML; k += WG) s_grad[k] = 0.0;
-    __syncthreads();
-    const int n = sc.table_n;
-    const long long* acc = sc.tab_acc + b * (int64_t)n * 4;
     const double inv = 1.0 / table_fx_scale(sc);
-    const int meta = m | ((sb >> 1) == 0 ? 1 << 8 : 0) | ((sb & 1) << 9);
     unsigned long long c_keys = 0, c_lay = 0;
-    auto run = [&](int j) {
-        const long long* a = acc + (int64_t)j * 4;
-        const cd Gs = mk((double)a[0] * inv, (double)a[1] * inv);
-        const cd Gp = mk((double)a[2] * inv, (double)a[3] * inv);
-        adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, table_kappa(pl->ng, j, n), Gs, Gp, meta, chk, cstride);
-        c_keys += 1;
-        c_lay += (unsigned long long)pl->nlay[m];
-    };
-    // wave w: a contiguous part of the entries; nonzero ones are compacted
-    // into the wave's LDS list and run 64 at a time
-    const int per = (n + n_waves - 1) / n_waves;
-    const int jb = min(wave * per, n), je = min(jb + per, n);
-    int cntl = 0;                                        // wave-uniform list length (< 64 between chunks)
-    for (int j0 = jb; j0 < je; j0 += 64) {
-        const int j = j0 + lane;
-        bool nz = false;
-        if (j < je) {
+    for (int64_t u = blockIdx.x; u < table_adj_units(sc); u += gridDim.x) {
+        const int64_t b = u / kTableParts;
+        const int part = (int)(u % kTableParts);
+        const int sb = (int)(b % 4);
+        const int m = (int)((b / 4) % sc.M);
+        const int64_t dl = b / 4 / sc.M;
+        const int d = (int)(dl / sc.n_lsel), l = (int)(dl % sc.n_lsel);
+        __syncthreads();                                     // the last unit's LDS is read
+        stage_point(sc, d, l, 0, pl, s_thk, s_slot);
+        for (int k = tid; k < n_waves * ML; k += WG) s_grad[k] = 0.0;
+        __syncthreads();
+        const int n = sc.table_n;
+        const long long* acc = sc.tab_acc + b * (int64_t)n * 4;
+        const int meta = m | ((sb >> 1) == 0 ? 1 << 8 : 0) | ((sb & 1) << 9);
+        auto run = [&](int j) {
             const long long* a = acc + (int64_t)j * 4;
-            nz = (a[0] | a[1] | a[2] | a[3]) != 0;
-        }
-        const unsigned long long bal = __ballot(nz);
-        const int pre = __popcll(bal & ((1ull << lane) - 1ull));
-        if (nz) lst[cntl + pre] = j;
-        cntl += __popcll(bal);
-        wave_lds_sync();
-        if (cntl >= 64) {
-            const int mine = lst[lane];
-            const int rem = cntl - 64;
-            const int moved = lane < rem ? lst[64 + lane] : 0;
+            const cd Gs = mk((double)a[0] * inv, (double)a[1] * inv);
+            const cd Gp = mk((double)a[2] * inv, (double)a[3] * inv);
+            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, table_kappa(pl->ng, j, n), Gs, Gp, meta, chk, cstride);
+            c_keys += 1;
+            c_lay += (unsigned long long)pl->nlay[m];
+        };
+        // each wave: every (n_waves kTableParts)-th chunk of 64 entries (the
+        // nonzero ones cluster at the angles of the field points); nonzero
+        // ones are compacted into the wave's LDS list and run 64 at a time
+        int cntl = 0;                                        // wave-uniform list length (< 64 between chunks)
+        for (int j0 = (part * n_waves + wave) * 64; j0 < n; j0 += n_waves * kTableParts * 64) {
+            const int j = j0 + lane;
+            bool nz = false;
+            if (j < n) {
+                const long long* a = acc + (int64_t)j * 4;
+                nz = (a[0] | a[1] | a[2] | a[3]) != 0;
+            }
+            const unsigned long long bal = __ballot(nz);
+            const int pre = __popcll(bal & ((1ull << lane) - 1ull));
+            if (nz) lst[cntl + pre] = j;
+            cntl += __popcll(bal);
             wave_lds_sync();
-            if (lane < rem) lst[lane] = moved;
-            wave_lds_sync();
-            cntl = rem;
-            run(mine);
+            if (cntl >= 64) {
+                const int mine = lst[lane];
+                const int rem = cntl - 64;
+                const int moved = lane < rem ? lst[64 + lane] : 0;
+                wave_lds_sync();
+                if (lane < rem) lst[lane] = moved;
+                wave_lds_sync();
+                cntl = rem;
+                run(mine);
+            }
         }
-    }
-    if (cntl > 0) {
-        const int mine = lane < cntl ? lst[lane] : -1;
-        if (mine >= 0) run(mine);
-    }
-    __syncthreads();
-    double* out = partial + b * (int64_t)sc.Lmax;
-    for (int k = tid; k < sc.Lmax; k += WG) {
-        double s = 0.0;
-        for (int w = 0; w < n_waves; ++w) s += s_grad[(int64_t)w * ML + m * sc.Lmax + k];
-        out[k] = s;
+        if (cntl > 0) {
+            const int mine = lane < cntl ? lst[lane] : -1;
+            if (mine >= 0) run(mine);
+        }
+        __syncthreads();
+        double* out = partial + u * sc.Lmax;
+        for (int k = tid; k < sc.Lmax; k += WG) {
+            double s = 0.0;
+            for (int w = 0; w < n_waves; ++w) s += s_grad[(int64_t)w * ML + m * sc.Lmax + k];
+            out[k] = s;
+        }
     }
     if (c_keys) atomicAdd(&stats[ST_ADJ_HITS], c_keys);
     if (c_lay) atomicAdd(&stats[ST_ADJ_LAYERS], c_lay);
 }
 
-int64_t table_adj_blocks(const SceneDev& sc)
-{
-    return (int64_t)sc.D * sc.n_lsel * sc.M * 4;
-}
+int64_t table_adj_rows(const SceneDev& sc) { return table_adj_units(sc); }
 
 size_t table_adj_smem_bytes(const SceneDev& sc)
 {
     return (size_t)smem_layout(sc.M, sc.Lmax, sc.n_slots, 128, sc.bins_x * sc.bins_y, false, 2).total + 2 * 128 * 4;
 }
 
-// grad[d][m][k] = sum over wavelengths, sides and branches (in that order) of
-// the partial rows; zero beyond the mirror's layer count.
+// grad[d][m][k] = sum over wavelengths, sides, branches and parts (in that
+// order) of the partial rows; zero beyond the mirror's layer count.
 __global__ void k_table_reduce(const double* __restrict__ partial, int D, int n_lsel, int M, int Lmax,
                                const int32_t* __restrict__ nlay, double* __restrict__ grad)
 {
@@ -251,7 +287,7 @@ __global__ void k_table_reduce(const double* __restrict__ partial, int D, int n_
     double s = 0.0;
     if (k < nlay[(int64_t)d * M + m])
         for (int l = 0; l < n_lsel; ++l)
-            for (int sb = 0; sb < 4; ++sb)
-                s += partial[((((int64_t)d * n_lsel + l) * M + m) * 4 + sb) * Lmax + k];
+            for (int sb = 0; sb < 4 * kTableParts; ++sb)
+                s += partial[((((int64_t)d * n_lsel + l) * M + m) * 4 * kTableParts + sb) * Lmax + k];
     grad[i] = s;
 }
