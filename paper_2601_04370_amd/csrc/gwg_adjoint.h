@@ -217,153 +217,177 @@ __device__ inline void tmm_adjoint(const double* __restrict__ thk, const uint8_t
     }
 }
 
-// Cotangent row of the taken coefficient with respect to [B; C] at the
-// incident side (Eq. 3 convention; r_p = -r_p of the characteristic matrix).
-__device__ inline void coef_cotangent(const V2d& v, double eta0, bool reflect, bool p_pol, cd G, cd* u1, cd* u2)
-{
-    cd B = mk(v.br, v.bi), C = mk(v.cr, v.ci);
-    cd den = cadd(cscale(B, eta0), C);
-    cd inv2 = cdiv(mk(1.0, 0.0), cmul(den, den));
-    cd dB, dC;
-    if (reflect) {
-        const double sg = p_pol ? -2.0 * eta0 : 2.0 * eta0;
-        dB = cscale(cmul(C, inv2), sg);
-        dC = cscale(cmul(B, inv2), -sg);
-    } else {
-        dB = cscale(inv2, -2.0 * eta0 * eta0);
-        dC = cscale(inv2, -2.0 * eta0);
-    }
-    *u1 = cmul(G, dB);
-    *u2 = cmul(G, dC);
-}
-
 // Adjoint of one mirror hit whose stack has no absorbing layer (every layer
 // matrix has real C, X, Y).  Same contract as tmm_adjoint.  HC = false: no
-// lane of the calling wave has an evanescent slot.  The contraction
-// uses the slot parameters (x_s, y_s, x_p, y_p) = (1/q, q, q/N^2, N^2/q) for a
-// propagating layer or (1/Q, -Q, -Q/N^2, N^2/Q) for an evanescent one
-// (q = iQ), with sg = +1 or -1 respectively:
+// lane of the calling wave has an evanescent slot.  The slot parameters
+// (x_s, y_s, x_p, y_p) are (1/q, q, q/N^2, N^2/q) for a propagating layer or
+// (1/Q, -Q, -Q/N^2, N^2/Q) for an evanescent one (q = iQ), with sg = +1 or -1
+// respectively:
 //     z = sg y_s^2,  z / N^2 = sg y_s x_p,  N^2 = sg y_s y_p.
+//
+// With C = i c a layer is the real matrix R = [[C, X], [-Y, C]] on (B, c), and
+// with u2' = i u2 the covector takes the same real matrix.  A layer's gradient
+// needs the state w and the covector u only as two entries of Q = Re(w u^T),
+//     Im(u1 C) = Q21,  Im(u2 B) = -Q12,
+// and from the layer's exit side to its incident side Q goes to R Q R^-1,
+// which leaves the trace alone.  So three reals a polarization pass the
+// layers: with A = Q11 - Q22, b = Q12, c = Q21 and m = C A + Y b + X c,
+//     b -= X m,  c -= Y m,  A = 2 C m - A
+// (from C^2 + X Y = 1, circular or hyperbolic): 8 operations where walking w
+// and u took 32, and no sign of C, X, Y to keep.
+//     1) segment matrices S_g of K layers, from a sweep;
+//     2) w_g = S_g w_{g+1} from the exit medium up, kept in scratch; the
+//        cotangent rows u_0 of the taken coefficients from w_0;
+//     3) down the segments: u_{g+1}, Q at the segment's exit side from it and
+//        w_{g+1}, then the segment's layers upwards.
+// Going up a segment a reflected hit's Q grows as the rounding it carries, and
+// a transmitted one's, of constant size, gathers at most the square of the
+// segment's transfer growth (as a walk of w against u would).  A reflected
+// hit's covector is c (C, -B) of the state at every depth (a ratio of B and C
+// is differentiated, and the layers are unimodular), which is exact where a
+// covector walked down a reflection band loses itself in rounding; a
+// transmitted one's grows downwards and is walked by S_g.
+// Scratch of the lane: field f of block k at scr + (8 k + f) ss; blocks 0 ..
+// nblk - 1: w_g, nblk .. 2 nblk - 1: S_g.
+struct SegPair { SegMat s, p; };
+
+// One polarization's covector on its way down: u of a transmitted hit, the
+// factor c (in u1) of a reflected one.
+struct CovRow { cd u1, u2; };
+
+__device__ inline CovRow cov_top(const V2d& v, double eta0, bool reflect, bool p_pol, cd G)
+{
+    const cd den = mk(fma(v.br, eta0, v.cr), fma(v.bi, eta0, v.ci));
+    const cd h = cmul(G, cdiv(mk(1.0, 0.0), cmul(den, den)));
+    const double e2 = 2.0 * eta0;
+    return { cscale(h, reflect ? (p_pol ? -e2 : e2) : -(e2 * eta0)), cscale(h, -e2) };
+}
+
+// Q of a covector and a state.
+__device__ inline void cov_q(cd u1, cd u2, const V2d& w, double& A, double& b, double& c)
+{
+    A = fma(w.br, u1.re, -(w.bi * u1.im)) - fma(w.cr, u2.re, -(w.ci * u2.im));
+    b = -fma(w.br, u2.im, w.bi * u2.re);
+    c = fma(w.cr, u1.im, w.ci * u1.re);
+}
+// Q of a reflected hit (covector factor c in u1) at state w.
+__device__ inline void cov_refl(const CovRow& r, const V2d& w, double& A, double& b, double& c)
+{
+    cov_q(mk(fma(r.u1.re, w.cr, -(r.u1.im * w.ci)), fma(r.u1.re, w.ci, r.u1.im * w.cr)),
+          mk(fma(r.u1.im, w.bi, -(r.u1.re * w.br)), -fma(r.u1.re, w.bi, r.u1.im * w.br)), w, A, b, c);
+}
+// A transmitted hit's covector past a segment: u^T S on (u1, i u2).
+__device__ inline void cov_step(CovRow& r, const SegMat& m)
+{
+    const cd u1 = mk(fma(m.m11, r.u1.re, -(m.m21 * r.u2.im)), fma(m.m11, r.u1.im, m.m21 * r.u2.re));
+    r.u2 = mk(fma(m.m12, r.u1.im, m.m22 * r.u2.re), fma(m.m22, r.u2.im, -(m.m12 * r.u1.re)));
+    r.u1 = u1;
+}
+
 template <bool HC = true>
 __device__ inline void tmm_adjoint_lossless(const double* __restrict__ thk, const uint8_t* __restrict__ slot,
                                             int L, bool front, const LaneSlots3& sl, double k0,
                                             double eta0s, double eta0p, bool reflect, cd Gs, cd Gp,
-                                            double* grad_row, double* __restrict__ chk, int64_t cstride,
-                                            bool stored = false, int kseg = kSegL)
+                                            double* grad_row, double* __restrict__ scr, int64_t ss, int nblk)
 {
-    // 1) exit -> incident sweep v_j = M_j v_{j+1}, checkpoints v_K, v_2K, ...
-    //    (K = kseg, the hit's interval, the same as the forward solve's
-    //    for a stored sweep): first the L % K layers above the last multiple of K,
-    //    then whole groups of K layers, each ending in a checkpoint (group 0
-    //    in none: v_0 stays in registers).  stored: the forward solve ran
-    //    this sweep and left v_0 in block 0 and the checkpoints in blocks
-    //    1.. (64-byte blocks, block g at chk + g cstride), with the same
-    //    arithmetic: the half-period sine/cosine, whose sign (-1)^(sum n)
-    //    is put back on each checkpoint and on v_0.
     if (L <= 0) return;
-    const int K = kseg;
-    V2d vs = { 1.0, 0.0, eta0s, 0.0 };
-    V2d vp = { 1.0, 0.0, eta0p, 0.0 };
-    double nsum = 0.0;
-    auto sign_bit = [&]() { return (uint32_t)((int)nsum & 1) << 31; };
-    auto layer_fwd = [&](int jj) {
-        const int idx = front ? jj : (L - 1 - jj);
-        double kq, xs, ys, xp, yp, C, S;
-        sl.lossless(slot[idx], kq, xs, ys, xp, yp);
-        layer_cs_half<double, HC>(kq, thk[idx], &C, &S, &nsum);   // t = 0 gives the identity exactly
-        step_real_d(vs, C, S * xs, S * ys);
-        step_real_d(vp, C, S * xp, S * yp);
+    constexpr int K = kSegUp;
+    const int G = (L - 1) / K + 1;
+    auto put = [&](int k, double a, double b, double c, double d, double e, double f, double g, double h) {
+        double* o = scr + (int64_t)k * 8 * ss;
+        o[0] = a; o[ss] = b; o[2 * ss] = c; o[3 * ss] = d;
+        o[4 * ss] = e; o[5 * ss] = f; o[6 * ss] = g; o[7 * ss] = h;
     };
-    auto checkpoint = [&](int g) {
-        const uint32_t sb = sign_bit();
-        double* c = chk + (int64_t)g * 8 * cstride;
-        c[0] = flip_sign(vs.br, sb); c[cstride] = flip_sign(vs.bi, sb);
-        c[2 * cstride] = flip_sign(vs.cr, sb); c[3 * cstride] = flip_sign(vs.ci, sb);
-        c[4 * cstride] = flip_sign(vp.br, sb); c[5 * cstride] = flip_sign(vp.bi, sb);
-        c[6 * cstride] = flip_sign(vp.cr, sb); c[7 * cstride] = flip_sign(vp.ci, sb);
+    auto get_seg = [&](int g) {
+        SegPair m;
+        const double* p = scr + (int64_t)(nblk + g) * 8 * ss;
+        m.s = { p[0], p[ss], p[2 * ss], p[3 * ss] };
+        m.p = { p[4 * ss], p[5 * ss], p[6 * ss], p[7 * ss] };
+        return m;
     };
-    // a stored block is 64 contiguous bytes, read whole
-    auto read_block = [&](const double* c, V2d& a, V2d& b) {
-        const double2* p = (const double2*)c;
-        const double2 x0 = p[0], x1 = p[1], x2 = p[2], x3 = p[3];
-        a = V2d{ x0.x, x0.y, x1.x, x1.y };
-        b = V2d{ x2.x, x2.y, x3.x, x3.y };
+    // 1), 2)
+    V2d ws = { 1.0, 0.0, eta0s, 0.0 }, wp = { 1.0, 0.0, eta0p, 0.0 };
+    auto up = [&](int g, const SegPair& m) {
+        seg_apply(m.s, ws.br, ws.bi, ws.cr, ws.ci);
+        seg_apply(m.p, wp.br, wp.bi, wp.cr, wp.ci);
+        if (g > 0) put(g, ws.br, ws.bi, ws.cr, ws.ci, wp.br, wp.bi, wp.cr, wp.ci);
     };
-    if (stored) {
-        read_block(chk, vs, vp);
-    } else {
-        const int ng = L / K;
-        for (int jj = L - 1; jj >= ng * K; --jj) layer_fwd(jj);
-        if (ng > 0 && ng * K < L) checkpoint(ng);    // v_{ng K}, after the top layers
-        for (int g = ng - 1; g >= 0; --g) {
+    for (int g = G - 1; g >= 0; --g) {
+        V2d vs = { 1.0, 0.0, -1.0, 0.0 }, vp = { 1.0, 0.0, -1.0, 0.0 };
+        double nsum = 0.0;
+        auto layer = [&](int jj) {
+            const int idx = front ? jj : (L - 1 - jj);
+            double kq, xs, ys, xp, yp, C, S;
+            sl.lossless(slot[idx], kq, xs, ys, xp, yp);
+            layer_cs_half<double, HC>(kq, thk[idx], &C, &S, &nsum);   // t = 0 gives the identity exactly
+            step_real_d(vs, C, S * xs, S * ys);
+            step_real_d(vp, C, S * xp, S * yp);
+        };
+        const int lo = g * K, hi = min(lo + K, L);
 #pragma unroll 2
-            for (int i = K - 1; i >= 0; --i) layer_fwd(g * K + i);
-            if (g > 0) checkpoint(g);
-        }
-        const uint32_t sb = sign_bit();
-        vs = V2d{ flip_sign(vs.br, sb), flip_sign(vs.bi, sb), flip_sign(vs.cr, sb), flip_sign(vs.ci, sb) };
-        vp = V2d{ flip_sign(vp.br, sb), flip_sign(vp.bi, sb), flip_sign(vp.cr, sb), flip_sign(vp.ci, sb) };
+        for (int j = hi - 1; j >= lo; --j) layer(j);
+        // the half-period sines and cosines leave out (-1)^n of each layer
+        const uint32_t sb = (uint32_t)((int)nsum & 1) << 31;
+        const SegPair m = { { flip_sign(vs.br, sb), flip_sign(vs.bi, sb), flip_sign(vs.ci, sb), flip_sign(-vs.cr, sb) },
+                            { flip_sign(vp.br, sb), flip_sign(vp.bi, sb), flip_sign(vp.ci, sb), flip_sign(-vp.cr, sb) } };
+        put(nblk + g, m.s.m11, m.s.m12, m.s.m21, m.s.m22, m.p.m11, m.p.m12, m.p.m21, m.p.m22);
+        up(g, m);
     }
-    // 2) cotangent rows of the taken coefficients
-    cd u1s, u2s, u1p, u2p;
-    coef_cotangent(vs, eta0s, reflect, false, Gs, &u1s, &u2s);
-    coef_cotangent(vp, eta0p, reflect, true, Gp, &u1p, &u2p);
-    // 3) incident -> exit covector sweep.  The state a layer's contraction
-    //    needs, v_j, is walked down from the top of its segment (v_0 from the
-    //    sweep, v_{kK} from checkpoint k) with the inverse layer matrix: a
-    //    lossless layer, circular or hyperbolic, is unimodular with
-    //    M^-1 = [[C, iX], [iY, C]], so one sine/cosine per layer serves the
-    //    contraction, the covector step and the inverse step, and no
-    //    per-segment state is kept.  Checkpoint k + 1 is loaded while segment
-    //    k runs; each layer's LDS operands are loaded one layer ahead.
-    //    The sines and cosines are the half-period ones, (-1)^n times the
-    //    layer's own: after layers 0..j-1 the covector and the walked vector
-    //    both carry the factor (-1)^(n_0 + ... + n_{j-1}), so their
-    //    contraction is exact; a checkpoint (exact sign) joins the walk with
-    //    that factor put on it.
+    // covectors of the taken coefficients, with the gradient's factor 2 k0
     const double k2 = 2.0 * k0;
-    double nsum_c = 0.0;                                // sum of the covector sweep's n so far
-    V2d ws = vs, wp = vp, nws = vs, nwp = vp;
-    auto load_chk = [&](int k) {
-        const double* c = chk + (int64_t)k * (stored ? cstride : 8 * cstride);
-        if (stored) {
-            read_block(c, nws, nwp);
+    CovRow us = cov_top(ws, eta0s, reflect, false, cscale(Gs, k2));
+    CovRow up_ = cov_top(wp, eta0p, reflect, true, cscale(Gp, k2));
+    // 3) the next segment's state and matrix are in flight while a segment runs
+    V2d nws, nwp;
+    SegPair nm;
+    auto fetch = [&](int g) {
+        nm = get_seg(g);
+        if (g + 1 < G) {
+            const double* c = scr + (int64_t)(g + 1) * 8 * ss;
+            nws = V2d{ c[0], c[ss], c[2 * ss], c[3 * ss] };
+            nwp = V2d{ c[4 * ss], c[5 * ss], c[6 * ss], c[7 * ss] };
         } else {
-            nws = V2d{ c[0], c[cstride], c[2 * cstride], c[3 * cstride] };
-            nwp = V2d{ c[4 * cstride], c[5 * cstride], c[6 * cstride], c[7 * cstride] };
+            nws = V2d{ 1.0, 0.0, eta0s, 0.0 };
+            nwp = V2d{ 1.0, 0.0, eta0p, 0.0 };
         }
     };
-    if (K < L) load_chk(1);
-    int gnext = 2;                                      // block of the checkpoint after the loaded one
-    // Software pipeline over the layers, as in the forward sweep: layer
-    // j+1's argument is reduced from slot parameters read one iteration
-    // earlier, layer j+2's parameters and thickness are read, and layer
-    // j+3's slot index.  Indices past the last layer stay at the last.
+    fetch(0);
     using LT = LayerTrig<double, HC>;
-    int idx = front ? 0 : L - 1;
-    const int step = front ? 1 : -1;
-    const int last = front ? L - 1 : 0;
-    auto nxt = [&](int i) { return i == last ? i : i + step; };
-    double kq, xs, ys, xp, yp;
-    sl.lossless(slot[idx], kq, xs, ys, xp, yp);
-    TrigArg ta = LT::reduce(kq, thk[idx]);              // t = 0 gives the identity exactly
-    int idn = nxt(idx);
-    double kq1, xs1, ys1, xp1, yp1;
-    sl.lossless(slot[idn], kq1, xs1, ys1, xp1, yp1);
-    double t1 = thk[idn];
-    int idn2 = nxt(idn);
-    int s2 = slot[idn2];
-    for (int lo = 0; lo < L; lo += K) {
-        if (lo > 0) {
-            const uint32_t sb = (uint32_t)((int)nsum_c & 1) << 31;
-            ws = V2d{ flip_sign(nws.br, sb), flip_sign(nws.bi, sb), flip_sign(nws.cr, sb), flip_sign(nws.ci, sb) };
-            wp = V2d{ flip_sign(nwp.br, sb), flip_sign(nwp.bi, sb), flip_sign(nwp.cr, sb), flip_sign(nwp.ci, sb) };
-            if (lo + K < L) load_chk(gnext);
-            ++gnext;
+    const int step = front ? -1 : 1;
+    for (int g = 0; g < G; ++g) {
+        const int lo = g * K, hi = lo + K < L ? lo + K : L;
+        // Software pipeline over the segment's layers, as in the forward
+        // sweep: the next layer's argument is reduced from slot parameters
+        // read one iteration earlier, the parameters and thickness of the one
+        // after are read, and the slot index of the third.  Indices past the
+        // segment's last layer stay there.
+        const int last = front ? lo : L - 1 - lo;
+        auto nxt = [&](int i) { return i == last ? i : i + step; };
+        int idx = front ? hi - 1 : L - hi;
+        double kq, xs, ys, xp, yp;
+        sl.lossless(slot[idx], kq, xs, ys, xp, yp);
+        const double t0 = thk[idx];
+        int idn = nxt(idx);
+        double kq1, xs1, ys1, xp1, yp1;
+        sl.lossless(slot[idn], kq1, xs1, ys1, xp1, yp1);
+        double t1 = thk[idn];
+        int idn2 = nxt(idn);
+        int s2 = slot[idn2];
+        double As, bs, cs, Ap, bp, cp;
+        if (reflect) {
+            cov_refl(us, nws, As, bs, cs);
+            cov_refl(up_, nwp, Ap, bp, cp);
+        } else {
+            cov_step(us, nm.s);
+            cov_step(up_, nm.p);
+            cov_q(us.u1, us.u2, nws, As, bs, cs);
+            cov_q(up_.u1, up_.u2, nwp, Ap, bp, cp);
         }
-        const int hi = lo + K < L ? lo + K : L;
+        if (g + 1 < G) fetch(g + 1);
+        TrigArg ta = LT::reduce(kq, t0);                    // t = 0 gives the identity exactly
+        double n_unused = 0.0;
 #pragma unroll 4
-        for (int j = lo; j < hi; ++j) {
+        for (int j = hi - 1; j >= lo; --j) {
             const int idn3 = nxt(idn2);
             double kq2, xs2, ys2, xp2, yp2;
             sl.lossless(s2, kq2, xs2, ys2, xp2, yp2);
@@ -371,22 +395,17 @@ __device__ inline void tmm_adjoint_lossless(const double* __restrict__ thk, cons
             s2 = slot[idn3];
             const TrigArg ta1 = LT::reduce(kq1, t1);        // the next layer's (the last layer's again at the end)
             double C, S;
-            LT::eval(ta, &C, &S, &nsum_c);
+            LT::eval(ta, &C, &S, &n_unused);
             const double sXs = S * xs, sYs = S * ys, sXp = S * xp, sYp = S * yp;
             const double gys = (HC && kq < 0.0) ? -ys : ys;       // sg y_s (an evanescent layer: sg = -1)
             // Im(u^T D w) summed over s and p, D = -i k0 [[0, a], [b, 0]]
             // (fused multiply-adds written out: the library builds without
             // contraction)
-            const double i_s1 = fma(u1s.re, ws.ci, u1s.im * ws.cr);   // Im(u1s C_s)
-            const double i_s2 = fma(u2s.re, ws.bi, u2s.im * ws.br);   // Im(u2s B_s)
-            const double i_p1 = fma(u1p.re, wp.ci, u1p.im * wp.cr);   // Im(u1p C_p)
-            const double i_p2 = fma(u2p.re, wp.bi, u2p.im * wp.br);   // Im(u2p B_p)
-            const double g = k2 * fma(gys, fma(yp, i_p2, fma(xp, i_p1, ys * i_s2)), i_s1);
-            atomicAdd(&grad_row[idx], g);
-            cov_step_real(u1s, u2s, C, sXs, sYs);
-            cov_step_real(u1p, u2p, C, sXp, sYp);
-            step_real_d(ws, C, -sXs, -sYs);
-            step_real_d(wp, C, -sXp, -sYp);
+            atomicAdd(&grad_row[idx], fma(gys, fma(-yp, bp, fma(xp, cp, -(ys * bs))), cs));
+            const double ms = fma(C, As, fma(sXs, cs, sYs * bs)), mp = fma(C, Ap, fma(sXp, cp, sYp * bp));
+            const double C2 = C + C;
+            bs = fma(-sXs, ms, bs); cs = fma(-sYs, ms, cs); As = fma(C2, ms, -As);
+            bp = fma(-sXp, mp, bp); cp = fma(-sYp, mp, cp); Ap = fma(C2, mp, -Ap);
             idx = idn; ta = ta1; kq = kq1; xs = xs1; ys = ys1; xp = xp1; yp = yp1;
             idn = idn2; kq1 = kq2; xs1 = xs2; ys1 = ys2; xp1 = xp2; yp1 = yp2; t1 = t2;
             idn2 = idn3;

@@ -115,7 +115,7 @@ struct gwg_ctx {
     bool have_forward = false;
     SceneDev fwd{};
     // adjoint entries recorded by the last forward (GWG_FWD_GRAD)
-    DevBuf adj_ent, adj_cnt, adj_ovf, fwd_tape, adj_ck, adj_order, adj_keys, key_sum;
+    DevBuf adj_ent, adj_cnt, adj_ovf, fwd_tape, adj_ck, adj_order, adj_keys, key_sum, adj_sort, sort_tab;
     // per-(item, wave) mirror hits of the last forward, and the order the
     // next forward of the same decomposition takes its items in
     DevBuf item_work, fwd_order;
@@ -662,7 +662,7 @@ int gwg_destroy(gwg_ctx* c)
         for (DevBuf* b : { &c->stats, &c->partial, &c->scratch, &c->fwd_scratch,
                            &c->loss_work, &c->tmm_tab, &c->tmm_slot, &c->adj_ent, &c->adj_cnt, &c->adj_ovf, &c->fwd_tape,
                            &c->tab, &c->tab_scale, &c->tab_acc, &c->tune_q, &c->tune_c, &c->tune_g, &c->tune_grad,
-                           &c->adj_ck, &c->adj_keys, &c->key_sum, &c->grad_tmp, &c->adj_order, &c->item_work, &c->fwd_order })
+                           &c->adj_ck, &c->adj_keys, &c->key_sum, &c->adj_sort, &c->sort_tab, &c->grad_tmp, &c->adj_order, &c->item_work, &c->fwd_order })
             b->release();
         for (KernelTimer& t : c->timer) t.destroy();
     }
@@ -880,14 +880,17 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         const size_t ent_b = sizeof(double) * (size_t)(total * kEntFields);
         const size_t cnt_b = sizeof(int32_t) * (size_t)(sc.n_items * waves);
         const size_t ovf_b = sizeof(int32_t) * (2 * (size_t)sc.n_items + 1);   // flags, then the list of overflowed items
+        // the order that the per-hit backward of a lossless scene sorts the entries into
+        const size_t sort_b = !sc.memo && !table && sc.slot_complex == 0u ? sizeof(uint32_t) * (size_t)total : 0;
         bool fits;
         if (cap) {
             // nothing may be allocated: use the entries if the buffers already hold them
-            fits = c->adj_ent.p && c->adj_ent.bytes >= ent_b && c->adj_cnt.bytes >= cnt_b && c->adj_ovf.bytes >= ovf_b;
+            fits = c->adj_ent.p && c->adj_ent.bytes >= ent_b && c->adj_cnt.bytes >= cnt_b && c->adj_ovf.bytes >= ovf_b &&
+                   c->adj_sort.bytes >= sort_b;
         } else {
             size_t free_b = 0, total_b = 0;
             (void)hipMemGetInfo(&free_b, &total_b);
-            const double bytes = (double)ent_b + (double)cnt_b + (double)ovf_b;
+            const double bytes = (double)ent_b + (double)cnt_b + (double)ovf_b + (double)sort_b;
             fits = bytes <= std::min<double>(kAdjBudgetBytes, 0.5 * (double)free_b + (double)c->adj_ent.bytes);
         }
         if (fits) {
@@ -897,37 +900,44 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
+            if (sort_b) {
+                rc = ensure_buf(c, c->adj_sort, sort_b, cap, "alloc entry order");
+                if (rc) return rc;
+            }
             HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items + 1, 0u, s), "zero overflow flags");
             c->adj = AdjStore{ (double*)c->adj_ent.p, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, cap_w, waves,
-                               nullptr, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
+                               nullptr, 0, 0, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
             adj = true;
-            // The FP64 solve can keep the adjoint's sweep checkpoints of the
-            // first ck_cap entries of every region (kCkEntriesPerRay per ray,
-            // fewer if memory is short); the adjoint then skips that sweep.
+            // The FP64 solve can keep the adjoint's segment matrices of the
+            // first ck_cap entries of every region (kCkEntriesPerRay per
+            // ray); the adjoint then skips that sweep.  If memory is short,
+            // those of hits whose layers all propagate (half the blocks, and
+            // nearly all hits), then those of the first items only: the
+            // sorted adjoint's waves then have entries of one kind, where a
+            // few of every region would make them sweep for the others.
             const int64_t ck_per = c->tune.ck_entries_per_ray == 0 ? kCkEntriesPerRay : c->tune.ck_entries_per_ray;
             if (precision == GWG_FP64 && !(flags & GWG_FWD_MEMO) && sc.slot_complex == 0u && ck_per > 0) {
-                const int64_t blocks = ck_blocks(sc.Lmax);
                 const int64_t rays_w = (sc.rays_per_tile + wg - 1) / wg * 64;
-                // in quarter entries per ray, down to a quarter
-                for (int64_t per4 = 4 * ck_per; per4 >= 1; --per4) {
-                    const int64_t ck_cap = std::min<int64_t>(cap_w, rays_w * per4 / 4);
-                    const int64_t ck_total = sc.n_items * waves * ck_cap;
-                    const size_t ck_b = sizeof(double) * 8 * (size_t)blocks * (size_t)ck_total;
-                    bool ok;
-                    if (cap) {
-                        ok = c->adj_ck.p && c->adj_ck.bytes >= ck_b;
-                    } else {
-                        size_t free_b = 0, total_b = 0;
-                        (void)hipMemGetInfo(&free_b, &total_b);
-                        ok = (double)ck_b <= std::min<double>(kCkBudgetBytes, 0.5 * (double)free_b + (double)c->adj_ck.bytes);
-                    }
-                    if (!ok) continue;
-                    rc = ensure_buf(c, c->adj_ck, ck_b, cap, "alloc sweep checkpoints");
+                const int64_t ck_cap = std::min<int64_t>(cap_w, rays_w * ck_per);
+                double budget = (double)c->adj_ck.bytes;
+                if (!cap) {
+                    size_t free_b = 0, total_b = 0;
+                    (void)hipMemGetInfo(&free_b, &total_b);
+                    budget = std::min<double>(kCkBudgetBytes, 0.5 * (double)free_b + (double)c->adj_ck.bytes);
+                }
+                const int64_t all = sc.n_items * waves;
+                const double region_b = (double)(sizeof(double) * 8 * (size_t)ck_cap);   // one block of each entry
+                const bool evan = (double)all * region_b * (double)ck_blocks(sc.Lmax) <= budget;
+                const int64_t blocks = evan ? ck_blocks(sc.Lmax) : ck_blocks_circ(sc.Lmax);
+                const int64_t regions = std::min<int64_t>(all, (int64_t)(budget / (region_b * (double)blocks)) / waves * waves);
+                if (regions > 0) {
+                    rc = ensure_buf(c, c->adj_ck, (size_t)region_b * (size_t)(blocks * regions), cap, "alloc segment matrices");
                     if (rc) return rc;
                     c->adj.ck = (double*)c->adj_ck.p;
                     c->adj.ck_cap = ck_cap;
-                    c->adj.ck_total = ck_total;
-                    break;
+                    c->adj.ck_nb = (int32_t)blocks;
+                    c->adj.ck_regions = regions;
+                    c->adj.ck_evan = evan ? 1 : 0;
                 }
             }
         } else if (table) {
@@ -939,7 +949,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items + 1, 0u, s), "zero overflow flags");
             c->adj = AdjStore{ nullptr, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, 0, waves,
-                               nullptr, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
+                               nullptr, 0, 0, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
         }
         adj_sweep = adj || table;
         if (adj && sc.dirs && (sc.memo || table)) {
@@ -1051,12 +1061,18 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     const int64_t n_cu = std::max(c->n_cu, 1);
     const int64_t grid = std::min<int64_t>(
         sc.n_items, n_cu * occupancy(c, sc.table ? KIND_BWD_REGEN_TAB : KIND_BWD_REGEN, sc.precision, wg, smem));
-    const int kind_e = sc.slot_complex == 0u ? KIND_ADJ_LOSSLESS : KIND_ADJ_ENTRIES;
-    const int64_t grid_e = std::min<int64_t>(sc.n_items, n_cu * occupancy(c, kind_e, sc.precision, wg, smem));
+    const bool per_hit = entries && !c->memo && !sc.table;
+    const bool sorted = per_hit && sc.slot_complex == 0u;
+    const int64_t grid_e = per_hit && !sorted
+        ? std::min<int64_t>(sc.n_items, n_cu * occupancy(c, KIND_ADJ_ENTRIES, sc.precision, wg, smem)) : 0;
+    const int64_t grid_s = sorted
+        ? std::min<int64_t>(sorted_rows(sc) * sc.D * sc.M, n_cu * occupancy(c, KIND_ADJ_SORTED, sc.precision, 64, sorted_smem_bytes(sc)))
+        : 0;
     const int kind_m = sc.slot_complex == 0u ? KIND_ADJ_MEMO_LOSSLESS : KIND_ADJ_MEMO;
     const int64_t grid_m = std::min<int64_t>(sc.n_items, n_cu * occupancy(c, kind_m, sc.precision, 64, memo_smem_bytes(sc)));
     const int ML = sc.M * sc.Lmax;
-    int64_t scratch_d = std::max(bwd_scratch_doubles(sc, grid, wg), entries ? adj_scratch_doubles(sc, grid_e, wg) : 0);
+    int64_t scratch_d = std::max(bwd_scratch_doubles(sc, grid, wg), adj_scratch_doubles(sc, grid_e, wg));
+    if (sorted) scratch_d = std::max(scratch_d, sorted_scratch_doubles(sc, grid_s));
     if (entries && c->memo) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_m, 64));
     // memoized entries with keys: summed per item, then one adjoint per key of a point
     const bool keyed = entries && c->memo && c->adj.n_keys &&
@@ -1069,7 +1085,8 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     if (sc.table) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_ta, 128));
     rc = ensure_buf(c, c->scratch, sizeof(double) * (size_t)scratch_d, cap, "alloc adjoint scratch");
     if (rc) return rc;
-    const int64_t partial_d = sc.table ? table_adj_rows(sc) * sc.Lmax : sc.n_items * (int64_t)ML;
+    const int64_t partial_d = sc.table ? table_adj_rows(sc) * sc.Lmax
+                                       : (sc.n_items + (sorted ? sorted_rows(sc) * sc.D : 0)) * (int64_t)ML;
     rc = ensure_buf(c, c->partial, sizeof(double) * (size_t)partial_d, cap, "alloc partial gradients");
     if (rc) return rc;
     rc = ensure_buf(c, c->stats, sizeof(uint64_t) * ST_WORDS, cap, "alloc stats");
@@ -1106,6 +1123,8 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         return GWG_OK;
     }
     if (c->timing && !cap) HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].begin(), s), "timing event");
+    // sorted adjoint: one row per group of items, behind the items' own
+    double* rows = (double*)c->partial.p + (sorted ? sc.n_items * (int64_t)ML : 0);
     if (entries && c->memo) {
         AdjStore st = c->adj;
         if (!keyed) st.n_keys = nullptr;                                     // every item's keys are searched for
@@ -1116,6 +1135,12 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         HIP_CHECK(c, launch_adj_memo(sc, (int)grid_m, d_dL_dI, (unsigned long long*)c->stats.p, (double*)c->partial.p,
                                      st, (double*)c->scratch.p, s),
                   "memoized adjoint kernel");
+    } else if (sorted) {
+        rc = ensure_buf(c, c->sort_tab, sizeof(int32_t) * (size_t)sorted_ints(sc), cap, "alloc entry classes");
+        if (rc) return rc;
+        HIP_CHECK(c, launch_adj_sorted(sc, (int)grid_s, d_dL_dI, (unsigned long long*)c->stats.p, rows, c->adj,
+                                       (uint32_t*)c->adj_sort.p, (int32_t*)c->sort_tab.p, (double*)c->scratch.p, s),
+                  "sorted adjoint kernels");
     } else if (entries) {
         // the entry kernel takes items largest first (entry counts from the
         // forward), so its workgroups finish together
@@ -1140,8 +1165,9 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     rc = ensure_buf(c, c->grad_tmp, sizeof(double) * (size_t)grad_reduce_tmp_doubles(ML, sc.D), cap,
                     "alloc gradient reduction");
     if (rc) return rc;
-    HIP_CHECK(c, launch_grad_reduce((const double*)c->partial.p, sc.n_items / sc.D, ML, sc.D, (double*)c->grad_tmp.p,
-                                    d_grad, sc.nlay, sc.M, sc.Lmax, s),
+    HIP_CHECK(c, launch_grad_reduce(rows, sorted ? sorted_rows(sc) : sc.n_items / sc.D, ML, sc.D, (const double*)c->partial.p,
+                                    sc.n_items / sc.D, c->adj.ovf, sorted ? c->adj.left : nullptr,
+                                    (double*)c->grad_tmp.p, d_grad, sc.nlay, sc.M, sc.Lmax, s),
               "gradient reduction");
     if (stats) return read_stats(c, s, stats);
     return GWG_OK;

@@ -53,13 +53,12 @@ __device__ inline void q_put(const Queue& q, int pos, double kappa, cd Gs, cd Gp
 // KIND: the scene has no absorbing slot (ADJ_LOSSLESS), has one (ADJ_ABSORBING),
 // or either (ADJ_ANY): the entry kernels are compiled for one of them, so that
 // each keeps within the 64 KB instruction cache.
-// stored: chk is the entry's checkpoint block written by the forward solve
-// (lossless stacks; the sweep is not run again).
+// chk: the lane's scratch (blocks of 8 doubles, stride cstride).
 enum { ADJ_ANY = 0, ADJ_LOSSLESS = 1, ADJ_ABSORBING = 2 };
 template <int KIND = ADJ_ANY>
 __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const double* s_thk,
                                    const uint8_t* s_slot, const LaneSlots3& sl, double* gw, double kappa, cd Gs,
-                                   cd Gp, int meta, double* chk, int64_t cstride, bool stored = false)
+                                   cd Gp, int meta, double* chk, int64_t cstride)
 {
     const int m = meta & 255;
     const bool front = (meta >> 8) & 1, refl = (meta >> 9) & 1;
@@ -74,21 +73,15 @@ __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const
     const double q0 = sqrt(z0 > kTinyZ ? z0 : kTinyZ);
     if (KIND == ADJ_LOSSLESS || (KIND == ADJ_ANY && sc.slot_complex == 0u)) {
         // waves whose lanes all see circular layers take the sweep without
-        // the hyperbolic case (same results).  A sweep the forward stored
-        // has its hit's checkpoint interval; a sweep run here takes one
-        // interval for the whole wave (lanes of one interval walk their
-        // segments together), the longer one only if no lane meets an
-        // evanescent layer.
+        // the hyperbolic case
         const bool circ = __ballot(hyp) == 0ull;
-        const int kseg = stored ? ck_interval(hyp) : ck_interval(!circ);
+        const int nblk = sc.Lmax / kSegUp + 1;
         if (circ)
             tmm_adjoint_lossless<false>(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, pl.k0, q0,
-                                        pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, stored,
-                                        kseg);
+                                        pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, nblk);
         else
             tmm_adjoint_lossless<true>(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, pl.k0, q0,
-                                       pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, stored,
-                                       kseg);
+                                       pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, nblk);
     }
     else if (KIND != ADJ_LOSSLESS)
         tmm_adjoint(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, sc.slot_complex,
@@ -147,7 +140,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
     // scratch: the tape (Kmax event slots of every lane), then n_chk x 8
     // checkpoint doubles per lane, then queues per wave
     const TapeRef tape = tape_lane(scratch, sc.Kmax, (int64_t)gridDim.x * n_waves, gwave, lane);
-    const int64_t n_chk = sc.Lmax / kSeg + 1;
+    const int64_t n_chk = adj_blocks(sc.Lmax);
     double* chk = scratch + (int64_t)sc.Kmax * kTapeStride * nthreads + gtid;
     const int qcap = 64 * (sc.Kmax + 1);
     const int64_t n_waves_total = (int64_t)gridDim.x * n_waves;
@@ -309,10 +302,9 @@ struct KindQueue {
     }
 };
 
-// Thin-film part of the adjoint over the entries stored by the forward trace.
-// Items whose regions overflowed are left to k_trace_bwd.  LOSSLESS: the
-// scene has no absorbing slot.
-template <bool LOSSLESS>
+// Thin-film part of the adjoint over the entries stored by the forward trace
+// of scenes with an absorbing slot (of others: k_adj_sorted).  Items whose
+// regions overflowed are left to k_trace_bwd.
 __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const double* __restrict__ dLdI,
                                                      double* __restrict__ partial, AdjStore st,
                                                      double* __restrict__ scratch,
@@ -338,7 +330,7 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
     const int64_t nthreads = (int64_t)gridDim.x * WG;
     double* chk = scratch + (int64_t)blockIdx.x * WG + tid;
     for (int k = tid; k < ST_WORDS; k += WG) s_st[k] = 0ull;
-    unsigned long long c_ahits = 0, c_alay = 0, c_astored = 0;
+    unsigned long long c_ahits = 0, c_alay = 0;
 
     for (int64_t it = draw_item(stats + ST_NEXT0); it < sc.n_items; it = draw_item(stats + ST_NEXT0)) {
         const int64_t item = st.order ? (int64_t)st.order[it] : it;
@@ -400,14 +392,9 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                     const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
                     const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
                     const int mm = (int)(meta & 1023);
-                    // the forward stored this entry's sweep (lossless FP64 stacks)
-                    const bool stored = LOSSLESS && st.ck && k < st.ck_cap;
-                    double* c = stored ? st.ck + ((item * st.waves + rr) * st.ck_cap + k) * 8 : chk;
-                    adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, c,
-                                          stored ? 8 * st.ck_total : nthreads, stored);
+                    adjoint_hit<ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, chk, nthreads);
                     c_ahits += 1;
                     c_alay += (unsigned long long)pl->nlay[mm & 255];
-                    if (stored) c_astored += (unsigned long long)pl->nlay[mm & 255];
                 }
             }
         }
@@ -421,7 +408,6 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
     }
     if (c_ahits) atomicAdd(&s_st[ST_ADJ_HITS], c_ahits);
     if (c_alay) atomicAdd(&s_st[ST_ADJ_LAYERS], c_alay);
-    if (c_astored) atomicAdd(&s_st[ST_ADJ_STORED], c_astored);
     __syncthreads();
     for (int k = tid; k < ST_WORDS; k += WG)
         if (s_st[k]) atomicAdd(&stats[k], s_st[k]);
@@ -429,13 +415,13 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
 
 int64_t adj_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg)
 {
-    return (sc.Lmax / kSeg + 1) * 8 * grid_blocks * wg;
+    return adj_blocks(sc.Lmax) * 8 * grid_blocks * wg;
 }
 
 int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg)
 {
     const int64_t nthreads = grid_blocks * wg;
-    const int64_t n_chk = sc.Lmax / kSeg + 1;
+    const int64_t n_chk = adj_blocks(sc.Lmax);
     const int64_t n_waves = grid_blocks * ((wg + 63) / 64);
     return ((int64_t)sc.Kmax * kTapeStride + n_chk * 8) * nthreads
            + n_waves * ((int64_t)kQFields * 64 * (sc.Kmax + 1) + (int64_t)kHitFields * 64 * sc.Kmax);

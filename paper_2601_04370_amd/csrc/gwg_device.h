@@ -771,30 +771,62 @@ __device__ inline double flip_sign(double x, uint32_t sb)
     return __hiloint2double(__double2hiint(x) ^ (int)sb, __double2loint(x));
 }
 
+// Real 2 x 2 matrix of a run of lossless layers on (B, c), C = i c.
+struct SegMat { double m11, m12, m21, m22; };
+__device__ inline void seg_apply(const SegMat& m, double& br, double& bi, double& cr, double& ci)
+{
+    const double r1 = fma(m.m11, br, m.m12 * ci), r2 = fma(m.m21, br, m.m22 * ci);
+    const double i1 = fma(m.m11, bi, -(m.m12 * cr)), i2 = fma(m.m21, bi, -(m.m22 * cr));
+    br = r1; ci = r2;
+    bi = i1; cr = -i2;
+}
+
 // Lossless stack: one loop body for every layer.  The LDS reads run ahead of
 // the arithmetic: the layer record two layers ahead, the slot's parameters
 // one layer ahead.  HC = false: no layer of any lane is evanescent.
 // In double precision the layers' cosines and sines come from the
 // half-period reduction with the sign (-1)^n of each left out, so the chain
-// vector is (-1)^(sum n) times the exact one; that sign is put back on the
-// stored checkpoints and on the result (exact negations).
-template <typename T, bool HC, class SL, class Cur>
+// vector is (-1)^(sum n) times the exact one; that sign is put back on each
+// segment matrix and on the result (exact negations).
+template <typename T, bool HC, bool SEG, class SL, class Cur>
 __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, int L, const SL& sl, V2<T>& vs,
                                                                      V2<T>& vp, int& es, int& ep, double* ck,
-                                                                     int64_t ckb, int kseg = kSegL)
+                                                                     int64_t ckb, int kseg = kSegL, bool top = false)
 {
     double nsum = 0.0;                                  // sum of the layers' n (exact: small integers)
     auto sign_bit = [&]() { return (uint32_t)((int)nsum & 1) << 31; };
-    // ck (T = double only): the adjoint's sweep checkpoints v_{g kseg}
-    // (incidence-order layer g kseg and below) go to the 64-byte block g at
-    // ck + g ckb, whole; v_0 goes to block 0 after the loop.
-    auto store = [&](int g) {
-        const uint32_t sb = sign_bit();
-        double2* c = (double2*)(ck + (int64_t)g * ckb);
-        c[0] = make_double2(flip_sign((double)vs.br, sb), flip_sign((double)vs.bi, sb));
-        c[1] = make_double2(flip_sign((double)vs.cr, sb), flip_sign((double)vs.ci, sb));
-        c[2] = make_double2(flip_sign((double)vp.br, sb), flip_sign((double)vp.bi, sb));
-        c[3] = make_double2(flip_sign((double)vp.cr, sb), flip_sign((double)vp.ci, sb));
+    // SEG (double precision): the chain runs per segment of kseg layers, as the
+    // segment's real 2 x 2 matrix (with C = i c every layer is the real matrix
+    // [[C, X], [-Y, C]] on (B, c); its columns are the real vectors (br, ci)
+    // and (bi, -cr) that start at the unit vectors), and the segments' product
+    // is applied to the exit vector.  ck, for the adjoint: segment matrix g
+    // (incidence-order layers g kseg and below) goes to the 64-byte block g at
+    // ck + g ckb, whole; of a reflected hit (top) only the result, to block 0.
+    [[maybe_unused]] double a[4], b[4];                 // chain vectors below the current segment
+    if constexpr (SEG) {
+        a[0] = vs.br; a[1] = vs.bi; a[2] = vs.cr; a[3] = vs.ci;
+        b[0] = vp.br; b[1] = vp.bi; b[2] = vp.cr; b[3] = vp.ci;
+        vs = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
+        vp = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
+    }
+    auto segment = [&](int g) {
+        if constexpr (SEG) {
+            const uint32_t sb = sign_bit();
+            const SegMat ms = { flip_sign(vs.br, sb), flip_sign(vs.bi, sb), flip_sign(vs.ci, sb), flip_sign(-vs.cr, sb) };
+            const SegMat mp = { flip_sign(vp.br, sb), flip_sign(vp.bi, sb), flip_sign(vp.ci, sb), flip_sign(-vp.cr, sb) };
+            if (ck && !top) {
+                double2* c = (double2*)(ck + (int64_t)g * ckb);
+                c[0] = make_double2(ms.m11, ms.m12);
+                c[1] = make_double2(ms.m21, ms.m22);
+                c[2] = make_double2(mp.m11, mp.m12);
+                c[3] = make_double2(mp.m21, mp.m22);
+            }
+            seg_apply(ms, a[0], a[1], a[2], a[3]);
+            seg_apply(mp, b[0], b[1], b[2], b[3]);
+            vs = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
+            vp = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
+            nsum = 0.0;
+        }
     };
     // Software pipeline over the layers: while layer j is evaluated and
     // applied, layer j+1's argument is reduced (from slot parameters read
@@ -812,14 +844,12 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
     double t1 = r1.t;
     cur.next();
     LayerRec r2 = cur.get();
-    // loop index j of the next checkpoint (incidence-order layer L-1-j a
-    // positive multiple of kseg, a power of two), or L when none is left.
-    // Checkpoint layers have j = L-1 (mod 4): after the first L mod 4
-    // layers the loop takes four layers at a time and looks for a
-    // checkpoint after the fourth only.
-    const int ksh = 31 - __builtin_clz((unsigned)kseg);
-    int jck = (L - 1) & (kseg - 1);
-    if (jck >= L - 1) jck = L;
+    // loop index j of the next segment's top layer (incidence-order layer
+    // L-1-j a positive multiple of kseg), or L when none is left.  These
+    // layers have j = L-1 (mod 4): after the first L mod 4 layers the loop
+    // takes four layers at a time and looks for one after the fourth only.
+    int gck = seg_of(L - 1, kseg);
+    int jck = gck > 0 ? L - 1 - gck * kseg : L;
     auto layer = [&](int j) {
         cur.next();
         const LayerRec r3 = cur.get();                               // past the stack: pad records
@@ -836,9 +866,10 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
         r2 = r3;
     };
     auto checkpoint = [&](int j) {
-        if (sizeof(T) == 8 && ck && j == jck) {
-            store((L - 1 - j) >> ksh);
-            jck = jck + (1 << ksh) < L - 1 ? jck + (1 << ksh) : L;
+        if (SEG && j == jck) {
+            segment(gck);
+            --gck;
+            jck = gck > 0 ? jck + kseg : L;
         }
     };
     const int pre = L & 3;
@@ -854,12 +885,24 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
         checkpoint(j + 3);
     }
     if constexpr (sizeof(T) == 8) {
-        if (ck) store(0);
-        const uint32_t sb = sign_bit();
-        vs.br = flip_sign(vs.br, sb); vs.bi = flip_sign(vs.bi, sb);
-        vs.cr = flip_sign(vs.cr, sb); vs.ci = flip_sign(vs.ci, sb);
-        vp.br = flip_sign(vp.br, sb); vp.bi = flip_sign(vp.bi, sb);
-        vp.cr = flip_sign(vp.cr, sb); vp.ci = flip_sign(vp.ci, sb);
+        if constexpr (SEG) {
+            segment(0);
+            vs = V2<T>{ a[0], a[1], a[2], a[3] };
+            vp = V2<T>{ b[0], b[1], b[2], b[3] };
+            if (ck && top) {
+                double2* c = (double2*)ck;
+                c[0] = make_double2(a[0], a[1]);
+                c[1] = make_double2(a[2], a[3]);
+                c[2] = make_double2(b[0], b[1]);
+                c[3] = make_double2(b[2], b[3]);
+            }
+        } else {
+            const uint32_t sb = sign_bit();
+            vs.br = flip_sign(vs.br, sb); vs.bi = flip_sign(vs.bi, sb);
+            vs.cr = flip_sign(vs.cr, sb); vs.ci = flip_sign(vs.ci, sb);
+            vp.br = flip_sign(vp.br, sb); vp.bi = flip_sign(vp.bi, sb);
+            vp.cr = flip_sign(vp.cr, sb); vp.ci = flip_sign(vp.ci, sb);
+        }
     }
 }
 
@@ -871,10 +914,10 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
 // and rounded to the chain precision T once per layer.  circ: no lane of the
 // calling wave has an evanescent lossless slot (the sweep then skips the
 // hyperbolic case; the results are the same).  ck (lossless FP64 stacks):
-// the entry's checkpoint blocks for the adjoint's sweep (block g at ck + g
-// ckb, one every kseg layers), or null.
-// TAKEN: finish_coeffs's.
-template <typename T, bool TAKEN = false, class SL, class Stk>
+// the entry's blocks for the adjoint (segment matrices of kseg layers, or
+// the state of a reflected hit), or null.
+// TAKEN: finish_coeffs's.  SEG: lossless_sweep's.
+template <typename T, bool TAKEN = false, bool SEG = false, class SL, class Stk>
 __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk, int L,
                                   bool front, const SL& sl, uint32_t cplx_mask, double k0d, double eta0s,
                                   double eta0p, cd etaEs, cd etaEp, cd tp_factor, bool circ = false,
@@ -887,9 +930,9 @@ __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk,
     if (L <= 0) return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
     if (cplx_mask == 0u) {
         if (circ)
-            lossless_sweep<T, false>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg);
+            lossless_sweep<T, false, SEG>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg, refl);
         else
-            lossless_sweep<T, true>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg);
+            lossless_sweep<T, true, SEG>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg, refl);
         return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
     }
     auto cur = stk.cursor(L, front);

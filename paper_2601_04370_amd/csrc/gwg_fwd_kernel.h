@@ -34,7 +34,8 @@
 template <int MODE, bool TAKEN = false, class SL, class Stks>
 __device__ inline Coef4 hit_solve(int n_slots, uint32_t cplx, const PointLds& pl, const Stks& stks,
                                   const SL& sl, int m, bool front, double kappa,
-                                  bool* used_fp64, double* ck = nullptr, int64_t ckb = 8, bool refl = false)
+                                  bool* used_fp64, double* ck = nullptr, int64_t ckb = 8, bool refl = false,
+                                  bool ck_evan = true)
 {
     bool hyp = false;                       // an evanescent lossless slot at this kappa
     for (int s = 0; s < n_slots; ++s) {
@@ -52,8 +53,9 @@ __device__ inline Coef4 hit_solve(int n_slots, uint32_t cplx, const PointLds& pl
     const bool fp64 = (MODE == GWG_FP64) || (MODE == GWG_FP32_MIXED && near_critical(pl, n_slots, kappa));
     *used_fp64 = fp64;
     if (fp64)
-        return tmm_solve<double, TAKEN>(stk, L, front, sl, cplx, pl.k0, eta0s, eta0p,
-                                 mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ, MODE == GWG_FP64 ? ck : nullptr,
+        return tmm_solve<double, TAKEN, true>(stk, L, front, sl, cplx, pl.k0, eta0s, eta0p,
+                                 mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ,
+                                 MODE == GWG_FP64 && (ck_evan || !hyp) ? ck : nullptr,
                                  ckb, ck_interval(hyp), refl);
     return tmm_solve<float, TAKEN>(stk, L, front, sl, cplx, pl.k0, eta0s, eta0p,
                             mk(eta0s, 0.0), mk(eta0p, 0.0), mk(1.0, 0.0), circ, nullptr, 8, kSegL, refl);
@@ -285,7 +287,7 @@ struct SolveCtx {
 // needed; 6 mirrors of 200 layers, 1.1e10 layer steps: 19.9 -> 18.8 ms).
 template <int MODE, class SL>
 __device__ __attribute__((noinline)) void solve_pool(SolveCtx cx, double* mem, int pool, int Kmax, int ne, int nc,
-                                                     double* ck, int64_t ck_total)
+                                                     double* ck, int ck_nb, bool ck_evan)
 {
     const PointLds& pl = *(const PointLds*)cx.pl;
     const RecStacks stks = { (const LayerRec*)cx.rec, cx.Lmax };
@@ -310,10 +312,10 @@ __device__ __attribute__((noinline)) void solve_pool(SolveCtx cx, double* mem, i
             double* ckp = nullptr;
             if (ck) {
                 const int c = q.ck[slot];
-                if (c >= 0) ckp = ck + (int64_t)c * 8;
+                if (c >= 0) ckp = ck + (int64_t)c * ck_nb * 8;
             }
             const Coef4 c = hit_solve<MODE, true>(n_slots, cplx, pl, stks, sl, m, (word >> 8) & 1, kappa, &u64, ckp,
-                                                  8 * ck_total, (word >> 9) & 1);
+                                                  8, (word >> 9) & 1, ck_evan);
             q.put_taken(h, place, c, word);
             n_fp64 += u64 ? 1ull : 0ull;
             n_lay += (unsigned long long)pl.nlay[m];
@@ -784,7 +786,7 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
         const int64_t first = i0 + (int64_t)wave * 64;
         const int n_rounds = first < i1 ? (int)((i1 - first + WG - 1) / WG) : 0;      // uniform
         const int n_rounds0 = (int)((i1 - i0 + WG - 1) / WG);                          // wave 0's, the most
-        const bool cks = ADJ && !TAB && !MEMO && MODE == GWG_FP64 && st.ck != nullptr;
+        const bool cks = ADJ && !TAB && !MEMO && MODE == GWG_FP64 && st.ck != nullptr && region < st.ck_regions;
         for (int r0 = 0; r0 < (KEYED ? n_rounds0 : n_rounds); r0 += sc.pool) {
             const int nr = max(0, n_rounds - r0 < sc.pool ? n_rounds - r0 : sc.pool);
             int n_e = 0, n_c = 0;                         // the pool's possibly evanescent / other hits (uniform)
@@ -922,7 +924,8 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                 }
             } else {
                 solve_pool<MODE, SlotTable>(cx, pmem, sc.pool, sc.Kmax, n_e, n_c,
-                                            cks ? st.ck + region * st.ck_cap * 8 : nullptr, st.ck_total);
+                                            cks ? st.ck + region * st.ck_cap * st.ck_nb * 8 : nullptr, st.ck_nb,
+                                            st.ck_evan != 0);
                 __threadfence_block();
             }
             for (int s2 = 0; s2 < nr; ++s2) {

@@ -140,27 +140,36 @@ __device__ inline int64_t draw_item(unsigned long long* ctr)
 #include "gwg_dirs.h"
 #include "gwg_fwd_kernel.h"
 #include "gwg_bwd_kernel.h"
+#include "gwg_adj_kernel.h"
 #include "gwg_memo_kernel.h"
 #include "gwg_table_kernel.h"
 #include "gwg_omega_kernel.h"
 
-// Sum per-item partial gradients in item order: grad[d][k] = sum_items(d) partial[item][k].
 // Gradient reduction over the per-item partials, in two launches with a
 // fixed order of additions (the gradient is the same bit for bit from run to
 // run): range r of kGradRanges contiguous item ranges of a design is summed
 // in item order, then the range sums in range order.
 constexpr int kGradRanges = 64;
 
-__global__ void k_grad_ranges(const double* __restrict__ partial, int64_t items_per_design, int ML,
-                              double* __restrict__ tmp)
+// Rows of `partial`: the design's work items, or (left given) its groups of
+// items, and then its regenerated items' rows (ovf) in `regen`.
+__global__ void k_grad_ranges(const double* __restrict__ partial, int64_t rows_per_design, int ML,
+                              const double* __restrict__ regen, int64_t items_per_design, const int32_t* __restrict__ ovf,
+                              const int32_t* __restrict__ left, double* __restrict__ tmp)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int r = blockIdx.y, d = blockIdx.z;
     if (k >= ML) return;
-    const int64_t a = items_per_design * r / kGradRanges, b = items_per_design * (r + 1) / kGradRanges;
-    const double* p = partial + (int64_t)d * items_per_design * ML + k;
+    const int64_t a = rows_per_design * r / kGradRanges, b = rows_per_design * (r + 1) / kGradRanges;
+    const double* p = partial + (int64_t)d * rows_per_design * ML + k;
     double acc = 0.0;
     for (int64_t it = a; it < b; ++it) acc += p[it * ML];
+    if (left && left[0] > 0) {
+        const int64_t i0 = (int64_t)d * items_per_design;
+        const int64_t ia = items_per_design * r / kGradRanges, ib = items_per_design * (r + 1) / kGradRanges;
+        for (int64_t it = i0 + ia; it < i0 + ib; ++it)
+            if (ovf[it]) acc += regen[it * ML + k];
+    }
     tmp[((int64_t)d * kGradRanges + r) * ML + k] = acc;
 }
 
@@ -521,8 +530,8 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
     switch (kind) {
     case KIND_BWD_REGEN: return bwd_blocks_per_cu<false>(precision, wg, smem);
     case KIND_BWD_REGEN_TAB: return bwd_blocks_per_cu<true>(precision, wg, smem);
-    case KIND_ADJ_LOSSLESS:
-        return blocks_per_cu(k_adj_entries<true>, wg, smem);
+    case KIND_ADJ_SORTED:
+        return blocks_per_cu(k_adj_sorted, 64, smem);
     case KIND_ADJ_MEMO:
         return blocks_per_cu(k_adj_memo<false>, 64 * kMemoWaves, smem);
     case KIND_ADJ_MEMO_LOSSLESS:
@@ -536,7 +545,7 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
     case KIND_OMEGA:
         return std::min(blocks_per_cu(k_omega_grad<true>, wg, smem), blocks_per_cu(k_omega_grad<false>, wg, smem));
     default:
-        return blocks_per_cu(k_adj_entries<false>, wg, smem);
+        return blocks_per_cu(k_adj_entries, wg, smem);
     }
 }
 
@@ -589,13 +598,22 @@ hipError_t launch_adj_entries(const SceneDev& sc, int wg, int grid_blocks, const
                               unsigned long long* stats, double* partial, const AdjStore& st, double* scratch,
                               hipStream_t s)
 {
-    size_t sm = bwd_smem_bytes(sc, wg);
-    if (sc.slot_complex == 0u)
-        hipLaunchKernelGGL(k_adj_entries<true>, dim3((unsigned)grid_blocks), dim3(wg), sm, s, sc, dLdI, partial, st,
-                           scratch, stats);
-    else
-        hipLaunchKernelGGL(k_adj_entries<false>, dim3((unsigned)grid_blocks), dim3(wg), sm, s, sc, dLdI, partial, st,
-                           scratch, stats);
+    hipLaunchKernelGGL(k_adj_entries, dim3((unsigned)grid_blocks), dim3(wg), bwd_smem_bytes(sc, wg), s, sc, dLdI, partial, st,
+                       scratch, stats);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_sorted(const SceneDev& sc, int grid_blocks, const double* dLdI, unsigned long long* stats,
+                             double* partial, const AdjStore& st, uint32_t* order, int32_t* ints, double* scratch,
+                             hipStream_t s)
+{
+    SortDev so;
+    sort_shape(sc, &so);
+    so.order = order;
+    so.start = ints;
+    hipLaunchKernelGGL(k_entry_sort, dim3((unsigned)so.groups), dim3(64 * kSortWaves), 0, s, sc, dLdI, st, so);
+    hipLaunchKernelGGL(k_adj_sorted, dim3((unsigned)grid_blocks), dim3(64), sorted_smem_bytes(sc), s, sc, dLdI, partial, st,
+                       so, scratch, stats);
     return hipGetLastError();
 }
 
@@ -714,12 +732,13 @@ hipError_t launch_omega_grad(const SceneDev& sc, int grid_blocks, int wg, const 
     return hipGetLastError();
 }
 
-hipError_t launch_grad_reduce(const double* partial, int64_t items_per_design, int ML, int D, double* tmp,
+hipError_t launch_grad_reduce(const double* partial, int64_t rows_per_design, int ML, int D, const double* regen,
+                              int64_t items_per_design, const int32_t* ovf, const int32_t* left, double* tmp,
                               double* grad, const int32_t* nlay, int M, int Lmax, hipStream_t s)
 {
     int64_t n = (int64_t)D * ML;
     hipLaunchKernelGGL(k_grad_ranges, dim3((unsigned)((ML + 255) / 256), kGradRanges, (unsigned)D), dim3(256), 0, s,
-                       partial, items_per_design, ML, tmp);
+                       partial, rows_per_design, ML, regen, items_per_design, ovf, left, tmp);
     hipLaunchKernelGGL(k_grad_reduce, dim3(grid_for(n, 256, 1 << 30)), dim3(256), 0, s, (const double*)tmp, ML, D, grad);
     hipLaunchKernelGGL(k_mask_padding, dim3(grid_for(n, 256, 1 << 30)), dim3(256), 0, s, grad, nlay, D, M, Lmax);
     return hipGetLastError();

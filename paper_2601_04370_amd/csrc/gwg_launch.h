@@ -20,7 +20,7 @@ size_t tmm_smem_bytes(int L, int n_slots, int wg);
 int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
 
 // KIND_FWD and up: forward kernels, KIND_FWD + gradient + 2 table + 4 memoized + 8 direction table
-enum { KIND_BWD_REGEN = 0, KIND_ADJ_ENTRIES = 1, KIND_ADJ_LOSSLESS = 2, KIND_ADJ_MEMO = 3, KIND_ADJ_MEMO_LOSSLESS = 4,
+enum { KIND_BWD_REGEN = 0, KIND_ADJ_ENTRIES = 1, KIND_ADJ_SORTED = 2, KIND_ADJ_MEMO = 3, KIND_ADJ_MEMO_LOSSLESS = 4,
        KIND_TABLE_ACCUM = 5, KIND_BWD_REGEN_TAB = 6, KIND_OMEGA = 7, KIND_FWD = 8,
        KIND_KEY_ADJ = 64, KIND_KEY_ADJ_LOSSLESS = 65 };
 int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem);
@@ -37,6 +37,14 @@ hipError_t launch_adj_entries(const SceneDev& sc, int wg, int grid_blocks, const
                               unsigned long long* stats, double* partial, const AdjStore& st, double* scratch,
                               hipStream_t s);
 size_t memo_smem_bytes(const SceneDev& sc);
+// the sorted adjoint's shape: partial rows a design, units of work, table words
+int64_t sorted_rows(const SceneDev& sc);
+int64_t sorted_ints(const SceneDev& sc);
+size_t sorted_smem_bytes(const SceneDev& sc);
+int64_t sorted_scratch_doubles(const SceneDev& sc, int64_t grid);
+hipError_t launch_adj_sorted(const SceneDev& sc, int grid_blocks, const double* dLdI, unsigned long long* stats,
+                             double* partial, const AdjStore& st, uint32_t* order, int32_t* ints, double* scratch,
+                             hipStream_t s);
 hipError_t launch_adj_memo(const SceneDev& sc, int grid_blocks, const double* dLdI, unsigned long long* stats,
                            double* partial, const AdjStore& st, double* scratch, hipStream_t s);
 hipError_t launch_table_build(const SceneDev& sc, double* tab, int n_cu, unsigned long long* stats, hipStream_t s);
@@ -59,7 +67,8 @@ size_t omega_scene_bytes(const SceneDev& sc, int wg);
 size_t omega_smem_bytes(const SceneDev& sc, int wg);
 hipError_t launch_omega_grad(const SceneDev& sc, int grid_blocks, int wg, const double* W, const uint32_t* counts,
                              double* partial, double* grad, hipStream_t s);
-hipError_t launch_grad_reduce(const double* partial, int64_t items_per_design, int ML, int D, double* tmp,
+hipError_t launch_grad_reduce(const double* partial, int64_t rows_per_design, int ML, int D, const double* regen,
+                              int64_t items_per_design, const int32_t* ovf, const int32_t* left, double* tmp,
                               double* grad, const int32_t* nlay, int M, int Lmax, hipStream_t s);
 int64_t grad_reduce_tmp_doubles(int ML, int D);
 hipError_t launch_item_order(const int32_t* cnt, int waves, int64_t n_items, int64_t max_count, int32_t* order,
