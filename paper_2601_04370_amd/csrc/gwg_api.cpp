@@ -791,7 +791,7 @@ int gwg_tmm_rt(gwg_ctx* c, const gwg_stack* stack, const gwg_materials* mats, in
     if (tmm_smem_bytes(stack->n_layers, n_slots, 256) > 65536) return fail(c, GWG_E_INVAL, "stack too large for one workgroup");
     HIP_CHECK(c, launch_tmm_rt(precision, stack->thk_nm, (const uint8_t*)c->tmm_slot.p, stack->n_layers,
                                (const double*)c->tmm_tab.p, mats->n_lambda, n_slots, cplx, d_lambda_idx, d_theta,
-                               n_q, d_out, s),
+                               n_q, d_out, std::max(c->n_cu, 1), s),
               "tmm kernel");
     return GWG_OK;
 }

@@ -916,8 +916,9 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
 // hyperbolic case; the results are the same).  ck (lossless FP64 stacks):
 // the entry's blocks for the adjoint (segment matrices of kseg layers, or
 // the state of a reflected hit), or null.
-// TAKEN: finish_coeffs's.  SEG: lossless_sweep's.
-template <typename T, bool TAKEN = false, bool SEG = false, class SL, class Stk>
+// TAKEN: finish_coeffs's.  SEG: lossless_sweep's.  SPLIT: circ picks between
+// two copies of the loop for absorbing stacks, too.
+template <typename T, bool TAKEN = false, bool SEG = false, bool SPLIT = false, class SL, class Stk>
 __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk, int L,
                                   bool front, const SL& sl, uint32_t cplx_mask, double k0d, double eta0s,
                                   double eta0p, cd etaEs, cd etaEp, cd tp_factor, bool circ = false,
@@ -935,29 +936,43 @@ __device__ __attribute__((always_inline)) inline Coef4 tmm_solve(const Stk& stk,
             lossless_sweep<T, true, SEG>(stk.cursor(L, front), L, sl, vs, vp, es, ep, ck, ckb, kseg, refl);
         return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
     }
-    auto cur = stk.cursor(L, front);
-    for (int j = 0; j < L; ++j, cur.next()) {
-        const LayerRec r = cur.get();
-        T t = (T)r.t;                       // t = 0 gives the identity exactly
-        const int s = (int)r.slot;
-        if (!((cplx_mask >> s) & 1u)) {
-            double kq, xs, ys, xp, yp;
-            sl.lossless_r(r, kq, xs, ys, xp, yp);
-            T C, S;
-            layer_cs((T)kq, t, &C, &S);
-            step_real(vs, C, S * (T)xs, S * (T)ys);
-            step_real(vp, C, S * (T)xp, S * (T)yp);
-        } else {
-            double Pd[4];
-            sl.absorbing(s, Pd);
-            T Pl[4] = { (T)Pd[0], (T)Pd[1], (T)Pd[2], (T)Pd[3] };
-            CTv<T> C, Xs, Ys, Xp, Yp;
-            layer_cplx(Pl, k0, t, &C, &Xs, &Ys, &Xp, &Yp);
-            step_cplx(vs, C, Xs, Ys);
-            step_cplx(vp, C, Xp, Yp);
+    // a layer's slot parameters are read one layer ahead (as a lossless
+    // slot's; an absorbing layer reads its own), its record two
+    auto general = [&](auto hc) {
+        auto cur = stk.cursor(L, front);
+        LayerRec r = cur.get();
+        cur.next();
+        LayerRec r1 = cur.get();
+        double kq, xs, ys, xp, yp;
+        sl.lossless_r(r, kq, xs, ys, xp, yp);
+        for (int j = 0; j < L; ++j) {
+            cur.next();
+            const LayerRec r2 = cur.get();
+            double kq1, xs1, ys1, xp1, yp1;
+            sl.lossless_r(r1, kq1, xs1, ys1, xp1, yp1);
+            T t = (T)r.t;                       // t = 0 gives the identity exactly
+            const int s = (int)r.slot;
+            if (!((cplx_mask >> s) & 1u)) {
+                T C, S;
+                layer_cs<T, decltype(hc)::value>((T)kq, t, &C, &S);
+                step_real(vs, C, S * (T)xs, S * (T)ys);
+                step_real(vp, C, S * (T)xp, S * (T)yp);
+            } else {
+                double Pd[4];
+                sl.absorbing(s, Pd);
+                T Pl[4] = { (T)Pd[0], (T)Pd[1], (T)Pd[2], (T)Pd[3] };
+                CTv<T> C, Xs, Ys, Xp, Yp;
+                layer_cplx(Pl, k0, t, &C, &Xs, &Ys, &Xp, &Yp);
+                step_cplx(vs, C, Xs, Ys);
+                step_cplx(vp, C, Xp, Yp);
+            }
+            if (sizeof(T) == 4 && (j & 7) == 7) { renorm(vs, es); renorm(vp, ep); }
+            r = r1; r1 = r2;
+            kq = kq1; xs = xs1; ys = ys1; xp = xp1; yp = yp1;
         }
-        if (sizeof(T) == 4 && (j & 7) == 7) { renorm(vs, es); renorm(vp, ep); }
-    }
+    };
+    if (SPLIT && circ) general(std::false_type{});
+    else general(std::true_type{});
     return finish_coeffs<T, TAKEN>(vs, vp, es, ep, eta0s, eta0p, tp_factor, refl);
 }
 

@@ -252,56 +252,138 @@ __global__ void k_irradiance(const uint64_t* __restrict__ q, int64_t n, double s
 }
 
 // ======================================================== thin-film queries
+// A workgroup takes `chunk` queries at a time and solves them by kind: double
+// precision or single, with an evanescent layer or without.  Queries of all
+// kinds side by side (angles and wavelengths in any order) made nearly every
+// wave run the hyperbolic case and, with mixed precision, both solves.  The
+// waves draw batches of 64 from the list of the chunk's queries by kind, the
+// dearest first; a batch over a border of kinds runs what its queries need.
+// Results do not depend on it.  Bound by vector issue.  2^20 queries:
+//   200 lossless layers, double precision: 480 -> 429 us (40 % evanescent:
+//     355 us if every wave had one kind and issued a vector instruction always)
+//   201 layers, one of them silver, mixed: 1326 -> 713 us, and 636 us with the
+//     slots' parameters read a layer ahead (tmm_solve)
+// chunk: a multiple of 256, at most kTmmChunk; 0: no room for the list in LDS,
+// queries in order.
+constexpr int kTmmChunk = 2048;
+constexpr int kTmmKinds = 4;                 // double 0, 1; single 2, 3; without an evanescent layer: odd
+
 template <int MODE>
 __global__ void __launch_bounds__(256) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot,
                                                 int L, const double* __restrict__ lam_tab, int n_lambda,
                                                 int n_slots, uint32_t cplx_mask,
                                                 const int32_t* __restrict__ lidx,
                                                 const double* __restrict__ theta, int64_t nq,
-                                                double* __restrict__ out)
+                                                double* __restrict__ out, int chunk)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int s_n[kTmmKinds], s_next;
     LayerRec* s_rec = (LayerRec*)smem;
     double* s_sp = (double*)(smem + sizeof(LayerRec) * rec_stride(L));
+    uint16_t* s_list = (uint16_t*)(s_sp + (int64_t)n_slots * LaneSlots5::kPer * 256);
     stage_recs(s_rec, thk, slot, 1, L, LaneSlots5::kPer);
-    __syncthreads();
-    const LaneSlots5 sl = { slot_lane_base(s_sp, n_slots, LaneSlots5::kPer, threadIdx.x) };
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += (int64_t)gridDim.x * blockDim.x) {
-        int li = lidx[q];
-        double th = theta[q];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const LaneSlots5 sl = { slot_lane_base(s_sp, n_slots, LaneSlots5::kPer, tid) };
+    const RecStack stk = { s_rec + kRecPad };
+    // kappa and kind of a valid query
+    auto kind_of = [&](int li, double th, double* kappa, bool* fp64) {
+        const double* lt = lam_tab + (int64_t)li * LT_STRIDE;
+        *kappa = lt[LT_NG] * sin(th);
+        *fp64 = (MODE == GWG_FP64);
+        bool evan = false;
+        for (int s = 0; s < n_slots; ++s) {
+            if (MODE == GWG_FP32_MIXED) *fp64 |= (*kappa > lt[LT_CRIT + 2 * s] && *kappa < lt[LT_CRIT + 2 * s + 1]);
+            // slot_params: an evanescent lossless slot
+            const double nr = lt[LT_SLOT + 2 * s];
+            evan |= !((cplx_mask >> s) & 1u) && nr * nr - *kappa * *kappa <= -kTinyZ;
+        }
+        return (*fp64 ? 0 : 2) + (evan ? 0 : 1);
+    };
+    auto valid = [&](int li, double th) { return li >= 0 && li < n_lambda && th >= 0.0 && th < 1.5707963267948966; };
+    // query i of the chunk from c0; chunk 0: query i
+    int64_t c0 = 0;
+    auto solve = [&](int i) {
+        const int64_t q = c0 + i;
+        const int li = lidx[q];
+        const double th = theta[q];
         double* o = out + q * 8;
-        if (li < 0 || li >= n_lambda || !(th >= 0.0 && th < 1.5707963267948966)) {
+        if (!valid(li, th)) {
             for (int k = 0; k < 8; ++k) o[k] = __builtin_nan("");
-            continue;
+            return;
         }
         const double* lt = lam_tab + (int64_t)li * LT_STRIDE;
-        double k0 = lt[LT_K0], n0 = lt[LT_NG];
-        cd NE = mk(lt[LT_NA], lt[LT_NA + 1]);
-        double kappa = n0 * sin(th);
+        const double k0 = lt[LT_K0], n0 = lt[LT_NG];
+        const cd NE = mk(lt[LT_NA], lt[LT_NA + 1]);
+        double kappa;
+        bool fp64;
+        const bool circ = __ballot((kind_of(li, th, &kappa, &fp64) & 1) == 0) == 0ull;
         for (int s = 0; s < n_slots; ++s) {
             double P[NPF];
             slot_params(lt[LT_SLOT + 2 * s], lt[LT_SLOT + 2 * s + 1], kappa, k0, P);
             sl.put(s, P);
         }
-        double z0 = n0 * n0 - kappa * kappa;
-        double q0 = sqrt(z0 > kTinyZ ? z0 : kTinyZ);
-        cd NE2 = cmul(NE, NE);
+        const double z0 = n0 * n0 - kappa * kappa;
+        const double q0 = sqrt(z0 > kTinyZ ? z0 : kTinyZ);
+        const cd NE2 = cmul(NE, NE);
         cd zE = csub(NE2, mk(kappa * kappa, 0.0));
         if (zE.im == 0.0 && fabs(zE.re) < kTinyZ) zE.re = kTinyZ;
-        cd qE = csqrt_up(zE);
-        cd etaEp = cdiv(NE2, qE);
+        const cd qE = csqrt_up(zE);
+        const cd etaEp = cdiv(NE2, qE);
         // t_p factor cos(theta_0) / cos(theta_exit) = (q0 / n0) / (qE / NE)
-        cd tpf = cdiv(cscale(NE, q0 / n0), qE);
-        bool fp64 = (MODE == GWG_FP64);
-        if (MODE == GWG_FP32_MIXED) {
-            for (int s = 0; s < n_slots; ++s)
-                fp64 |= (kappa > lt[LT_CRIT + 2 * s] && kappa < lt[LT_CRIT + 2 * s + 1]);
-        }
-        const RecStack stk = { s_rec + kRecPad };
-        Coef4 c = fp64 ? tmm_solve<double>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf)
-                       : tmm_solve<float>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf);
+        const cd tpf = cdiv(cscale(NE, q0 / n0), qE);
+        const Coef4 c =
+            fp64 ? tmm_solve<double, false, false, true>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ)
+                 : tmm_solve<float, false, false, true>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ);
         o[0] = c.rs.re; o[1] = c.rs.im; o[2] = c.rp.re; o[3] = c.rp.im;
         o[4] = c.ts.re; o[5] = c.ts.im; o[6] = c.tp.re; o[7] = c.tp.im;
+    };
+    const int step = chunk ? chunk : 256;
+    for (c0 = (int64_t)blockIdx.x * step; c0 < nq; c0 += (int64_t)gridDim.x * step) {
+        const int n = (int)min((int64_t)step, nq - c0);
+        __syncthreads();                                     // the records; the last chunk's list is read
+        if (tid < kTmmKinds) s_n[tid] = 0;
+        if (tid == 0) s_next = 0;
+        __syncthreads();
+        if (chunk) {
+            int kind[kTmmChunk / 256], place[kTmmChunk / 256];
+#pragma unroll
+            for (int u = 0; u < kTmmChunk / 256; ++u) {
+                const int i = u * 256 + tid;
+                kind[u] = -1;
+                place[u] = 0;
+                if (i < n) {
+                    const int li = lidx[c0 + i];
+                    const double th = theta[c0 + i];
+                    double kappa;
+                    bool fp64;
+                    kind[u] = valid(li, th) ? kind_of(li, th, &kappa, &fp64) : kTmmKinds - 1;
+                }
+                for (int k = 0; k < kTmmKinds; ++k) {
+                    const unsigned long long b = __ballot(kind[u] == k);
+                    if (b == 0ull) continue;
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(&s_n[k], __popcll(b));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (kind[u] == k) place[u] = at + __popcll(b & ((1ull << lane) - 1ull));
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kTmmChunk / 256; ++u) {
+                int first = 0;
+                for (int k = 0; k < kTmmKinds; ++k) first += k < kind[u] ? s_n[k] : 0;
+                if (kind[u] >= 0) s_list[first + place[u]] = (uint16_t)(u * 256 + tid);
+            }
+            __syncthreads();
+        }
+        for (;;) {
+            int b = 0;
+            if (lane == 0) b = atomicAdd(&s_next, 64);
+            b = __builtin_amdgcn_readfirstlane(b);
+            if (b >= n) break;
+            const int i = b + lane;
+            if (i < n) solve(chunk ? s_list[i] : i);
+        }
     }
 }
 
@@ -757,22 +839,20 @@ size_t tmm_smem_bytes(int L, int n_slots, int wg)
 
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
                          const double* lam_tab, int n_lambda, int n_slots, uint32_t cplx_mask,
-                         const int32_t* lidx, const double* theta, int64_t nq, double* out, hipStream_t s)
+                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu, hipStream_t s)
 {
+    // as many queries a workgroup as leave two workgroups per CU (what the
+    // registers allow): the longer its list, the fewer its mixed batches
     const int wg = 256;
+    const int64_t want = (nq + 2 * n_cu - 1) / (2 * (int64_t)n_cu);
+    int chunk = (int)std::min<int64_t>(kTmmChunk, (want + wg - 1) / wg * wg);
     size_t sm = tmm_smem_bytes(L, n_slots, wg);
-    dim3 grid(grid_for(nq, wg, 8192)), block(wg);
-    switch (precision) {
-    case GWG_FP64:
-        hipLaunchKernelGGL(k_tmm_rt<GWG_FP64>, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out);
-        break;
-    case GWG_FP32_MIXED:
-        hipLaunchKernelGGL(k_tmm_rt<GWG_FP32_MIXED>, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out);
-        break;
-    default:
-        hipLaunchKernelGGL(k_tmm_rt<GWG_FP32>, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out);
-        break;
-    }
+    if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
+    sm += sizeof(uint16_t) * chunk;
+    dim3 grid(grid_for(nq, chunk ? chunk : wg, 8192)), block(wg);
+    auto k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED>
+                                                                                    : k_tmm_rt<GWG_FP32>;
+    hipLaunchKernelGGL(k, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out, chunk);
     return hipGetLastError();
 }
 
