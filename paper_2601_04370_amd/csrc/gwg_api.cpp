@@ -783,15 +783,22 @@ int gwg_tmm_rt(gwg_ctx* c, const gwg_stack* stack, const gwg_materials* mats, in
     }
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
-    HIP_CHECK(c, c->tmm_tab.ensure(lt.size() * sizeof(double)), "alloc table");
-    HIP_CHECK(c, c->tmm_slot.ensure(sl.size()), "alloc slots");
-    HIP_CHECK(c, hipMemcpyAsync(c->tmm_tab.p, lt.data(), lt.size() * sizeof(double), hipMemcpyHostToDevice, s), "upload table");
-    HIP_CHECK(c, hipMemcpyAsync(c->tmm_slot.p, sl.data(), sl.size(), hipMemcpyHostToDevice, s), "upload slots");
-    HIP_CHECK(c, hipStreamSynchronize(s), "upload");
+    if (stream_capturing(s))
+        return fail(c, GWG_E_HIP, "upload: operation not permitted when stream is capturing");
     if (tmm_smem_bytes(stack->n_layers, n_slots, 256) > 65536) return fail(c, GWG_E_INVAL, "stack too large for one workgroup");
+    // small tables go with the launch; two copies and a synchronization for
+    // them were 22 of a short query's 34 us
+    const bool small = lt.size() * sizeof(double) + (size_t)stack->n_layers <= kTmmTabBytes;
+    if (!small) {
+        HIP_CHECK(c, c->tmm_tab.ensure(lt.size() * sizeof(double)), "alloc table");
+        HIP_CHECK(c, c->tmm_slot.ensure(sl.size()), "alloc slots");
+        HIP_CHECK(c, hipMemcpyAsync(c->tmm_tab.p, lt.data(), lt.size() * sizeof(double), hipMemcpyHostToDevice, s), "upload table");
+        HIP_CHECK(c, hipMemcpyAsync(c->tmm_slot.p, sl.data(), sl.size(), hipMemcpyHostToDevice, s), "upload slots");
+        HIP_CHECK(c, hipStreamSynchronize(s), "upload");
+    }
     HIP_CHECK(c, launch_tmm_rt(precision, stack->thk_nm, (const uint8_t*)c->tmm_slot.p, stack->n_layers,
                                (const double*)c->tmm_tab.p, mats->n_lambda, n_slots, cplx, d_lambda_idx, d_theta,
-                               n_q, d_out, std::max(c->n_cu, 1), s),
+                               n_q, d_out, std::max(c->n_cu, 1), small ? lt.data() : nullptr, sl.data(), s),
               "tmm kernel");
     return GWG_OK;
 }

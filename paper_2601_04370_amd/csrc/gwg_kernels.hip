@@ -2,6 +2,7 @@
 // with fixed-point eyebox scatter, adjoint trace, gradient reduction,
 // irradiance and loss.  Launch wrappers at the end are the only entry points
 // used by the host API (gwg_api.cpp).
+#include <cstring>
 #include <mutex>
 #include <type_traits>
 
@@ -268,14 +269,19 @@ __global__ void k_irradiance(const uint64_t* __restrict__ q, int64_t n, double s
 constexpr int kTmmChunk = 2048;
 constexpr int kTmmKinds = 4;                 // double 0, 1; single 2, 3; without an evanescent layer: odd
 
-template <int MODE>
-__global__ void __launch_bounds__(256) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot,
-                                                int L, const double* __restrict__ lam_tab, int n_lambda,
+// The wavelength rows and the layers' slots travel with the launch.
+struct TmmTab { alignas(16) unsigned char b[kTmmTabBytes]; };
+
+template <int MODE, bool VAL>
+__global__ void __launch_bounds__(256) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot_p,
+                                                int L, const double* __restrict__ lam_p, int n_lambda,
                                                 int n_slots, uint32_t cplx_mask,
                                                 const int32_t* __restrict__ lidx,
                                                 const double* __restrict__ theta, int64_t nq,
-                                                double* __restrict__ out, int chunk)
+                                                double* __restrict__ out, int chunk, const TmmTab tab)
 {
+    const double* const lam_tab = VAL ? (const double*)tab.b : lam_p;
+    const uint8_t* const slot = VAL ? tab.b + (int64_t)n_lambda * LT_STRIDE * 8 : slot_p;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_n[kTmmKinds], s_next;
     LayerRec* s_rec = (LayerRec*)smem;
@@ -839,7 +845,8 @@ size_t tmm_smem_bytes(int L, int n_slots, int wg)
 
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
                          const double* lam_tab, int n_lambda, int n_slots, uint32_t cplx_mask,
-                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu, hipStream_t s)
+                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu,
+                         const double* host_tab, const uint8_t* host_slot, hipStream_t s)
 {
     // as many queries a workgroup as leave two workgroups per CU (what the
     // registers allow): the longer its list, the fewer its mixed batches
@@ -850,9 +857,18 @@ hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, 
     if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
     sm += sizeof(uint16_t) * chunk;
     dim3 grid(grid_for(nq, chunk ? chunk : wg, 8192)), block(wg);
-    auto k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED>
-                                                                                    : k_tmm_rt<GWG_FP32>;
-    hipLaunchKernelGGL(k, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out, chunk);
+    auto k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64, false> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED, false>
+                                                                                           : k_tmm_rt<GWG_FP32, false>;
+    TmmTab tab;
+    if (host_tab) {
+        k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64, true> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED, true>
+                                                                                         : k_tmm_rt<GWG_FP32, true>;
+        const size_t nb = sizeof(double) * LT_STRIDE * (size_t)n_lambda;
+        std::memcpy(tab.b, host_tab, nb);
+        std::memcpy(tab.b + nb, host_slot, (size_t)L);
+    }
+    hipLaunchKernelGGL(k, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out, chunk,
+                       tab);
     return hipGetLastError();
 }
 

@@ -74,9 +74,12 @@ int64_t grad_reduce_tmp_doubles(int ML, int D);
 hipError_t launch_item_order(const int32_t* cnt, int waves, int64_t n_items, int64_t max_count, int32_t* order,
                              hipStream_t s);
 hipError_t launch_irradiance(const uint64_t* q, int64_t n, double scale, double* irr, hipStream_t s);
+// Bytes of wavelength rows and slots that a thin-film launch carries; with
+// more (host_tab null) it reads them from device memory.
+constexpr size_t kTmmTabBytes = 3584;
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
                          const double* lam_tab, int n_lambda, int n_slots, uint32_t cplx_mask,
-                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu,
+                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu, const double* host_tab, const uint8_t* host_slot,
                          hipStream_t s);
 hipError_t launch_loss(const double* I, int D, int nl, int F, int B, int kind, double w_f, double w_e,
                        double* work, double* loss, double* G, hipStream_t s);
