@@ -1,4 +1,4 @@
-// Thin-film adjoint of the entries of lossless stacks, sorted by mirror.
+// Thin-film adjoint of stored entries, sorted by mirror.
 // Included by gwg_kernels.hip inside namespace gwg.
 //
 // A wave whose 64 entries meet one mirror from one side walks one stack in
@@ -54,8 +54,9 @@ __global__ void __launch_bounds__(64 * kSortWaves) k_entry_sort(SceneDev sc, con
     group_items(sc, so, blockIdx.x, &ia, &ib);
     const int64_t dl = blockIdx.x / so.groups_dl;
     const double* lt = sc.lam_tab + dl % sc.n_lsel * LT_STRIDE;
-    double k2e = 1e300;                                  // smallest N^2 of a slot
-    for (int s = 0; s < sc.n_slots; ++s) k2e = fmin(k2e, lt[LT_SLOT + 2 * s] * lt[LT_SLOT + 2 * s]);
+    double k2e = 1e300;                                  // smallest N^2 of a lossless slot
+    for (int s = 0; s < sc.n_slots; ++s)
+        if (!((sc.slot_complex >> s) & 1u)) k2e = fmin(k2e, lt[LT_SLOT + 2 * s] * lt[LT_SLOT + 2 * s]);
     for (int k = tid; k < kSortWaves * kClasses; k += 64 * kSortWaves) ((int*)s_at)[k] = 0;
     __syncthreads();
     // each wave: a contiguous share of the group's regions, 64 entries at a time
@@ -163,6 +164,66 @@ __device__ inline double sum8(double x)
     return x;
 }
 
+// Q at one side of a layer, carried through n layers: up from the exit side of
+// incidence-order layer j0, or (not up) down from its incident side (the
+// inverse layers: S -> -S).  The layers' gradients are added to gw.
+template <bool HC, class SL>
+__device__ __attribute__((always_inline)) inline void class_walk(const LayerRec* rec, int L, bool front, const SL& sl, double As,
+                                                                 double bs, double cs, double Ap, double bp, double cp, int j0,
+                                                                 int n, bool up, double* stage, double* gw)
+{
+    using LT = LayerTrig<double, HC>;
+    const int lane = wave_lane();
+    double n_unused = 0.0;
+    const uint32_t sflip = up ? 0u : 1u << 31;
+    const int i0 = front ? j0 : L - 1 - j0;              // in the mirror's layer order
+    const int dir = front != up ? 1 : -1;
+    // as in the forward sweep: the next layer's argument is reduced from
+    // slot parameters read one layer earlier, the parameters of the one
+    // after are read, and the record of the third (past the stack: pads)
+    const LayerRec* p = rec + i0;
+    const LayerRec r0 = p[0], r1 = p[dir];
+    LayerRec r2 = p[2 * dir];
+    p += 3 * dir;
+    double kq, xs, ys, xp, yp, kq1, xs1, ys1, xp1, yp1;
+    sl.lossless_r(r0, kq, xs, ys, xp, yp);
+    sl.lossless_r(r1, kq1, xs1, ys1, xp1, yp1);
+    double t1 = r1.t;
+    typename LT::Arg ta = LT::reduce(kq, r0.t);          // t = 0 gives the identity exactly
+    for (int k0_ = 0; k0_ < n; k0_ += kStageRows) {
+        const int rows = min(kStageRows, n - k0_);
+        double* o = stage + lane;
+#pragma unroll 4
+        for (int q = 0; q < rows; ++q, o += kStageLanes) {
+            const LayerRec r3 = *p;
+            p += dir;
+            double kq2, xs2, ys2, xp2, yp2;
+            sl.lossless_r(r2, kq2, xs2, ys2, xp2, yp2);
+            const typename LT::Arg ta1 = LT::reduce(kq1, t1);
+            double C, S0;
+            LT::eval(ta, &C, &S0, &n_unused);
+            const double S = flip_sign(S0, sflip);
+            const double sXs = S * xs, sYs = S * ys, sXp = S * xp, sYp = S * yp;
+            const double gys = (HC && kq < 0.0) ? -ys : ys;       // sg y_s (an evanescent layer: sg = -1)
+            *o = fma(gys, fma(-yp, bp, fma(xp, cp, -(ys * bs))), cs);
+            const double ms = fma(C, As, fma(sXs, cs, sYs * bs)), mp = fma(C, Ap, fma(sXp, cp, sYp * bp));
+            const double C2 = C + C;
+            bs = fma(-sXs, ms, bs); cs = fma(-sYs, ms, cs); As = fma(C2, ms, -As);
+            bp = fma(-sXp, mp, bp); cp = fma(-sYp, mp, cp); Ap = fma(C2, mp, -Ap);
+            ta = ta1; kq = kq1; xs = xs1; ys = ys1; xp = xp1; yp = yp1;
+            kq1 = kq2; xs1 = xs2; ys1 = ys2; xp1 = xp2; yp1 = yp2; t1 = r2.t;
+            r2 = r3;
+        }
+        wave_lds_sync();
+        // lane: row lane / 8 (rows past the last: stale, not used)
+        const double2* v = (const double2*)(stage + (lane >> 3) * kStageLanes) + (lane & 7);
+        const double2 v0 = v[0], v1 = v[8], v2 = v[16], v3 = v[24];
+        const double s = sum8(((v0.x + v0.y) + (v1.x + v1.y)) + ((v2.x + v2.y) + (v3.x + v3.y)));
+        if ((lane & 7) == 0 && (lane >> 3) < rows) gw[i0 + dir * (k0_ + (lane >> 3))] += s;
+        wave_lds_sync();
+    }
+}
+
 // The method of tmm_adjoint_lossless for a wave whose lanes meet one mirror (L
 // layers, rec: its records) from one side, all reflected (REFL) or all
 // transmitted, all in segments of K layers.  Lanes without an entry have zero
@@ -180,61 +241,9 @@ __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerR
                                                                     int K, const double* blk, int64_t bstride, double* wst,
                                                                     int64_t wstride, double* stage, double* gw)
 {
-    using LT = LayerTrig<double, HC>;
-    const int lane = wave_lane();
     const double k2 = 2.0 * k0;
-    double n_unused = 0.0;
-    // Q at one side of a layer, carried through n layers: up from the exit
-    // side of incidence-order layer j0, or down from its incident side (the
-    // inverse layers: S -> -S)
     auto walk = [&](double As, double bs, double cs, double Ap, double bp, double cp, int j0, int n, bool up) {
-        const uint32_t sflip = up ? 0u : 1u << 31;
-        const int i0 = front ? j0 : L - 1 - j0;              // in the mirror's layer order
-        const int dir = front != up ? 1 : -1;
-        // as in the forward sweep: the next layer's argument is reduced from
-        // slot parameters read one layer earlier, the parameters of the one
-        // after are read, and the record of the third (past the stack: pads)
-        const LayerRec* p = rec + i0;
-        const LayerRec r0 = p[0], r1 = p[dir];
-        LayerRec r2 = p[2 * dir];
-        p += 3 * dir;
-        double kq, xs, ys, xp, yp, kq1, xs1, ys1, xp1, yp1;
-        sl.lossless_r(r0, kq, xs, ys, xp, yp);
-        sl.lossless_r(r1, kq1, xs1, ys1, xp1, yp1);
-        double t1 = r1.t;
-        typename LT::Arg ta = LT::reduce(kq, r0.t);          // t = 0 gives the identity exactly
-        for (int k0_ = 0; k0_ < n; k0_ += kStageRows) {
-            const int rows = min(kStageRows, n - k0_);
-            double* o = stage + lane;
-#pragma unroll 4
-            for (int q = 0; q < rows; ++q, o += kStageLanes) {
-                const LayerRec r3 = *p;
-                p += dir;
-                double kq2, xs2, ys2, xp2, yp2;
-                sl.lossless_r(r2, kq2, xs2, ys2, xp2, yp2);
-                const typename LT::Arg ta1 = LT::reduce(kq1, t1);
-                double C, S0;
-                LT::eval(ta, &C, &S0, &n_unused);
-                const double S = REFL ? S0 : flip_sign(S0, sflip);
-                const double sXs = S * xs, sYs = S * ys, sXp = S * xp, sYp = S * yp;
-                const double gys = (HC && kq < 0.0) ? -ys : ys;       // sg y_s (an evanescent layer: sg = -1)
-                *o = fma(gys, fma(-yp, bp, fma(xp, cp, -(ys * bs))), cs);
-                const double ms = fma(C, As, fma(sXs, cs, sYs * bs)), mp = fma(C, Ap, fma(sXp, cp, sYp * bp));
-                const double C2 = C + C;
-                bs = fma(-sXs, ms, bs); cs = fma(-sYs, ms, cs); As = fma(C2, ms, -As);
-                bp = fma(-sXp, mp, bp); cp = fma(-sYp, mp, cp); Ap = fma(C2, mp, -Ap);
-                ta = ta1; kq = kq1; xs = xs1; ys = ys1; xp = xp1; yp = yp1;
-                kq1 = kq2; xs1 = xs2; ys1 = ys2; xp1 = xp2; yp1 = yp2; t1 = r2.t;
-                r2 = r3;
-            }
-            wave_lds_sync();
-            // lane: row lane / 8 (rows past the last: stale, not used)
-            const double2* v = (const double2*)(stage + (lane >> 3) * kStageLanes) + (lane & 7);
-            const double2 v0 = v[0], v1 = v[8], v2 = v[16], v3 = v[24];
-            const double s = sum8(((v0.x + v0.y) + (v1.x + v1.y)) + ((v2.x + v2.y) + (v3.x + v3.y)));
-            if ((lane & 7) == 0 && (lane >> 3) < rows) gw[i0 + dir * (k0_ + (lane >> 3))] += s;
-            wave_lds_sync();
-        }
+        class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, j0, n, up, stage, gw);
     };
     auto read = [](const double* q, V2d& a, V2d& b) {
         const double2* p = (const double2*)q;
@@ -299,6 +308,122 @@ __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerR
     }
 }
 
+// Adjoint of a class where the mirror has absorbing layers.  The stack is cut
+// into pieces: absorbing layers, and runs of up to kSegL lossless ones (pc[0]:
+// their number; pc[1 + p]: piece p's first layer in stack order, bit 15 set if
+// it is an absorbing layer).  A run goes as in adjoint_class, half of it down
+// from its top and half up from its exit side (a reflected hit's all up); an
+// absorbing layer takes the state and the covector themselves.  (A reflected
+// hit's covector is c (C, -B) there as well: absorbing layers are unimodular.)
+// own: room for the runs' segment matrices, as wst.
+// 363 points x 4096 rays, 201 layers, one of them silver: 14.3 ms with every
+// four layers solved again between stored states, 5.4 ms in pieces, sorted.
+template <bool HC, class SL>
+__device__ __attribute__((always_inline)) inline void adjoint_pieces(const LayerRec* rec, int L, const uint16_t* pc, bool front,
+                                                                     const SL& sl, double k0, double kappa2, double eta0s,
+                                                                     double eta0p, bool refl, cd Gs, cd Gp, double* own,
+                                                                     double* wst, int64_t wstride, double* stage, double* gw)
+{
+    const int lane = wave_lane();
+    const double k2 = 2.0 * k0;
+    const int P = __builtin_amdgcn_readfirstlane((int)pc[0]);
+    int a = 0, b = 0;                                        // the piece's layers [a, b) in stack order
+    bool absorbing = false;
+    auto piece = [&](int i) {                                // i-th in incidence order
+        const int p = front ? i : P - 1 - i;
+        const int v = __builtin_amdgcn_readfirstlane((int)pc[1 + p]);
+        a = v & 0x7fff;
+        absorbing = (v >> 15) != 0;
+        b = p + 1 < P ? __builtin_amdgcn_readfirstlane((int)pc[2 + p]) & 0x7fff : L;
+    };
+    auto entries = [&](CTv<double>& C, CTv<double>& Xs, CTv<double>& Ys, CTv<double>& Xp, CTv<double>& Yp, double* Pd) {
+        const LayerRec r = rec[a];
+        sl.absorbing((int)r.slot, Pd);
+        layer_cplx(Pd, k0, r.t, &C, &Xs, &Ys, &Xp, &Yp);     // t = 0 gives the identity exactly
+    };
+    auto read = [](const double* q, V2d& x, V2d& y) {
+        const double2* p = (const double2*)q;
+        const double2 x0 = p[0], x1 = p[1], x2 = p[2], x3 = p[3];
+        x = V2d{ x0.x, x0.y, x1.x, x1.y };
+        y = V2d{ x2.x, x2.y, x3.x, x3.y };
+    };
+    V2<double> vs = { 1.0, 0.0, eta0s, 0.0 }, vp = { 1.0, 0.0, eta0p, 0.0 };
+    for (int i = P - 1; i >= 0; --i) {
+        piece(i);
+        if (!absorbing) {
+            int es = 0, ep = 0;
+            const RecCursor cur = { rec + (front ? b - 1 : a), front ? -1 : 1 };
+            lossless_sweep<double, HC, true>(cur, b - a, sl, vs, vp, es, ep, own + i * wstride, wstride, kSegL);
+        } else {
+            CTv<double> C, Xs, Ys, Xp, Yp;
+            double Pd[4];
+            entries(C, Xs, Ys, Xp, Yp, Pd);
+            step_cplx(vs, C, Xs, Ys);
+            step_cplx(vp, C, Xp, Yp);
+        }
+        if (i > 0) {
+            double2* o = (double2*)(wst + i * wstride);
+            o[0] = make_double2(vs.br, vs.bi); o[1] = make_double2(vs.cr, vs.ci);
+            o[2] = make_double2(vp.br, vp.bi); o[3] = make_double2(vp.cr, vp.ci);
+        }
+    }
+    V2d ws = { vs.br, vs.bi, vs.cr, vs.ci }, wp = { vp.br, vp.bi, vp.cr, vp.ci };
+    CovRow us = cov_top(ws, eta0s, refl, false, cscale(Gs, k2));
+    CovRow up = cov_top(wp, eta0p, refl, true, cscale(Gp, k2));
+    for (int i = 0; i < P; ++i) {
+        piece(i);
+        V2d ns = { 1.0, 0.0, eta0s, 0.0 }, np = { 1.0, 0.0, eta0p, 0.0 };       // the states below
+        if (i + 1 < P) read(wst + (i + 1) * wstride, ns, np);
+        if (!absorbing) {
+            const int lo = front ? a : L - b, hi = front ? b : L - a, mid = refl ? lo : (lo + hi) / 2;
+            double As, bs, cs, Ap, bp, cp;
+            if (refl) {
+                cov_refl(us, ns, As, bs, cs);
+                cov_refl(up, np, Ap, bp, cp);
+            } else {
+                cov_q(us.u1, us.u2, ws, As, bs, cs);
+                cov_q(up.u1, up.u2, wp, Ap, bp, cp);
+                class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, lo, mid - lo, false, stage, gw);
+                const double2* q = (const double2*)(own + i * wstride);
+                const double2 x0 = q[0], x1 = q[1], x2 = q[2], x3 = q[3];
+                cov_step(us, SegMat{ x0.x, x0.y, x1.x, x1.y });
+                cov_step(up, SegMat{ x2.x, x2.y, x3.x, x3.y });
+                cov_q(us.u1, us.u2, ns, As, bs, cs);
+                cov_q(up.u1, up.u2, np, Ap, bp, cp);
+            }
+            class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, hi - 1, hi - mid, true, stage, gw);
+        } else {
+            CTv<double> C, Xs, Ys, Xp, Yp;
+            double Pd[4];
+            entries(C, Xs, Ys, Xp, Yp, Pd);
+            const cd N2 = mk(Pd[2], Pd[3]), z = csub(N2, mk(kappa2, 0.0));
+            const cd Bs = mk(ws.br, ws.bi), Cs = mk(ws.cr, ws.ci), Bp = mk(wp.br, wp.bi), Cp = mk(wp.cr, wp.ci);
+            cd u1s = us.u1, u2s = us.u2, u1p = up.u1, u2p = up.u2;
+            if (refl) {
+                u1s = cmul(us.u1, Cs); u2s = cscale(cmul(us.u1, Bs), -1.0);
+                u1p = cmul(up.u1, Cp); u2p = cscale(cmul(up.u1, Bp), -1.0);
+            }
+            // contraction u^T D w, D = -i k0 [[0, a], [b, 0]]
+            const cd As = cadd(cmul(u1s, Cs), cmul(z, cmul(u2s, Bs)));
+            const cd Ap = cadd(cmul(cdiv(z, N2), cmul(u1p, Cp)), cmul(N2, cmul(u2p, Bp)));
+            stage[lane] = As.im + Ap.im;
+            wave_lds_sync();
+            const double2* v = (const double2*)stage + (lane & 7);
+            const double2 v0 = v[0], v1 = v[8], v2 = v[16], v3 = v[24];
+            const double sum = sum8(((v0.x + v0.y) + (v1.x + v1.y)) + ((v2.x + v2.y) + (v3.x + v3.y)));
+            if (lane == 0) gw[a] += sum;
+            wave_lds_sync();
+            if (!refl) {
+                const cd c = mk(C.re, C.im);
+                cov_step(us.u1, us.u2, c, mk(Xs.re, Xs.im), mk(Ys.re, Ys.im));
+                cov_step(up.u1, up.u2, c, mk(Xp.re, Xp.im), mk(Yp.re, Yp.im));
+            }
+        }
+        ws = ns;
+        wp = np;
+    }
+}
+
 struct SortedLayout { int off_pl, off_rec, off_sp, off_stage, off_grad, total; };
 __host__ __device__ inline SortedLayout sorted_layout(int Lmax, int n_slots)
 {
@@ -313,8 +438,9 @@ __host__ __device__ inline SortedLayout sorted_layout(int Lmax, int n_slots)
     return s;
 }
 
-// One wave per workgroup; scratch: per lane 2 ck_blocks(Lmax) blocks of 64
-// bytes, block k of lane t of the grid at scratch + 8 (k nthreads + t).
+// One wave per workgroup; scratch: per lane twice ck_blocks(Lmax) (absorbing
+// slots: max_pieces) blocks of 64 bytes, block k of lane t of the grid at scratch + 8 (k nthreads + t).
+template <bool LOSSLESS>
 __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double* __restrict__ dLdI,
                                                       double* __restrict__ partial, AdjStore st, SortDev so,
                                                       double* __restrict__ scratch,
@@ -332,7 +458,9 @@ __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double*
                             pl->pxy };
     const int64_t wstride = (int64_t)gridDim.x * 64 * 8;
     double* wst = scratch + ((int64_t)blockIdx.x * 64 + lane) * 8;
-    double* own = wst + ck_blocks(sc.Lmax) * wstride;    // segment matrices of a sweep run here
+    // segment matrices of a sweep run here
+    double* own = wst + (LOSSLESS ? ck_blocks(sc.Lmax) : (int64_t)sc.max_pieces) * wstride;
+    __shared__ uint16_t s_pc[kMaxPieces + 1];
     unsigned long long c_hits = 0, c_lay = 0, c_stored = 0;
     int64_t staged = -1;
     for (int k = lane; k < kStageRows * kStageLanes; k += 64) stage[k] = 0.0;
@@ -356,6 +484,7 @@ __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double*
             if (lane < kMaxSlots) {
                 const double nr = lt[LT_SLOT + 2 * lane], ni = lt[LT_SLOT + 2 * lane + 1];
                 pl->slotN[2 * lane] = nr; pl->slotN[2 * lane + 1] = ni;
+                pl->nsq[2 * lane] = nr * nr - ni * ni; pl->nsq[2 * lane + 1] = 2.0 * nr * ni;
                 pl->pxy[2 * lane] = (ni == 0.0 && nr != 0.0) ? 1.0 / (nr * nr) : 0.0;
                 pl->pxy[2 * lane + 1] = nr * nr - ni * ni;
             }
@@ -366,6 +495,7 @@ __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double*
         stage_recs(s_rec, sc.thk + ((int64_t)d * sc.M + m) * sc.Lmax, sc.slot + ((int64_t)d * sc.M + m) * sc.Lmax, 1,
                    sc.Lmax, LaneSlots3x::kPer);
         for (int k = lane; k < sc.Lmax; k += 64) gw[k] = 0.0;
+        if (!LOSSLESS && lane <= kMaxPieces) s_pc[lane] = sc.pieces[((int64_t)d * sc.M + m) * (kMaxPieces + 1) + lane];
         __syncthreads();
         const int L = pl->nlay[m];
         const double k0 = pl->k0, ng = pl->ng;
@@ -403,11 +533,16 @@ __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double*
                 // here (the same arithmetic: whether an entry is stored
                 // decides neither its batch nor its gradient)
                 const int64_t k = rel - region * st.cap_w, greg = ia * st.waves + region;
-                const bool stored = st.ck && greg < st.ck_regions && k < st.ck_cap && (!evan || st.ck_evan);
+                const bool stored = LOSSLESS && st.ck && greg < st.ck_regions && k < st.ck_cap && (!evan || st.ck_evan);
                 const double* blk = stored ? st.ck + (greg * st.ck_cap + k) * st.ck_nb * 8 : own;
                 const int64_t bstride = stored ? 8 : wstride;
                 auto run = [&](auto hc) {
                     constexpr bool HC = decltype(hc)::value;
+                    if constexpr (!LOSSLESS) {
+                        adjoint_pieces<HC>(stk.rec, L, s_pc, front, sl, k0, kappa * kappa, q0, q0p, refl, Gs, Gp, own, wst,
+                                           wstride, stage, gw);
+                        return;
+                    }
                     if (!stored) {
                         V2<double> vs = { 1.0, 0.0, q0, 0.0 }, vp = { 1.0, 0.0, q0p, 0.0 };
                         int es = 0, ep = 0;
@@ -474,4 +609,7 @@ int64_t sorted_ints(const SceneDev& sc)
     return so.groups * (kClasses + 1);
 }
 size_t sorted_smem_bytes(const SceneDev& sc) { return (size_t)sorted_layout(sc.Lmax, sc.n_slots).total; }
-int64_t sorted_scratch_doubles(const SceneDev& sc, int64_t grid) { return 2 * ck_blocks(sc.Lmax) * 8 * 64 * grid; }
+int64_t sorted_scratch_doubles(const SceneDev& sc, int64_t grid)
+{
+    return 2 * (sc.slot_complex ? (int64_t)sc.max_pieces : ck_blocks(sc.Lmax)) * 8 * 64 * grid;
+}

@@ -82,11 +82,11 @@ struct SceneEntry {
     uint64_t hash = 0;
     uint64_t last_use = 0;
     SceneDev sc{};
-    DevBuf lam_tab, dir_tab, slot, nlay, pupil_xy, dirs, dir_n;
+    DevBuf lam_tab, dir_tab, slot, nlay, pupil_xy, dirs, dir_n, pieces;
     std::vector<int32_t> h_nlay;
     void release()
     {
-        for (DevBuf* b : { &lam_tab, &dir_tab, &slot, &nlay, &pupil_xy, &dirs, &dir_n }) b->release();
+        for (DevBuf* b : { &lam_tab, &dir_tab, &slot, &nlay, &pupil_xy, &dirs, &dir_n, &pieces }) b->release();
     }
 };
 // Largest direction table of a scene (1 GiB, 87381 points).
@@ -480,6 +480,29 @@ int build_scene(gwg_ctx* c, const gwg_slab* sl, const gwg_prma* pr, const gwg_ma
         s.fov_y0 = ry->fov_deg[2]; s.fov_y1 = ry->fov_deg[3];
         dirs.assign(4, 0.0);
     }
+    // absorbing slots: each stack's pieces (absorbing layers, runs of lossless
+    // ones) for the sorted adjoint
+    std::vector<uint16_t> pieces;
+    s.max_pieces = 0;
+    if (s.slot_complex != 0u && s.Lmax < 0x8000) {
+        pieces.assign((size_t)DM * (kMaxPieces + 1), 0);
+        for (int64_t i = 0; i < (int64_t)DM; ++i) {
+            uint16_t* pc = &pieces[(size_t)i * (kMaxPieces + 1)];
+            int n = 0, run = 0;
+            for (int j = 0; j < st->n_layers[i] && n <= kMaxPieces; ++j) {
+                const bool ab = (s.slot_complex >> slots[(size_t)i * s.Lmax + j]) & 1u;
+                if (ab || run == 0 || run == kSegL) {
+                    if (n < kMaxPieces) pc[1 + n] = (uint16_t)(j | (ab ? 0x8000 : 0));
+                    ++n;
+                    run = 0;
+                }
+                run = ab ? 0 : run + 1;
+            }
+            if (n > kMaxPieces) { pieces.clear(); s.max_pieces = 0; break; }
+            pc[0] = (uint16_t)n;
+            s.max_pieces = std::max(s.max_pieces, n);
+        }
+    }
     s.N = ry->rays_per_point;
     s.id_base = (int64_t)ry->first_design * s.n_lsel * s.F * s.N;
     s.Kmax = ry->max_events;
@@ -496,6 +519,13 @@ int build_scene(gwg_ctx* c, const gwg_slab* sl, const gwg_prma* pr, const gwg_ma
     HIP_CHECK(c, hipMemcpyAsync(ent->lam_tab.p, lt.data(), lt.size() * sizeof(double), hipMemcpyHostToDevice, stream), "upload lam_tab");
     HIP_CHECK(c, hipMemcpyAsync(ent->dir_tab.p, dirs.data(), dirs.size() * sizeof(double), hipMemcpyHostToDevice, stream), "upload dir_tab");
     HIP_CHECK(c, hipMemcpyAsync(ent->slot.p, slots.data(), slots.size(), hipMemcpyHostToDevice, stream), "upload slots");
+    s.pieces = nullptr;
+    if (!pieces.empty()) {
+        HIP_CHECK(c, ent->pieces.ensure(sizeof(uint16_t) * pieces.size()), "alloc pieces");
+        HIP_CHECK(c, hipMemcpyAsync(ent->pieces.p, pieces.data(), sizeof(uint16_t) * pieces.size(), hipMemcpyHostToDevice, stream),
+                  "upload pieces");
+        s.pieces = (const uint16_t*)ent->pieces.p;
+    }
     HIP_CHECK(c, hipMemcpyAsync(ent->nlay.p, st->n_layers, sizeof(int32_t) * DM, hipMemcpyHostToDevice, stream), "upload n_layers");
     HIP_CHECK(c, hipStreamSynchronize(stream), "scene upload");
     s.lam_tab = (const double*)ent->lam_tab.p;
@@ -887,8 +917,8 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         const size_t ent_b = sizeof(double) * (size_t)(total * kEntFields);
         const size_t cnt_b = sizeof(int32_t) * (size_t)(sc.n_items * waves);
         const size_t ovf_b = sizeof(int32_t) * (2 * (size_t)sc.n_items + 1);   // flags, then the list of overflowed items
-        // the order that the per-hit backward of a lossless scene sorts the entries into
-        const size_t sort_b = !sc.memo && !table && sc.slot_complex == 0u ? sizeof(uint32_t) * (size_t)total : 0;
+        // the order that the per-hit backward sorts the entries into
+        const size_t sort_b = !sc.memo && !table && (sc.slot_complex == 0u || sc.pieces) ? sizeof(uint32_t) * (size_t)total : 0;
         bool fits;
         if (cap) {
             // nothing may be allocated: use the entries if the buffers already hold them
@@ -1069,11 +1099,12 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     const int64_t grid = std::min<int64_t>(
         sc.n_items, n_cu * occupancy(c, sc.table ? KIND_BWD_REGEN_TAB : KIND_BWD_REGEN, sc.precision, wg, smem));
     const bool per_hit = entries && !c->memo && !sc.table;
-    const bool sorted = per_hit && sc.slot_complex == 0u;
+    const bool sorted = per_hit && (sc.slot_complex == 0u || sc.pieces);
     const int64_t grid_e = per_hit && !sorted
         ? std::min<int64_t>(sc.n_items, n_cu * occupancy(c, KIND_ADJ_ENTRIES, sc.precision, wg, smem)) : 0;
     const int64_t grid_s = sorted
-        ? std::min<int64_t>(sorted_rows(sc) * sc.D * sc.M, n_cu * occupancy(c, KIND_ADJ_SORTED, sc.precision, 64, sorted_smem_bytes(sc)))
+        ? std::min<int64_t>(sorted_rows(sc) * sc.D * sc.M, n_cu * occupancy(c, sc.slot_complex == 0u ? KIND_ADJ_SORTED : KIND_ADJ_SORTED_ABS,
+                                                                             sc.precision, 64, sorted_smem_bytes(sc)))
         : 0;
     const int kind_m = sc.slot_complex == 0u ? KIND_ADJ_MEMO_LOSSLESS : KIND_ADJ_MEMO;
     const int64_t grid_m = std::min<int64_t>(sc.n_items, n_cu * occupancy(c, kind_m, sc.precision, 64, memo_smem_bytes(sc)));

@@ -303,7 +303,9 @@ struct KindQueue {
 };
 
 // Thin-film part of the adjoint over the entries stored by the forward trace
-// of scenes with an absorbing slot (of others: k_adj_sorted).  Items whose
+// of scenes with a stack of more pieces than k_adj_sorted takes (an absorbing
+// layer in about every second: the pieces' states would be as many as its
+// four-layer segments').  Items whose
 // regions overflowed are left to k_trace_bwd.
 __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const double* __restrict__ dLdI,
                                                      double* __restrict__ partial, AdjStore st,

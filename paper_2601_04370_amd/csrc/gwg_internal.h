@@ -138,7 +138,13 @@ constexpr int kNoSlot = 255;
 constexpr int kEntSlotShift = 34;         // meta: bin in bits 10..33, key slot above
 __host__ __device__ inline int ent_bin(int64_t meta) { return (int)((meta >> 10) & 0xffffff); }
 
+constexpr int kMaxPieces = 32;         // pieces of a stack with absorbing layers that the sorted adjoint takes
+
 struct SceneDev {
+    // Absorbing slots: [D][M][kMaxPieces + 1] each stack's pieces (see
+    // adjoint_pieces; null: some stack has more) and the most of any stack.
+    const uint16_t* pieces;
+    int32_t max_pieces;
     // slab
     double T, Lx, ER;
     double px0, pw, ph;

@@ -619,7 +619,9 @@ int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
     case KIND_BWD_REGEN: return bwd_blocks_per_cu<false>(precision, wg, smem);
     case KIND_BWD_REGEN_TAB: return bwd_blocks_per_cu<true>(precision, wg, smem);
     case KIND_ADJ_SORTED:
-        return blocks_per_cu(k_adj_sorted, 64, smem);
+        return blocks_per_cu(k_adj_sorted<true>, 64, smem);
+    case KIND_ADJ_SORTED_ABS:
+        return blocks_per_cu(k_adj_sorted<false>, 64, smem);
     case KIND_ADJ_MEMO:
         return blocks_per_cu(k_adj_memo<false>, 64 * kMemoWaves, smem);
     case KIND_ADJ_MEMO_LOSSLESS:
@@ -700,8 +702,8 @@ hipError_t launch_adj_sorted(const SceneDev& sc, int grid_blocks, const double* 
     so.order = order;
     so.start = ints;
     hipLaunchKernelGGL(k_entry_sort, dim3((unsigned)so.groups), dim3(64 * kSortWaves), 0, s, sc, dLdI, st, so);
-    hipLaunchKernelGGL(k_adj_sorted, dim3((unsigned)grid_blocks), dim3(64), sorted_smem_bytes(sc), s, sc, dLdI, partial, st,
-                       so, scratch, stats);
+    hipLaunchKernelGGL(sc.slot_complex == 0u ? k_adj_sorted<true> : k_adj_sorted<false>, dim3((unsigned)grid_blocks), dim3(64),
+                       sorted_smem_bytes(sc), s, sc, dLdI, partial, st, so, scratch, stats);
     return hipGetLastError();
 }
 
