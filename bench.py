@@ -29,14 +29,14 @@ PEAK_FP64 = 78.6
 # FMA as two and one sine/cosine pair as zero (reported separately):
 #   forward solve 29 = phase 1 + four X/Y products 4 + two real-coefficient
 #     complex 2x2 matrix-vector products 2 x 12;
-#   adjoint 125 = exit-to-incident sweep 29 + inverse step back down 29 +
-#     contraction u^T D w for s and p 39 + covector step for s and p 28;
-#     96 where the forward solve stored the sweep's checkpoints (its 29 are
-#     then part of the forward's work).
+#   adjoint 63 = exit-to-incident sweep 29 + X/Y products 4 + gradient from
+#     the carried reals 7 + those three reals per polarization past the layer 23;
+#     34 where the forward solve stored the sweep's matrices (its 29 are then
+#     part of the forward's work).
 # Adjoint layer steps are counted per hit that enters the thin-film adjoint;
 # regenerated hits (items whose entry regions overflowed) add 29 each.
 FLOP_FWD_LAYER = 29.0
-FLOP_ADJ_LAYER = 125.0
+FLOP_ADJ_LAYER = 63.0
 
 
 def source_hash() -> str:
@@ -464,10 +464,10 @@ def main():
     f_bwd = (FLOP_FWD_LAYER * lay_b + FLOP_ADJ_LAYER * lay_a - FLOP_FWD_LAYER * lay_s) / K
     t_fwd = float(np.mean(kfwd_ms)) * 1e-3
     t_bwd = float(np.mean(kbwd_ms)) * 1e-3
-    # the adjoint launch is the entry kernel (plus the regenerating kernel,
+    # the adjoint launches are the sort and the entry kernel (and the regenerating kernel,
     # which only runs for items whose entry regions overflowed)
     if not fo and t_bwd >= t_fwd:
-        kname, flops, tk = ("k_adj_memo" if a.memo else "k_table_adj" if a.table else "k_adj_entries"), f_bwd, t_bwd
+        kname, flops, tk = ("k_adj_memo" if a.memo else "k_table_adj" if a.table else "k_adj_sorted"), f_bwd, t_bwd
     else:
         kname, flops, tk = "k_trace_fwd", f_fwd, t_fwd
     achieved = flops / tk / 1e12

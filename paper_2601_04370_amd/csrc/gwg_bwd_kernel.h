@@ -19,9 +19,11 @@
 // thin-film solve of the hit adds (dL/dI[bin] / N) d(2 Re(G_s c_s + G_p c_p))/dt_j
 // into the wave's private LDS row of that mirror.
 //
-// Work items go to persistent workgroups with a fixed stride, each wave owns
-// its LDS accumulator, and the per-item partials are summed in item order
-// afterwards, so the gradient is bit-identical from run to run.
+// (Entries of lossless scenes and of scenes with few absorbing layers go to
+// gwg_adj_kernel.h instead.)
+//
+// Each wave owns its LDS accumulator, and the partial rows are summed in a
+// fixed order afterwards, so the gradient is bit-identical from run to run.
 
 constexpr int kQFields = 6;      // kappa, Gs.re, Gs.im, Gp.re, Gp.im, meta
 

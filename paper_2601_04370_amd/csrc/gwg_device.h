@@ -24,9 +24,10 @@
 // so for a coefficient c with cotangent row rho = dc/d[B; C],
 //     dc/dt_j = u_{j-1}^T D_j w_j,  u_{j-1}^T = rho^T M_0..M_{j-1},  w_j = M_j..M_{L-1}[1; eta_exit].
 // The covector u runs from the incident side, the vector w from the exit
-// side; w is recomputed segment by segment from checkpoints stored during a
-// first exit-to-incident sweep, which keeps both recurrences in their
-// numerically stable direction.
+// side, each in its numerically stable direction.  Lossless runs carry only
+// what the derivative needs of both (tmm_adjoint_lossless); stacks with many
+// absorbing layers recompute w segment by segment from states stored during a
+// first exit-to-incident sweep (tmm_adjoint).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -142,8 +142,8 @@ __device__ inline void wave_lds_sync()
 // columns (one per ray) of Kmax slots.  The geometry walk writes hit h of
 // column col to slot h * ncol + col of kap (kappa) and word (its word); the
 // per-hit solves read them in the order of ord (h << 16 | col), the
-// checkpoint slot of the hit's adjoint entry (relative to the wave's region,
-// or -1) from ck, and write the hit's taken coefficients and word at the
+// slot of the hit's adjoint entry (relative to the wave's region, or -1) from
+// ck, and write the hit's taken coefficients and word at the
 // ray's place pos in the field-pass order: word to slot h * ncol + pos of
 // tword, (c_s, c_p) as two 16-byte words to tcoef, the 64 lanes of a field
 // pass side by side, so that its loads are whole cache lines.
@@ -278,9 +278,9 @@ struct SolveCtx {
 // Solve a pool's ne + nc queued hits in batches of 64 (one per lane): ord
 // lists the possibly evanescent hits from its front (positions 0 .. ne-1)
 // and the others from its back (cap-1 down to cap-nc), so the batches of the
-// second kind take the circular-only sweep.  ck (non-null): the checkpoint
-// store of the wave's region; a hit whose slot c >= 0 stores its sweep
-// checkpoints there.
+// second kind take the circular-only sweep.  ck (non-null): the blocks
+// of the wave's region's entries; a hit whose slot c >= 0 stores its segment
+// matrices (reflected: its state) there.
 // Out of line: the layer loop needs some 50 scalar registers for its
 // polynomials, and inlined among the walks it had 20 of them reloaded from
 // vector lanes in every four layers (211 vector instructions where 188 are
@@ -830,8 +830,8 @@ __global__ void __launch_bounds__(256, TAB && DIRS ? (ADJ ? 3 : 4) : 2) k_trace_
                 const int te = t2 & 0xffff, tc = t2 >> 16;
                 n_work += te + tc;
                 // the ray's adjoint entries (rays bound for the eyebox) start
-                // at kent of the wave's region; with a checkpoint store its
-                // hits learn their entries' checkpoint slots
+                // at kent of the wave's region; with a store for their blocks
+                // the ray's hits learn their entries' slots
                 int64_t kent = 0;
                 if (ADJ) {
                     int etot;

@@ -95,7 +95,7 @@ enum StatWord { ST_RAYS = 0, ST_EVENTS = 1, ST_PRMA = 2, ST_FP64 = 3, ST_SAT = 4
 constexpr int kEntFields = 6;
 constexpr int kFwdMemoKeys = 128;      // largest key table of a work item of the keyed forwards
 constexpr int kTableNodesDefault = 8192;
-constexpr int kCkEntriesPerRay = 4;        // sweep checkpoints kept per ray (entry regions)
+constexpr int kCkEntriesPerRay = 4;        // entries per ray that keep their blocks (entry regions)
 constexpr int kPoolMax = 8;                // forward: rounds of 64 rays per wave pool, at most
 constexpr double kCkBudgetBytes = 128.0 * (1ull << 30);
 constexpr int kTableNodesMax = 1 << 20;

@@ -264,7 +264,7 @@ __global__ void k_irradiance(const uint64_t* __restrict__ q, int64_t n, double s
 //     355 us if every wave had one kind and issued a vector instruction always)
 //   201 layers, one of them silver, mixed: 1326 -> 713 us, and 636 us with the
 //     slots' parameters read a layer ahead (tmm_solve)
-// chunk: a multiple of 256, at most kTmmChunk; 0: no room for the list in LDS,
+// chunk: a multiple of 64, at most kTmmChunk; 0: no room for the list in LDS,
 // queries in order.
 constexpr int kTmmChunk = 2048;
 constexpr int kTmmKinds = 4;                 // double 0, 1; single 2, 3; without an evanescent layer: odd
@@ -273,7 +273,7 @@ constexpr int kTmmKinds = 4;                 // double 0, 1; single 2, 3; withou
 struct TmmTab { alignas(16) unsigned char b[kTmmTabBytes]; };
 
 template <int MODE, bool VAL>
-__global__ void __launch_bounds__(256) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot_p,
+__global__ void __launch_bounds__(256, MODE == GWG_FP32 ? 3 : 2) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot_p,
                                                 int L, const double* __restrict__ lam_p, int n_lambda,
                                                 int n_slots, uint32_t cplx_mask,
                                                 const int32_t* __restrict__ lidx,
@@ -850,11 +850,15 @@ hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, 
                          const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu,
                          const double* host_tab, const uint8_t* host_slot, hipStream_t s)
 {
-    // as many queries a workgroup as leave two workgroups per CU (what the
-    // registers allow): the longer its list, the fewer its mixed batches
+    // as many queries a workgroup as fill the GPU once (the longer its list,
+    // the fewer its mixed batches); launches of less than two queries a lane
+    // keep one, else the waves solve their two batches one after another
+    // where other waves could (160000 queries of 200 layers, single
+    // precision: 127 us with 512 a workgroup, 118 with 256)
     const int wg = 256;
-    const int64_t want = (nq + 2 * n_cu - 1) / (2 * (int64_t)n_cu);
-    int chunk = (int)std::min<int64_t>(kTmmChunk, (want + wg - 1) / wg * wg);
+    const int64_t slots = (int64_t)n_cu * (precision == GWG_FP32 ? 3 : 2);
+    const int64_t want = nq < 2 * slots * wg ? wg : (nq + slots - 1) / slots;
+    int chunk = (int)std::min<int64_t>(kTmmChunk, (want + 63) / 64 * 64);
     size_t sm = tmm_smem_bytes(L, n_slots, wg);
     if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
     sm += sizeof(uint16_t) * chunk;

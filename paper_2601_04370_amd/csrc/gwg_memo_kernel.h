@@ -7,8 +7,10 @@
 // part of the gradient is linear in the cotangents,
 //     sum_h 2 Re(G_h dc(kappa_h)/dt) = 2 Re((sum_{h in key} G_h) dc(kappa_key)/dt),
 // so the backward sums the (dL/dI-scaled) cotangents of each key in entry
-// order and runs one thin-film adjoint per key.  One workgroup per item; the
-// sums run in a fixed order, so the gradient is deterministic: kMemoWaves
+// order and runs one thin-film adjoint per key; the sums run in a fixed order,
+// so the gradient is deterministic.  Entries come with their key's slot
+// (k_key_sums, k_key_adj) unless their item met too many keys or their ray left
+// the direction table.  Those are searched: one workgroup per item, kMemoWaves
 // waves each take a contiguous part of the item's entries with their own key
 // table, and wave 0 merges the tables in wave and key order.  An item with
 // more than kMemoKeys keys is drained hit by hit instead.

@@ -7,17 +7,18 @@
 //
 // Backward, for a forward that stored adjoint entries:
 //   1. k_absmax: the largest |dL/dI| (completes the fixed-point scale);
-//   2. k_table_accum: per work item, the entries' dL/dI-scaled cotangents
+//   2. k_table_keys: per work item, the entries' dL/dI-scaled cotangents
 //      are summed per (kappa, mirror, side, branch) key as in the memoized
-//      adjoint, and each key's sums go to its four table entries (an item
-//      with too many keys sends every entry on its own);
+//      adjoint, and each key's sums go to its four table entries;
+//      k_table_accum does so for the entries without keys, which it searches
+//      (an item with too many keys sends every entry on its own);
 //   3. k_trace_bwd regenerates the items whose entry regions overflowed and
 //      sends their cotangents to the accumulators the same way;
-//   4. k_table_adj: one workgroup per (design, wavelength, mirror, side,
-//      branch) runs one thin-film adjoint per table entry with a nonzero
-//      cotangent into its LDS row;
-//   5. k_table_reduce sums the rows over wavelengths, sides and branches in
-//      a fixed order.
+//   4. k_table_adj: kTableParts units per (design, wavelength, mirror, side,
+//      branch) run one thin-film adjoint per table entry with a nonzero
+//      cotangent into their LDS rows;
+//   5. k_table_reduce sums the rows over wavelengths, sides, branches and
+//      parts in a fixed order.
 // Integer accumulation and fixed-order sums make the gradient bit-identical
 // from run to run.
 
