@@ -927,7 +927,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         } else {
             size_t free_b = 0, total_b = 0;
             (void)hipMemGetInfo(&free_b, &total_b);
-            const double bytes = (double)ent_b + (double)cnt_b + (double)ovf_b + (double)sort_b;
+            const double bytes = (double)ent_b + (double)cnt_b + (double)ovf_b;     // (the order: a twelfth more)
             fits = bytes <= std::min<double>(kAdjBudgetBytes, 0.5 * (double)free_b + (double)c->adj_ent.bytes);
         }
         if (fits) {

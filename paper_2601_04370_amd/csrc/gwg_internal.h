@@ -43,8 +43,8 @@ constexpr int kSeg = 4;               // layers per recomputation segment (backw
 // Against 80-bit arithmetic, stacks of 64 and 200 such layers with random
 // thicknesses: 48 layers are 10 to 50 times as accurate as a walk of the
 // inverse layers from every 32nd state, 64 layers are not.  Longer segments
-// also take less memory and time: 1323 points x 8192 rays, forward and adjoint 42.9 ms with
-// 32, 39.0 ms with 64 layers (walked one way).
+// also take less memory and time: 1323 points x 8192 rays, forward and adjoint
+// 42.9 ms with 32, 39.0 ms with 64 layers (walked one way).
 constexpr int kSegL = 24;
 constexpr int kSegLC = 48;                 // twice kSegL; multiples of 4
 __host__ __device__ inline int ck_interval(bool evanescent) { return evanescent ? kSegL : kSegLC; }
