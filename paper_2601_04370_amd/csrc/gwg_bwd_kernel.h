@@ -92,13 +92,14 @@ __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const
 }
 
 // Adjoint thin-film solve of ring-queue entry `pos`.
+template <int KIND>
 __device__ inline void adjoint_entry(const SceneDev& sc, const PointLds& pl, const double* s_thk,
                                      const uint8_t* s_slot, const LaneSlots3& sl, double* gw, const Queue& q,
                                      int pos, double* chk, int64_t cstride)
 {
     const int p = pos % q.cap;
-    adjoint_hit(sc, pl, s_thk, s_slot, sl, gw, q.base[p], mk(q.base[1 * q.cap + p], q.base[2 * q.cap + p]),
-                mk(q.base[3 * q.cap + p], q.base[4 * q.cap + p]), (int)q.base[5 * q.cap + p], chk, cstride);
+    adjoint_hit<KIND>(sc, pl, s_thk, s_slot, sl, gw, q.base[p], mk(q.base[1 * q.cap + p], q.base[2 * q.cap + p]),
+                      mk(q.base[3 * q.cap + p], q.base[4 * q.cap + p]), (int)q.base[5 * q.cap + p], chk, cstride);
 }
 
 // Pushes the entries of one ray onto the ring queue with the dL/dI factor applied.
@@ -112,7 +113,7 @@ struct QueueEmit {
     }
 };
 
-template <int MODE, bool TAB>
+template <int MODE, bool TAB, int KIND>
 __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double* __restrict__ dLdI,
                                                    double* __restrict__ partial,
                                                    double* __restrict__ scratch, int64_t sample_stride,
@@ -240,7 +241,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
             __threadfence_block();
             // phase 2: drain full batches
             while (qcount >= 64) {
-                adjoint_entry(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
+                adjoint_entry<KIND>(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
                 const int m = ((int)q.base[5 * q.cap + (qhead + lane) % q.cap]) & 255;
                 c_ahits += 1;
                 c_alay += (unsigned long long)pl->nlay[m];
@@ -250,7 +251,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
         }
         if (qcount > 0) {
             if (lane < qcount) {
-                adjoint_entry(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
+                adjoint_entry<KIND>(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
                 const int m = ((int)q.base[5 * q.cap + (qhead + lane) % q.cap]) & 255;
                 c_ahits += 1;
                 c_alay += (unsigned long long)pl->nlay[m];
