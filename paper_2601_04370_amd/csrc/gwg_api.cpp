@@ -795,21 +795,34 @@ int gwg_tmm_rt(gwg_ctx* c, const gwg_stack* stack, const gwg_materials* mats, in
     }
     int n_slots = std::max<int>(1, (int)mats_of.size());
     if (mats_of.empty()) mats_of.push_back(stack->mat_in);
-    uint32_t cplx = 0;
-    std::vector<double> lt((size_t)mats->n_lambda * LT_STRIDE, 0.0);
+    TmmRows rows = { n_slots, 0, 0u };
+    for (int q = 0; q < n_slots; ++q)
+        if (!lossless(mats, mats_of[q])) rows.cplx |= 1u << q;
+    // near-critical intervals of the slots that have one at some wavelength
+    // (mixed precision asks for them)
+    std::vector<int> crit;
+    for (int q = 0; q < n_slots && precision == GWG_FP32_MIXED; ++q)
+        for (int l = 0; l < mats->n_lambda; ++l)
+            if (mats->n_im[l * mats->n_mat + mats_of[q]] == 0.0 &&
+                mats->n_re[l * mats->n_mat + mats_of[q]] < mats->n_re[l * mats->n_mat + stack->mat_in]) {
+                crit.push_back(q);
+                break;
+            }
+    rows.n_crit = (int)crit.size();
+    std::vector<double> lt((size_t)mats->n_lambda * rows.stride(), 0.0);
     for (int l = 0; l < mats->n_lambda; ++l) {
-        double* row = &lt[(size_t)l * LT_STRIDE];
-        row[LT_K0] = 2.0 * 3.14159265358979323846 / mats->lambda_nm[l];
-        row[LT_NG] = mats->n_re[l * mats->n_mat + stack->mat_in];
-        row[LT_NA] = mats->n_re[l * mats->n_mat + stack->mat_out];
-        row[LT_NA + 1] = mats->n_im[l * mats->n_mat + stack->mat_out];
+        double* row = &lt[(size_t)l * rows.stride()];
+        const double *nr = mats->n_re + (size_t)l * mats->n_mat, *ni = mats->n_im + (size_t)l * mats->n_mat;
+        row[TR_K0] = 2.0 * 3.14159265358979323846 / mats->lambda_nm[l];
+        row[TR_NG] = nr[stack->mat_in];
+        row[TR_NA] = nr[stack->mat_out];
+        row[TR_NA + 1] = ni[stack->mat_out];
         for (int q = 0; q < n_slots; ++q) {
-            double nr = mats->n_re[l * mats->n_mat + mats_of[q]], ni = mats->n_im[l * mats->n_mat + mats_of[q]];
-            row[LT_SLOT + 2 * q] = nr;
-            row[LT_SLOT + 2 * q + 1] = ni;
-            if (ni != 0.0) cplx |= 1u << q;
-            crit_interval(row[LT_NG], nr, ni, &row[LT_CRIT + 2 * q], &row[LT_CRIT + 2 * q + 1]);
+            row[TR_SLOT + q] = nr[mats_of[q]];
+            if ((rows.cplx >> q) & 1u) row[rows.imag(q)] = ni[mats_of[q]];
         }
+        for (int k = 0; k < rows.n_crit; ++k)
+            crit_interval(row[TR_NG], nr[mats_of[crit[k]]], ni[mats_of[crit[k]]], &row[rows.crit(k)], &row[rows.crit(k) + 1]);
     }
     DeviceGuard g(c->device);
     hipStream_t s = (hipStream_t)stream;
@@ -817,7 +830,7 @@ int gwg_tmm_rt(gwg_ctx* c, const gwg_stack* stack, const gwg_materials* mats, in
         return fail(c, GWG_E_HIP, "upload: operation not permitted when stream is capturing");
     if (tmm_smem_bytes(stack->n_layers, n_slots, 256) > 65536) return fail(c, GWG_E_INVAL, "stack too large for one workgroup");
     // small tables go with the launch; two copies and a synchronization for
-    // them were 22 of a short query's 34 us
+    // them were 22 of a short query's 34 us, whatever the number of wavelengths
     const bool small = lt.size() * sizeof(double) + (size_t)stack->n_layers <= kTmmTabBytes;
     if (!small) {
         HIP_CHECK(c, c->tmm_tab.ensure(lt.size() * sizeof(double)), "alloc table");
@@ -827,8 +840,7 @@ int gwg_tmm_rt(gwg_ctx* c, const gwg_stack* stack, const gwg_materials* mats, in
         HIP_CHECK(c, hipStreamSynchronize(s), "upload");
     }
     HIP_CHECK(c, launch_tmm_rt(precision, stack->thk_nm, (const uint8_t*)c->tmm_slot.p, stack->n_layers,
-                               (const double*)c->tmm_tab.p, mats->n_lambda, n_slots, cplx, d_lambda_idx, d_theta,
-                               n_q, d_out, std::max(c->n_cu, 1), small ? lt.data() : nullptr, sl.data(), s),
+                               (const double*)c->tmm_tab.p, mats->n_lambda, rows, d_lambda_idx, d_theta, n_q, d_out, std::max(c->n_cu, 1), small ? lt.data() : nullptr, sl.data(), s),
               "tmm kernel");
     return GWG_OK;
 }

@@ -253,63 +253,67 @@ __global__ void k_irradiance(const uint64_t* __restrict__ q, int64_t n, double s
 }
 
 // ======================================================== thin-film queries
-// A workgroup takes `chunk` queries at a time and solves them by kind: double
-// precision or single, with an evanescent layer or without.  Queries of all
-// kinds side by side (angles and wavelengths in any order) made nearly every
-// wave run the hyperbolic case and, with mixed precision, both solves.  The
-// waves draw batches of 64 from the list of the chunk's queries by kind, the
-// dearest first; a batch over a border of kinds runs what its queries need.
-// Results do not depend on it.  Bound by vector issue.  2^20 queries:
-//   200 lossless layers, double precision: 480 -> 429 us (40 % evanescent:
+// SORT: a workgroup takes `chunk` queries at a time and solves them by kind:
+// double precision or single, with an evanescent layer or without.  Queries of
+// all kinds side by side (angles and wavelengths in any order) make nearly
+// every wave run the hyperbolic case and, with mixed precision, both solves.
+// The waves draw batches of 64 from the list of the chunk's queries by kind,
+// the dearest first; a batch over a border of kinds runs what its queries need.
+// Else: queries in order, one a lane (tmm_sorted's rule).
+// Results do not depend on it.  Bound by vector issue.  2^20 queries, in order
+// and by kind:
+//   200 lossless layers, double precision: 469 and 422 us (40 % evanescent:
 //     355 us if every wave had one kind and issued a vector instruction always)
-//   201 layers, one of them silver, mixed: 1326 -> 713 us, and 636 us with the
-//     slots' parameters read a layer ahead (tmm_solve)
-// chunk: a multiple of 64, at most kTmmChunk; 0: no room for the list in LDS,
-// queries in order.
+//   201 layers, one of them silver, mixed: 1287 and 619 us
+// chunk: a multiple of 64, at most kTmmChunk.
 constexpr int kTmmChunk = 2048;
 constexpr int kTmmKinds = 4;                 // double 0, 1; single 2, 3; without an evanescent layer: odd
 
-// The wavelength rows and the layers' slots travel with the launch.
+// The wavelength rows and the layers' slots as they travel with the launch.
 struct TmmTab { alignas(16) unsigned char b[kTmmTabBytes]; };
+struct TmmNoTab {};
 
-template <int MODE, bool VAL>
+template <int MODE, bool VAL, bool SORT>
 __global__ void __launch_bounds__(256, MODE == GWG_FP32 ? 3 : 2) k_tmm_rt(const double* __restrict__ thk, const uint8_t* __restrict__ slot_p,
                                                 int L, const double* __restrict__ lam_p, int n_lambda,
-                                                int n_slots, uint32_t cplx_mask,
-                                                const int32_t* __restrict__ lidx,
+                                                TmmRows rows, const int32_t* __restrict__ lidx,
                                                 const double* __restrict__ theta, int64_t nq,
-                                                double* __restrict__ out, int chunk, const TmmTab tab)
+                                                double* __restrict__ out, int chunk,
+                                                const typename std::conditional<VAL, TmmTab, TmmNoTab>::type tab)
 {
-    const double* const lam_tab = VAL ? (const double*)tab.b : lam_p;
-    const uint8_t* const slot = VAL ? tab.b + (int64_t)n_lambda * LT_STRIDE * 8 : slot_p;
+    const double* lam_tab = lam_p;
+    const uint8_t* slot = slot_p;
+    if constexpr (VAL) {
+        lam_tab = (const double*)tab.b;
+        slot = tab.b + (int64_t)n_lambda * rows.stride() * 8;
+    }
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_n[kTmmKinds], s_next;
     LayerRec* s_rec = (LayerRec*)smem;
     double* s_sp = (double*)(smem + sizeof(LayerRec) * rec_stride(L));
-    uint16_t* s_list = (uint16_t*)(s_sp + (int64_t)n_slots * LaneSlots5::kPer * 256);
     stage_recs(s_rec, thk, slot, 1, L, LaneSlots5::kPer);
     const int tid = threadIdx.x, lane = tid & 63;
+    const int n_slots = rows.n_slots;
     const LaneSlots5 sl = { slot_lane_base(s_sp, n_slots, LaneSlots5::kPer, tid) };
     const RecStack stk = { s_rec + kRecPad };
     // kappa and kind of a valid query
-    auto kind_of = [&](int li, double th, double* kappa, bool* fp64) {
-        const double* lt = lam_tab + (int64_t)li * LT_STRIDE;
-        *kappa = lt[LT_NG] * sin(th);
+    auto kind_of = [&](const double* lt, double th, double* kappa, bool* fp64) {
+        *kappa = lt[TR_NG] * sin(th);
         *fp64 = (MODE == GWG_FP64);
         bool evan = false;
         for (int s = 0; s < n_slots; ++s) {
-            if (MODE == GWG_FP32_MIXED) *fp64 |= (*kappa > lt[LT_CRIT + 2 * s] && *kappa < lt[LT_CRIT + 2 * s + 1]);
             // slot_params: an evanescent lossless slot
-            const double nr = lt[LT_SLOT + 2 * s];
-            evan |= !((cplx_mask >> s) & 1u) && nr * nr - *kappa * *kappa <= -kTinyZ;
+            const double nr = lt[TR_SLOT + s];
+            evan |= !((rows.cplx >> s) & 1u) && nr * nr - *kappa * *kappa <= -kTinyZ;
         }
+        if (MODE == GWG_FP32_MIXED)
+            for (int k = 0; k < rows.n_crit; ++k) {
+                const double* c = lt + rows.crit(k);
+                *fp64 |= *kappa > c[0] && *kappa < c[1];
+            }
         return (*fp64 ? 0 : 2) + (evan ? 0 : 1);
     };
     auto valid = [&](int li, double th) { return li >= 0 && li < n_lambda && th >= 0.0 && th < 1.5707963267948966; };
-    // query i of the chunk from c0; chunk 0: query i
-    int64_t c0 = 0;
-    auto solve = [&](int i) {
-        const int64_t q = c0 + i;
+    auto solve = [&](int64_t q) {
         const int li = lidx[q];
         const double th = theta[q];
         double* o = out + q * 8;
@@ -317,15 +321,16 @@ __global__ void __launch_bounds__(256, MODE == GWG_FP32 ? 3 : 2) k_tmm_rt(const 
             for (int k = 0; k < 8; ++k) o[k] = __builtin_nan("");
             return;
         }
-        const double* lt = lam_tab + (int64_t)li * LT_STRIDE;
-        const double k0 = lt[LT_K0], n0 = lt[LT_NG];
-        const cd NE = mk(lt[LT_NA], lt[LT_NA + 1]);
+        const double* lt = lam_tab + (int64_t)li * rows.stride();
+        const double k0 = lt[TR_K0], n0 = lt[TR_NG];
+        const cd NE = mk(lt[TR_NA], lt[TR_NA + 1]);
         double kappa;
         bool fp64;
-        const bool circ = __ballot((kind_of(li, th, &kappa, &fp64) & 1) == 0) == 0ull;
+        const bool circ = __ballot((kind_of(lt, th, &kappa, &fp64) & 1) == 0) == 0ull;
         for (int s = 0; s < n_slots; ++s) {
             double P[NPF];
-            slot_params(lt[LT_SLOT + 2 * s], lt[LT_SLOT + 2 * s + 1], kappa, k0, P);
+            const bool ab = (rows.cplx >> s) & 1u;
+            slot_params(lt[TR_SLOT + s], ab ? lt[rows.imag(s)] : 0.0, kappa, k0, P);
             sl.put(s, P);
         }
         const double z0 = n0 * n0 - kappa * kappa;
@@ -338,57 +343,61 @@ __global__ void __launch_bounds__(256, MODE == GWG_FP32 ? 3 : 2) k_tmm_rt(const 
         // t_p factor cos(theta_0) / cos(theta_exit) = (q0 / n0) / (qE / NE)
         const cd tpf = cdiv(cscale(NE, q0 / n0), qE);
         const Coef4 c =
-            fp64 ? tmm_solve<double, false, false, true>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ)
-                 : tmm_solve<float, false, false, true>(stk, L, true, sl, cplx_mask, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ);
+            fp64 ? tmm_solve<double, false, false, true>(stk, L, true, sl, rows.cplx, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ)
+                 : tmm_solve<float, false, false, true>(stk, L, true, sl, rows.cplx, k0, q0, n0 * n0 / q0, qE, etaEp, tpf, circ);
         o[0] = c.rs.re; o[1] = c.rs.im; o[2] = c.rp.re; o[3] = c.rp.im;
         o[4] = c.ts.re; o[5] = c.ts.im; o[6] = c.tp.re; o[7] = c.tp.im;
     };
-    const int step = chunk ? chunk : 256;
-    for (c0 = (int64_t)blockIdx.x * step; c0 < nq; c0 += (int64_t)gridDim.x * step) {
-        const int n = (int)min((int64_t)step, nq - c0);
+    if constexpr (!SORT) {
+        __syncthreads();                                         // the records
+        for (int64_t q = (int64_t)blockIdx.x * 256 + tid; q < nq; q += (int64_t)gridDim.x * 256) solve(q);
+        return;
+    }
+    __shared__ int s_n[kTmmKinds], s_next;
+    uint16_t* s_list = (uint16_t*)(s_sp + (int64_t)n_slots * LaneSlots5::kPer * 256);
+    for (int64_t c0 = (int64_t)blockIdx.x * chunk; c0 < nq; c0 += (int64_t)gridDim.x * chunk) {
+        const int n = (int)min((int64_t)chunk, nq - c0);
         __syncthreads();                                     // the records; the last chunk's list is read
         if (tid < kTmmKinds) s_n[tid] = 0;
         if (tid == 0) s_next = 0;
         __syncthreads();
-        if (chunk) {
-            int kind[kTmmChunk / 256], place[kTmmChunk / 256];
+        int kind[kTmmChunk / 256], place[kTmmChunk / 256];
 #pragma unroll
-            for (int u = 0; u < kTmmChunk / 256; ++u) {
-                const int i = u * 256 + tid;
-                kind[u] = -1;
-                place[u] = 0;
-                if (i < n) {
-                    const int li = lidx[c0 + i];
-                    const double th = theta[c0 + i];
-                    double kappa;
-                    bool fp64;
-                    kind[u] = valid(li, th) ? kind_of(li, th, &kappa, &fp64) : kTmmKinds - 1;
-                }
-                for (int k = 0; k < kTmmKinds; ++k) {
-                    const unsigned long long b = __ballot(kind[u] == k);
-                    if (b == 0ull) continue;
-                    int at = 0;
-                    if (lane == 0) at = atomicAdd(&s_n[k], __popcll(b));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                    if (kind[u] == k) place[u] = at + __popcll(b & ((1ull << lane) - 1ull));
-                }
+        for (int u = 0; u < kTmmChunk / 256; ++u) {
+            const int i = u * 256 + tid;
+            kind[u] = -1;
+            place[u] = 0;
+            if (i < n) {
+                const int li = lidx[c0 + i];
+                const double th = theta[c0 + i];
+                double kappa;
+                bool fp64;
+                kind[u] = valid(li, th) ? kind_of(lam_tab + (int64_t)li * rows.stride(), th, &kappa, &fp64) : kTmmKinds - 1;
             }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kTmmChunk / 256; ++u) {
-                int first = 0;
-                for (int k = 0; k < kTmmKinds; ++k) first += k < kind[u] ? s_n[k] : 0;
-                if (kind[u] >= 0) s_list[first + place[u]] = (uint16_t)(u * 256 + tid);
+            for (int k = 0; k < kTmmKinds; ++k) {
+                const unsigned long long b = __ballot(kind[u] == k);
+                if (b == 0ull) continue;
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_n[k], __popcll(b));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (kind[u] == k) place[u] = at + __popcll(b & ((1ull << lane) - 1ull));
             }
-            __syncthreads();
         }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTmmChunk / 256; ++u) {
+            int first = 0;
+            for (int k = 0; k < kTmmKinds; ++k) first += k < kind[u] ? s_n[k] : 0;
+            if (kind[u] >= 0) s_list[first + place[u]] = (uint16_t)(u * 256 + tid);
+        }
+        __syncthreads();
         for (;;) {
             int b = 0;
             if (lane == 0) b = atomicAdd(&s_next, 64);
             b = __builtin_amdgcn_readfirstlane(b);
             if (b >= n) break;
             const int i = b + lane;
-            if (i < n) solve(chunk ? s_list[i] : i);
+            if (i < n) solve(c0 + s_list[i]);
         }
     }
 }
@@ -850,37 +859,70 @@ size_t tmm_smem_bytes(int L, int n_slots, int wg)
     return (size_t)(sizeof(LayerRec) * rec_stride(L) + 8 * n_slots * LaneSlots5::kPer * ((wg + 63) / 64 * 64));
 }
 
+template <int MODE>
+static hipError_t launch_tmm_mode(const double* thk, const uint8_t* slot, int L, const double* lam_tab, int n_lambda,
+                                  const TmmRows& rows, const int32_t* lidx, const double* theta, int64_t nq, double* out,
+                                  int chunk, const TmmTab* tab, dim3 grid, size_t sm, hipStream_t s)
+{
+    const dim3 block(256);
+    auto launch = [&](auto val, auto sort, const auto& t) {
+        hipLaunchKernelGGL((k_tmm_rt<MODE, decltype(val)::value, decltype(sort)::value>), grid, block, sm, s, thk, slot, L, lam_tab,
+                           n_lambda, rows, lidx, theta, nq, out, chunk, t);
+    };
+    if constexpr (MODE != GWG_FP32) {                            // tmm_sorted
+        if (chunk) {
+            if (tab) launch(std::true_type{}, std::true_type{}, *tab);
+            else launch(std::false_type{}, std::true_type{}, TmmNoTab{});
+            return hipGetLastError();
+        }
+    }
+    if (tab) launch(std::true_type{}, std::false_type{}, *tab);
+    else launch(std::false_type{}, std::false_type{}, TmmNoTab{});
+    return hipGetLastError();
+}
+
+// Whether queries are solved by kind.  A launch whose waves all run at once
+// (two workgroups a CU) is as long as its longest wave, and sorting adds to it
+// (100000 queries of 200 layers: double precision 73 us in order and 77 by
+// kind, mixed 111 and 114).  Beyond that mixed precision gains always (200000
+// queries of 8, 40 and 200 layers: 33, 64 and 219 us in order, 26, 42 and 118
+// by kind); double precision on lossless stacks of more than a few layers (8,
+// 40 and 200: 24.0, 43.8 and 134 us in order, 25.1, 41.4 and 118 by kind).
+// Silver's complex path hides the hyperbolic case (300000 queries of 201
+// layers: 225 and 234 us), and single precision hardly pays for it (115 and
+// 129 us).
+static bool tmm_sorted(int precision, int L, uint32_t cplx, int64_t nq, int n_cu)
+{
+    if (nq <= 2 * 256 * (int64_t)n_cu) return false;
+    return precision == GWG_FP32_MIXED || (precision == GWG_FP64 && cplx == 0u && L >= 32);
+}
+
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
-                         const double* lam_tab, int n_lambda, int n_slots, uint32_t cplx_mask,
+                         const double* lam_tab, int n_lambda, const TmmRows& rows,
                          const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu,
                          const double* host_tab, const uint8_t* host_slot, hipStream_t s)
 {
-    // as many queries a workgroup as fill the GPU once (the longer its list,
-    // the fewer its mixed batches); launches of less than two queries a lane
-    // keep one, else the waves solve their two batches one after another
-    // where other waves could (160000 queries of 200 layers, single
-    // precision: 127 us with 512 a workgroup, 118 with 256)
     const int wg = 256;
-    const int64_t slots = (int64_t)n_cu * (precision == GWG_FP32 ? 3 : 2);
-    const int64_t want = nq < 2 * slots * wg ? wg : (nq + slots - 1) / slots;
-    int chunk = (int)std::min<int64_t>(kTmmChunk, (want + 63) / 64 * 64);
-    size_t sm = tmm_smem_bytes(L, n_slots, wg);
-    if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
-    sm += sizeof(uint16_t) * chunk;
-    dim3 grid(grid_for(nq, chunk ? chunk : wg, 8192)), block(wg);
-    auto k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64, false> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED, false>
-                                                                                           : k_tmm_rt<GWG_FP32, false>;
+    size_t sm = tmm_smem_bytes(L, rows.n_slots, wg);
+    int chunk = 0;
+    if (tmm_sorted(precision, L, rows.cplx, nq, n_cu)) {
+        // as many queries a workgroup as fill the GPU once (the longer its
+        // list, the fewer its mixed batches), if their list fits in LDS
+        const int64_t want = (nq + 2 * n_cu - 1) / (2 * n_cu);
+        chunk = (int)std::min<int64_t>(kTmmChunk, (want + 63) / 64 * 64);
+        if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
+        sm += sizeof(uint16_t) * chunk;
+    }
+    const dim3 grid(grid_for(nq, chunk ? chunk : wg, 8192));
     TmmTab tab;
     if (host_tab) {
-        k = precision == GWG_FP64 ? k_tmm_rt<GWG_FP64, true> : precision == GWG_FP32_MIXED ? k_tmm_rt<GWG_FP32_MIXED, true>
-                                                                                         : k_tmm_rt<GWG_FP32, true>;
-        const size_t nb = sizeof(double) * LT_STRIDE * (size_t)n_lambda;
+        const size_t nb = sizeof(double) * rows.stride() * (size_t)n_lambda;
         std::memcpy(tab.b, host_tab, nb);
         std::memcpy(tab.b + nb, host_slot, (size_t)L);
     }
-    hipLaunchKernelGGL(k, grid, block, sm, s, thk, slot, L, lam_tab, n_lambda, n_slots, cplx_mask, lidx, theta, nq, out, chunk,
-                       tab);
-    return hipGetLastError();
+    const auto launch = precision == GWG_FP64 ? launch_tmm_mode<GWG_FP64>
+                        : precision == GWG_FP32_MIXED ? launch_tmm_mode<GWG_FP32_MIXED> : launch_tmm_mode<GWG_FP32>;
+    return launch(thk, slot, L, lam_tab, n_lambda, rows, lidx, theta, nq, out, chunk, host_tab ? &tab : nullptr, grid, sm, s);
 }
 
 hipError_t launch_loss(const double* I, int D, int nl, int F, int B, int kind, double w_f, double w_e,

@@ -74,13 +74,26 @@ int64_t grad_reduce_tmp_doubles(int ML, int D);
 hipError_t launch_item_order(const int32_t* cnt, int waves, int64_t n_items, int64_t max_count, int32_t* order,
                              hipStream_t s);
 hipError_t launch_irradiance(const uint64_t* q, int64_t n, double scale, double* irr, hipStream_t s);
-// Bytes of wavelength rows and slots that a thin-film launch carries; with
-// more (host_tab null) it reads them from device memory.
+// Wavelength rows of the thin-film queries, doubles: the free-space wavenumber,
+// the incident index, the exit index (re, im), the slots' real indices, the
+// imaginary ones of absorbing slots (bits of cplx), n_crit near-critical kappa
+// intervals (lo, hi).
+enum { TR_K0 = 0, TR_NG = 1, TR_NA = 2, TR_SLOT = 4 };
+struct TmmRows {
+    int32_t n_slots, n_crit;
+    uint32_t cplx;
+    __host__ __device__ int imag(int s) const { return TR_SLOT + n_slots + __builtin_popcount(cplx & ((1u << s) - 1u)); }
+    __host__ __device__ int crit(int k) const { return TR_SLOT + n_slots + __builtin_popcount(cplx) + 2 * k; }
+    __host__ __device__ int stride() const { return crit(n_crit); }
+};
+// Bytes of rows and slots that a thin-film launch carries (31 wavelengths of a
+// 400-layer stack of four materials); with more (host_tab null) it reads them
+// from device memory.
 constexpr size_t kTmmTabBytes = 3584;
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
-                         const double* lam_tab, int n_lambda, int n_slots, uint32_t cplx_mask,
-                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu, const double* host_tab, const uint8_t* host_slot,
-                         hipStream_t s);
+                         const double* lam_tab, int n_lambda, const TmmRows& rows,
+                         const int32_t* lidx, const double* theta, int64_t nq, double* out, int n_cu, const double* host_tab,
+                         const uint8_t* host_slot, hipStream_t s);
 hipError_t launch_loss(const double* I, int D, int nl, int F, int B, int kind, double w_f, double w_e,
                        double* work, double* loss, double* G, hipStream_t s);
 // Doubles of work a loss of shape (D, nl, F, B) uses (launch_loss's work).
