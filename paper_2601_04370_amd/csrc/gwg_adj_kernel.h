@@ -524,7 +524,7 @@ __global__ void __launch_bounds__(64, 2) k_adj_sorted(SceneDev sc, const double*
                 const double kappa = en.kappa;
                 for (int s = 0; s < sc.n_slots; ++s) {
                     double P[NPF];
-                    slot_params(pl->slotN[2 * s], pl->slotN[2 * s + 1], kappa, k0, P);
+                    slot_params(pl->slotN[2 * s], pl->slotN[2 * s + 1], !LOSSLESS && ((sc.slot_complex >> s) & 1u), kappa, k0, P);
                     sl.put(s, P);
                 }
                 const double z0 = ng * ng - kappa * kappa;

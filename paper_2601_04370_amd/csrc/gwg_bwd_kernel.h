@@ -67,7 +67,7 @@ __device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const
     bool hyp = false;                       // an evanescent lossless slot at this kappa
     for (int s = 0; s < sc.n_slots; ++s) {
         double P[NPF];
-        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], kappa, pl.k0, P);
+        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], KIND != ADJ_LOSSLESS && ((sc.slot_complex >> s) & 1u), kappa, pl.k0, P);
         sl.put(s, P);
         hyp |= !((sc.slot_complex >> s) & 1u) && P[0] < 0.0;
     }

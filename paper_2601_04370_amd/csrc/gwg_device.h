@@ -383,13 +383,15 @@ __device__ inline void coshsinh(float x, float* ch, float* sh)
 //   lossless:  P0 kq (signed: >= 0 circular with d = kq t; < 0 hyperbolic with
 //              d = -kq t), P1 xs, P2 ys, P3 xp, P4 yp  (X = S x, Y = S y for s / p)
 //   absorbing: P0, P1 = q (re, im); P2, P3 = N^2 (re, im); P4 unused.
+// A slot is absorbing if its material is at any wavelength of the table (the
+// callers' masks); at a wavelength without absorption it keeps the complex form.
 // The table of a lane stores element (s, p) at sp[(s * NPF + p) * ls].
 constexpr int NPF = 5;
 constexpr double kTinyZ = 1e-24;   // |z| floor: keeps q != 0 exactly at the critical angle
 
-__device__ inline void slot_params(double nre, double nim, double kappa, double k0, double* P)
+__device__ inline void slot_params(double nre, double nim, bool absorbing, double kappa, double k0, double* P)
 {
-    if (nim == 0.0) {
+    if (!absorbing) {
         double n2 = nre * nre;
         double z = n2 - kappa * kappa;
         if (fabs(z) < kTinyZ) z = kTinyZ;
@@ -406,6 +408,7 @@ __device__ inline void slot_params(double nre, double nim, double kappa, double 
         cd N = mk(nre, nim);
         cd N2 = cmul(N, N);
         cd z = csub(N2, mk(kappa * kappa, 0.0));
+        if (z.im == 0.0 && fabs(z.re) < kTinyZ) z.re = kTinyZ;
         cd q = csqrt_up(z);
         P[0] = q.re; P[1] = q.im; P[2] = N2.re; P[3] = N2.im; P[4] = 0.0;
     }

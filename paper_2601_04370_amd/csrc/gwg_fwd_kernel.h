@@ -40,7 +40,7 @@ __device__ inline Coef4 hit_solve(int n_slots, uint32_t cplx, const PointLds& pl
     bool hyp = false;                       // an evanescent lossless slot at this kappa
     for (int s = 0; s < n_slots; ++s) {
         double P[NPF];
-        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], kappa, pl.k0, P);
+        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], (cplx >> s) & 1u, kappa, pl.k0, P);
         sl.put(s, P);
         hyp |= !((cplx >> s) & 1u) && P[0] < 0.0;
     }

@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(256, MODE == GWG_FP32 ? 3 : 2) k_tmm_rt(const 
         for (int s = 0; s < n_slots; ++s) {
             double P[NPF];
             const bool ab = (rows.cplx >> s) & 1u;
-            slot_params(lt[TR_SLOT + s], ab ? lt[rows.imag(s)] : 0.0, kappa, k0, P);
+            slot_params(lt[TR_SLOT + s], ab ? lt[rows.imag(s)] : 0.0, ab, kappa, k0, P);
             sl.put(s, P);
         }
         const double z0 = n0 * n0 - kappa * kappa;
