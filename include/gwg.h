@@ -356,10 +356,9 @@ int gwg_loss_noalloc(gwg_ctx* ctx, const double* d_irr, int32_t D, int32_t n_l, 
  * table_nodes (0 = 8192, else 4..2^20) is the number of incidence angles of
  * the angle table (GWG_FWD_TABLE).  ck_entries_per_ray (0 = 4, -1 = none,
  * else 1..64): with GWG_FWD_GRAD at FP64 on lossless stacks, the forward
- * solve keeps what the adjoint needs of its sweep (of a transmitted hit the
- * transfer matrices of its segments, 8 doubles every 48 layers, 24 if it meets
- * an evanescent layer; of a reflected hit 8 doubles) for up to this many
- * entries per ray of each entry region, within a memory budget (the smaller
+ * solve keeps what the adjoint needs of its sweep (transfer matrices or
+ * states, 8 doubles every 48 layers of a hit, 24 if it meets an evanescent layer)
+ * for up to this many entries per ray of each entry region, within a memory budget (the smaller
  * of 128 GiB and half the free memory; beyond it, not of evanescent hits, then
  * not of the later items), so the backward skips that sweep for them; the gradient is the
  * same bit for bit. */

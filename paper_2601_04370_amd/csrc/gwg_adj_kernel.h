@@ -11,8 +11,9 @@
 //
 // 1323 points x 8192 rays, 6 mirrors x 200 layers, 3.3e7 entries: entries in
 // item order with w and u walked 22.4 ms; Q walked (gwg_adjoint.h) 20.3 ms,
-// LDS-bound; sorted 15.6 ms and 0.9 ms for the sort.  Bound now by vector
-// issue (83 %; 47 instructions per layer, 44 of them double precision, and 10
+// LDS-bound; sorted 16.4 ms (15.6 with every hit's Q walked) and 0.9 ms for the
+// sort.  Bound now by vector issue (83 %; 47 instructions per layer, 44 of them
+// double precision, 54 of a reflected hit, and 10
 // for segment ends, sums and partly filled batches) at the clock that the
 // power limit leaves it (2.0 GHz).
 //
@@ -164,13 +165,53 @@ __device__ inline double sum8(double x)
     return x;
 }
 
-// Q at one side of a layer, carried through n layers: up from the exit side of
-// incidence-order layer j0, or (not up) down from its incident side (the
+// What a walk carries through the layers.  Both give a layer's gradient from
+// b = Q12 and c = Q21 at one of its sides and pass the layer: X = S x, Y = S y.
+__device__ inline double layer_gradient(double gys, double ys, double xp, double yp, double bs, double cs, double bp, double cp)
+{
+    return fma(gys, fma(-yp, bp, fma(xp, cp, -(ys * bs))), cs);
+}
+// Three reals a polarization of Q (A = Q11 - Q22).
+struct CarryQ {
+    double As, bs, cs, Ap, bp, cp;
+    __device__ double gradient(double gys, double ys, double xp, double yp) const
+    {
+        return layer_gradient(gys, ys, xp, yp, bs, cs, bp, cp);
+    }
+    __device__ void pass(double C, double Xs, double Ys, double Xp, double Yp)
+    {
+        const double ms = fma(C, As, fma(Xs, cs, Ys * bs)), mp = fma(C, Ap, fma(Xp, cp, Yp * bp));
+        const double C2 = C + C;
+        bs = fma(-Xs, ms, bs); cs = fma(-Ys, ms, cs); As = fma(C2, ms, -As);
+        bp = fma(-Xp, mp, bp); cp = fma(-Yp, mp, cp); Ap = fma(C2, mp, -Ap);
+    }
+};
+// A reflected hit's state times the root of twice its covector's factor c:
+// Q12 = Im(c B^2) and Q21 = Im(c C^2) are products of its parts.  (Its own Q
+// would do with fewer operations, but is of second order in the state: where
+// the state shrinks on its way up, at a resonance of the stack, Q keeps the
+// rounding of the square of what it was: cavities of 20 pairs a side, 1 pm off
+// resonance, 4e-7 of the gradient where the state keeps 1e-10; 200 layers of
+// random thickness, the worst of 2000: 2e-9 and 4e-11.)
+struct CarryW {
+    V2d s, p;
+    __device__ double gradient(double gys, double ys, double xp, double yp) const
+    {
+        return layer_gradient(gys, ys, xp, yp, s.br * s.bi, s.cr * s.ci, p.br * p.bi, p.cr * p.ci);
+    }
+    __device__ void pass(double C, double Xs, double Ys, double Xp, double Yp)
+    {
+        step_real_d(s, C, Xs, Ys);
+        step_real_d(p, C, Xp, Yp);
+    }
+};
+
+// A carrier at one side of a layer, taken through n layers: up from the exit
+// side of incidence-order layer j0, or (not up) down from its incident side (the
 // inverse layers: S -> -S).  The layers' gradients are added to gw.
-template <bool HC, class SL>
-__device__ __attribute__((always_inline)) inline void class_walk(const LayerRec* rec, int L, bool front, const SL& sl, double As,
-                                                                 double bs, double cs, double Ap, double bp, double cp, int j0,
-                                                                 int n, bool up, double* stage, double* gw)
+template <bool HC, class SL, class Carry>
+__device__ __attribute__((always_inline)) inline void class_walk(const LayerRec* rec, int L, bool front, const SL& sl, Carry v,
+                                                                 int j0, int n, bool up, double* stage, double* gw)
 {
     using LT = LayerTrig<double, HC>;
     const int lane = wave_lane();
@@ -205,19 +246,16 @@ __device__ __attribute__((always_inline)) inline void class_walk(const LayerRec*
             const double S = flip_sign(S0, sflip);
             const double sXs = S * xs, sYs = S * ys, sXp = S * xp, sYp = S * yp;
             const double gys = (HC && kq < 0.0) ? -ys : ys;       // sg y_s (an evanescent layer: sg = -1)
-            *o = fma(gys, fma(-yp, bp, fma(xp, cp, -(ys * bs))), cs);
-            const double ms = fma(C, As, fma(sXs, cs, sYs * bs)), mp = fma(C, Ap, fma(sXp, cp, sYp * bp));
-            const double C2 = C + C;
-            bs = fma(-sXs, ms, bs); cs = fma(-sYs, ms, cs); As = fma(C2, ms, -As);
-            bp = fma(-sXp, mp, bp); cp = fma(-sYp, mp, cp); Ap = fma(C2, mp, -Ap);
+            *o = v.gradient(gys, ys, xp, yp);
+            v.pass(C, sXs, sYs, sXp, sYp);
             ta = ta1; kq = kq1; xs = xs1; ys = ys1; xp = xp1; yp = yp1;
             kq1 = kq2; xs1 = xs2; ys1 = ys2; xp1 = xp2; yp1 = yp2; t1 = r2.t;
             r2 = r3;
         }
         wave_lds_sync();
         // lane: row lane / 8 (rows past the last: stale, not used)
-        const double2* v = (const double2*)(stage + (lane >> 3) * kStageLanes) + (lane & 7);
-        const double2 v0 = v[0], v1 = v[8], v2 = v[16], v3 = v[24];
+        const double2* r = (const double2*)(stage + (lane >> 3) * kStageLanes) + (lane & 7);
+        const double2 v0 = r[0], v1 = r[8], v2 = r[16], v3 = r[24];
         const double s = sum8(((v0.x + v0.y) + (v1.x + v1.y)) + ((v2.x + v2.y) + (v3.x + v3.y)));
         if ((lane & 7) == 0 && (lane >> 3) < rows) gw[i0 + dir * (k0_ + (lane >> 3))] += s;
         wave_lds_sync();
@@ -229,12 +267,11 @@ __device__ __attribute__((always_inline)) inline void class_walk(const LayerRec*
 // transmitted, all in segments of K layers.  Lanes without an entry have zero
 // cotangents.  The gradient of a layer is summed over the lanes, kStageRows
 // layers at a time.
-// A reflected hit's Q goes up the whole stack from the exit, growing as its
-// rounding does; blk: its state at the incident side.  A transmitted hit's Q
-// is formed at each segment end g from w_g and u_g and goes half a segment up
-// and half a segment down; blk: its segment matrices (64-byte blocks, block g
-// at blk + g bstride), wst: room for its states w_g (block g at wst + g
-// wstride).
+// A reflected hit's scaled state goes up each segment from its exit side; blk:
+// its states above the segments (64-byte blocks, block g at blk + g bstride).
+// A transmitted hit's Q is formed at each segment end g from w_g and u_g and
+// goes half a segment up and half a segment down; blk: its segment matrices,
+// wst: room for its states w_g (block g at wst + g wstride).
 template <bool HC, bool REFL, class SL>
 __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerRec* rec, int L, bool front, const SL& sl,
                                                                     double k0, double eta0s, double eta0p, cd Gs, cd Gp,
@@ -243,7 +280,7 @@ __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerR
 {
     const double k2 = 2.0 * k0;
     auto walk = [&](double As, double bs, double cs, double Ap, double bp, double cp, int j0, int n, bool up) {
-        class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, j0, n, up, stage, gw);
+        class_walk<HC>(rec, L, front, sl, CarryQ{ As, bs, cs, Ap, bp, cp }, j0, n, up, stage, gw);
     };
     auto read = [](const double* q, V2d& a, V2d& b) {
         const double2* p = (const double2*)q;
@@ -252,18 +289,20 @@ __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerR
         b = V2d{ x2.x, x2.y, x3.x, x3.y };
     };
     V2d ws = { 1.0, 0.0, eta0s, 0.0 }, wp = { 1.0, 0.0, eta0p, 0.0 };
+    const int G = seg_of(L - 1, K) + 1;
     if constexpr (REFL) {
         V2d ts, tp;
         read(blk, ts, tp);
-        const CovRow us = cov_top(ts, eta0s, true, false, cscale(Gs, k2));
-        const CovRow up = cov_top(tp, eta0p, true, true, cscale(Gp, k2));
-        double As, bs, cs, Ap, bp, cp;
-        cov_refl(us, ws, As, bs, cs);
-        cov_refl(up, wp, Ap, bp, cp);
-        walk(As, bs, cs, Ap, bp, cp, L - 1, L, true);
+        const cd fs = csqrt_any(cscale(cov_top(ts, eta0s, true, false, cscale(Gs, k2)).u1, 2.0));
+        const cd fp = csqrt_any(cscale(cov_top(tp, eta0p, true, true, cscale(Gp, k2)).u1, 2.0));
+        for (int g = G - 1; g >= 0; --g) {
+            const CarryW v = { state_scale(fs, ws), state_scale(fp, wp) };
+            const int j = min((g + 1) * K, L);
+            if (g > 0) read(blk + (int64_t)g * bstride, ws, wp);         // in flight
+            class_walk<HC>(rec, L, front, sl, v, j - 1, j - g * K, true, stage, gw);
+        }
         return;
     }
-    const int G = seg_of(L - 1, K) + 1;
     auto get_seg = [&](int g) {
         const double2* p = (const double2*)(blk + (int64_t)g * bstride);
         const double2 a = p[0], b = p[1], c = p[2], d = p[3];
@@ -312,8 +351,8 @@ __device__ __attribute__((always_inline)) inline void adjoint_class(const LayerR
 // into pieces: absorbing layers, and runs of up to kSegL lossless ones (pc[0]:
 // their number; pc[1 + p]: piece p's first layer in stack order, bit 15 set if
 // it is an absorbing layer).  A run goes as in adjoint_class, half of it down
-// from its top and half up from its exit side (a reflected hit's all up); an
-// absorbing layer takes the state and the covector themselves.  (A reflected
+// from its top and half up from its exit side (a reflected hit's scaled state
+// all up); an absorbing layer takes the state and the covector themselves.  (A reflected
 // hit's covector is c (C, -B) there as well: absorbing layers are unimodular.)
 // own: room for the runs' segment matrices, as wst.
 // 363 points x 4096 rays, 201 layers, one of them silver: 14.3 ms with every
@@ -370,28 +409,30 @@ __device__ __attribute__((always_inline)) inline void adjoint_pieces(const Layer
     V2d ws = { vs.br, vs.bi, vs.cr, vs.ci }, wp = { vp.br, vp.bi, vp.cr, vp.ci };
     CovRow us = cov_top(ws, eta0s, refl, false, cscale(Gs, k2));
     CovRow up = cov_top(wp, eta0p, refl, true, cscale(Gp, k2));
+    const cd fs = csqrt_any(cscale(us.u1, 2.0)), fp = csqrt_any(cscale(up.u1, 2.0));     // of a reflected hit
     for (int i = 0; i < P; ++i) {
         piece(i);
         V2d ns = { 1.0, 0.0, eta0s, 0.0 }, np = { 1.0, 0.0, eta0p, 0.0 };       // the states below
         if (i + 1 < P) read(wst + (i + 1) * wstride, ns, np);
         if (!absorbing) {
-            const int lo = front ? a : L - b, hi = front ? b : L - a, mid = refl ? lo : (lo + hi) / 2;
-            double As, bs, cs, Ap, bp, cp;
+            const int lo = front ? a : L - b, hi = front ? b : L - a;
             if (refl) {
-                cov_refl(us, ns, As, bs, cs);
-                cov_refl(up, np, Ap, bp, cp);
+                class_walk<HC>(rec, L, front, sl, CarryW{ state_scale(fs, ns), state_scale(fp, np) }, hi - 1, hi - lo, true,
+                               stage, gw);
             } else {
+                const int mid = (lo + hi) / 2;
+                double As, bs, cs, Ap, bp, cp;
                 cov_q(us.u1, us.u2, ws, As, bs, cs);
                 cov_q(up.u1, up.u2, wp, Ap, bp, cp);
-                class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, lo, mid - lo, false, stage, gw);
+                class_walk<HC>(rec, L, front, sl, CarryQ{ As, bs, cs, Ap, bp, cp }, lo, mid - lo, false, stage, gw);
                 const double2* q = (const double2*)(own + i * wstride);
                 const double2 x0 = q[0], x1 = q[1], x2 = q[2], x3 = q[3];
                 cov_step(us, SegMat{ x0.x, x0.y, x1.x, x1.y });
                 cov_step(up, SegMat{ x2.x, x2.y, x3.x, x3.y });
                 cov_q(us.u1, us.u2, ns, As, bs, cs);
                 cov_q(up.u1, up.u2, np, Ap, bp, cp);
+                class_walk<HC>(rec, L, front, sl, CarryQ{ As, bs, cs, Ap, bp, cp }, hi - 1, hi - mid, true, stage, gw);
             }
-            class_walk<HC>(rec, L, front, sl, As, bs, cs, Ap, bp, cp, hi - 1, hi - mid, true, stage, gw);
         } else {
             CTv<double> C, Xs, Ys, Xp, Yp;
             double Pd[4];

@@ -270,6 +270,21 @@ __device__ inline void cov_q(cd u1, cd u2, const V2d& w, double& A, double& b, d
     b = -fma(w.br, u2.im, w.bi * u2.re);
     c = fma(w.cr, u1.im, w.ci * u1.re);
 }
+// Square root of z (either one), also where |z|^2 leaves the range of a double.
+__device__ inline cd csqrt_any(cd z)
+{
+    int e;
+    (void)frexp(fmax(fabs(z.re), fabs(z.im)), &e);
+    e &= ~1;
+    const cd r = csqrt_up(mk(ldexp(z.re, -e), ldexp(z.im, -e)));
+    return mk(ldexp(r.re, e / 2), ldexp(r.im, e / 2));
+}
+// f times a state.
+__device__ inline V2d state_scale(cd f, const V2d& w)
+{
+    return { fma(f.re, w.br, -(f.im * w.bi)), fma(f.re, w.bi, f.im * w.br), fma(f.re, w.cr, -(f.im * w.ci)),
+             fma(f.re, w.ci, f.im * w.cr) };
+}
 // Q of a reflected hit (covector factor c in u1) at state w.
 __device__ inline void cov_refl(const CovRow& r, const V2d& w, double& A, double& b, double& c)
 {

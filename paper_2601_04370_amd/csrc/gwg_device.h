@@ -805,7 +805,7 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
     // and (bi, -cr) that start at the unit vectors), and the segments' product
     // is applied to the exit vector.  ck, for the adjoint: segment matrix g
     // (incidence-order layers g kseg and below) goes to the 64-byte block g at
-    // ck + g ckb, whole; of a reflected hit (top) only the result, to block 0.
+    // ck + g ckb, whole; of a reflected hit (top) the state above the segment.
     [[maybe_unused]] double a[4], b[4];                 // chain vectors below the current segment
     if constexpr (SEG) {
         a[0] = vs.br; a[1] = vs.bi; a[2] = vs.cr; a[3] = vs.ci;
@@ -818,15 +818,15 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
             const uint32_t sb = sign_bit();
             const SegMat ms = { flip_sign(vs.br, sb), flip_sign(vs.bi, sb), flip_sign(vs.ci, sb), flip_sign(-vs.cr, sb) };
             const SegMat mp = { flip_sign(vp.br, sb), flip_sign(vp.bi, sb), flip_sign(vp.ci, sb), flip_sign(-vp.cr, sb) };
-            if (ck && !top) {
-                double2* c = (double2*)(ck + (int64_t)g * ckb);
-                c[0] = make_double2(ms.m11, ms.m12);
-                c[1] = make_double2(ms.m21, ms.m22);
-                c[2] = make_double2(mp.m11, mp.m12);
-                c[3] = make_double2(mp.m21, mp.m22);
-            }
             seg_apply(ms, a[0], a[1], a[2], a[3]);
             seg_apply(mp, b[0], b[1], b[2], b[3]);
+            if (ck) {
+                double2* c = (double2*)(ck + (int64_t)g * ckb);
+                c[0] = top ? make_double2(a[0], a[1]) : make_double2(ms.m11, ms.m12);
+                c[1] = top ? make_double2(a[2], a[3]) : make_double2(ms.m21, ms.m22);
+                c[2] = top ? make_double2(b[0], b[1]) : make_double2(mp.m11, mp.m12);
+                c[3] = top ? make_double2(b[2], b[3]) : make_double2(mp.m21, mp.m22);
+            }
             vs = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
             vp = V2<T>{ 1.0, 0.0, -1.0, 0.0 };
             nsum = 0.0;
@@ -893,13 +893,6 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
             segment(0);
             vs = V2<T>{ a[0], a[1], a[2], a[3] };
             vp = V2<T>{ b[0], b[1], b[2], b[3] };
-            if (ck && top) {
-                double2* c = (double2*)ck;
-                c[0] = make_double2(a[0], a[1]);
-                c[1] = make_double2(a[2], a[3]);
-                c[2] = make_double2(b[0], b[1]);
-                c[3] = make_double2(b[2], b[3]);
-            }
         } else {
             const uint32_t sb = sign_bit();
             vs.br = flip_sign(vs.br, sb); vs.bi = flip_sign(vs.bi, sb);
@@ -919,7 +912,7 @@ __device__ __attribute__((always_inline)) inline void lossless_sweep(Cur cur, in
 // calling wave has an evanescent lossless slot (the sweep then skips the
 // hyperbolic case; the results are the same).  ck (lossless FP64 stacks):
 // the entry's blocks for the adjoint (segment matrices of kseg layers, or
-// the state of a reflected hit), or null.
+// the states of a reflected hit), or null.
 // TAKEN: finish_coeffs's.  SEG: lossless_sweep's.  SPLIT: circ picks between
 // two copies of the loop for absorbing stacks, too.
 template <typename T, bool TAKEN = false, bool SEG = false, bool SPLIT = false, class SL, class Stk>

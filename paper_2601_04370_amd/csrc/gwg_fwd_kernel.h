@@ -280,7 +280,7 @@ struct SolveCtx {
 // and the others from its back (cap-1 down to cap-nc), so the batches of the
 // second kind take the circular-only sweep.  ck (non-null): the blocks
 // of the wave's region's entries; a hit whose slot c >= 0 stores its segment
-// matrices (reflected: its state) there.
+// matrices (reflected: its states) there.
 // Out of line: the layer loop needs some 50 scalar registers for its
 // polynomials, and inlined among the walks it had 20 of them reloaded from
 // vector lanes in every four layers (211 vector instructions where 188 are

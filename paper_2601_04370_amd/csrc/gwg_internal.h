@@ -42,7 +42,9 @@ constexpr int kSeg = 4;               // layers per recomputation segment (backw
 // below 1e6); hyperbolic layers grow it exponentially in their thickness.
 // Against 80-bit arithmetic, stacks of 64 and 200 such layers with random
 // thicknesses: 48 layers are 10 to 50 times as accurate as a walk of the
-// inverse layers from every 32nd state, 64 layers are not.  Longer segments
+// inverse layers from every 32nd state, 64 layers are not.  A reflected hit's
+// scaled state walks up whole segments from the state at their exit side: as
+// accurate as the state itself, whatever the segment.  Longer segments
 // also take less memory and time: 1323 points x 8192 rays, forward and adjoint
 // 42.9 ms with 32, 39.0 ms with 64 layers (walked one way).
 constexpr int kSegL = 24;
@@ -113,8 +115,8 @@ struct AdjStore {
     // and read whole), one after another, as the sorted adjoint gathers
     // entries and a line holds two blocks: field f of block g at
     // ck[(c * ck_nb + g) * 8 + f].  A transmitted hit: S_g of the s
-    // polarization (m11, m12, m21, m22), then of p; a reflected one: only the
-    // state at its incident side, block 0 (B_s, C_s, B_p, C_p).
+    // polarization (m11, m12, m21, m22), then of p; a reflected one: the state
+    // above the segment (B_s, C_s, B_p, C_p).
     double* ck;
     int64_t ck_cap;
     int64_t ck_regions;
