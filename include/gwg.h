@@ -246,8 +246,10 @@ typedef struct {
  * and FoV point; within it the collimated rays share a few keys).  The
  * forward solves each distinct (kappa, mirror, side) key once and reuses its
  * coefficients, which are those of the per-hit solve bit for bit, so the bins
- * are identical (fov_mode 0 only; with fov_mode 1, or where the key tables do
- * not fit in LDS, the forward solves per hit).  With GWG_FWD_GRAD the
+ * are identical (fov_mode 0 only; with fov_mode 1, where the key tables do not
+ * fit in LDS, or where the points' direction tables, 12 KB each, would take more
+ * than a quarter of the free memory or 32 GiB in all, the forward solves per
+ * hit).  With GWG_FWD_GRAD the
  * backward solves one thin-film adjoint per distinct (kappa, mirror, side,
  * branch) key, with the key's summed cotangents, instead of one per mirror
  * hit (exact by linearity, up to summation order; the sums run in a fixed
@@ -351,8 +353,8 @@ int gwg_loss_noalloc(gwg_ctx* ctx, const double* d_irr, int32_t D, int32_t n_l, 
  * adj_entries_per_ray (0..64, 0 = 8) sizes the adjoint entry regions of
  * GWG_FWD_GRAD: a region holding more entries than this times its rays is
  * regenerated by the backward instead.  memo_keys (0..128, 0 = 128) is the
- * capacity of each wave's key table in the memoized forward (GWG_FWD_MEMO):
- * a wave meeting more keys in one work item solves the rest of it per hit.
+ * capacity of a work item's key table in the memoized forward (GWG_FWD_MEMO):
+ * an item meeting more keys solves the rest of its hits one by one.
  * table_nodes (0 = 8192, else 4..2^20) is the number of incidence angles of
  * the angle table (GWG_FWD_TABLE).  ck_entries_per_ray (0 = 4, -1 = none,
  * else 1..64): with GWG_FWD_GRAD at FP64 on lossless stacks, the forward
