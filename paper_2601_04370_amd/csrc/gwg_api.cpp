@@ -996,14 +996,15 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         bool fits;
         if (cap) {
             // nothing may be allocated: use the entries if the buffers already hold them
-            fits = c->adj_ent.p && c->adj_ent.bytes >= ent_b && c->adj_cnt.bytes >= cnt_b && c->adj_ovf.bytes >= ovf_b &&
-                   c->adj_sort.bytes >= sort_b;
+            fits = c->adj_ent.p && c->adj_ent.bytes >= ent_b && c->adj_cnt.bytes >= cnt_b && c->adj_ovf.bytes >= ovf_b;
         } else {
             size_t free_b = 0, total_b = 0;
             (void)hipMemGetInfo(&free_b, &total_b);
             const double bytes = (double)ent_b + (double)cnt_b + (double)ovf_b;     // (the order: a twelfth more)
             fits = bytes <= std::min<double>(kAdjBudgetBytes, 0.5 * (double)free_b + (double)c->adj_ent.bytes);
         }
+        // (without room for their order the backward traces again, as without room for the entries)
+        if (fits && sort_b) fits = room_for(c, c->adj_sort, sort_b, cap);
         if (fits) {
             rc = ensure_buf(c, c->adj_ent, ent_b, cap, "alloc adjoint entries");
             if (rc) return rc;
@@ -1011,10 +1012,6 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             if (rc) return rc;
             rc = ensure_buf(c, c->adj_ovf, ovf_b, cap, "alloc overflow flags");
             if (rc) return rc;
-            if (sort_b) {
-                rc = ensure_buf(c, c->adj_sort, sort_b, cap, "alloc entry order");
-                if (rc) return rc;
-            }
             HIP_CHECK(c, launch_fill_u32((uint32_t*)c->adj_ovf.p, sc.n_items + 1, 0u, s), "zero overflow flags");
             c->adj = AdjStore{ (double*)c->adj_ent.p, (int32_t*)c->adj_cnt.p, (int32_t*)c->adj_ovf.p, cap_w, waves,
                                nullptr, 0, 0, 0, 0, nullptr, nullptr, nullptr, (int32_t*)c->adj_ovf.p + sc.n_items, nullptr };
@@ -1164,7 +1161,15 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     // With entries from the forward, the backward keeps the forward's work
     // items: the entry kernel covers items whose regions fit, the
     // regenerating kernel the rest.  Otherwise every item is regenerated.
-    const bool entries = c->adj_valid && sample_stride == 1;
+    bool entries = c->adj_valid && sample_stride == 1;
+    const int ML = sc.M * sc.Lmax;
+    bool sorted = entries && !c->memo && !sc.table && (sc.slot_complex == 0u || sc.pieces);
+    // the sorted adjoint's rows: one per group of items, behind the items' own
+    // (regenerated ones); no room for them: every item is regenerated
+    const int64_t sorted_d = sorted ? (sc.n_items + sorted_rows(sc) * sc.D) * (int64_t)ML : 0;
+    if (sorted && !(room_for(c, c->sort_tab, sizeof(int32_t) * (size_t)sorted_ints(sc), cap) &&
+                    room_for(c, c->partial, sizeof(double) * (size_t)sorted_d, cap)))
+        entries = sorted = false;
     if (!entries) set_tiles(sc, c->tune.bwd_rays_per_block, wg, c->n_cu, true, true);
     if (bwd_smem_bytes(sc, wg) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     // persistent grids: as many workgroups as fit on the device at once
@@ -1172,9 +1177,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     const int64_t n_cu = std::max(c->n_cu, 1);
     const int64_t grid = std::min<int64_t>(
         sc.n_items, n_cu * occupancy(c, sc.table ? KIND_BWD_REGEN_TAB : KIND_BWD_REGEN, sc.precision, wg, smem));
-    const bool per_hit = entries && !c->memo && !sc.table;
-    const bool sorted = per_hit && (sc.slot_complex == 0u || sc.pieces);
-    const int64_t grid_e = per_hit && !sorted
+    const int64_t grid_e = entries && !c->memo && !sc.table && !sorted
         ? std::min<int64_t>(sc.n_items, n_cu * occupancy(c, KIND_ADJ_ENTRIES, sc.precision, wg, smem)) : 0;
     const int64_t grid_s = sorted
         ? std::min<int64_t>(sorted_rows(sc) * sc.D * sc.M, n_cu * occupancy(c, sc.slot_complex == 0u ? KIND_ADJ_SORTED : KIND_ADJ_SORTED_ABS,
@@ -1182,7 +1185,6 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         : 0;
     const int kind_m = sc.slot_complex == 0u ? KIND_ADJ_MEMO_LOSSLESS : KIND_ADJ_MEMO;
     const int64_t grid_m = std::min<int64_t>(sc.n_items, n_cu * occupancy(c, kind_m, sc.precision, 64, memo_smem_bytes(sc)));
-    const int ML = sc.M * sc.Lmax;
     int64_t scratch_d = std::max(bwd_scratch_doubles(sc, grid, wg), adj_scratch_doubles(sc, grid_e, wg));
     if (sorted) scratch_d = std::max(scratch_d, sorted_scratch_doubles(sc, grid_s));
     if (entries && c->memo) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_m, 64));
@@ -1197,8 +1199,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     if (sc.table) scratch_d = std::max(scratch_d, adj_scratch_doubles(sc, grid_ta, 128));
     rc = ensure_buf(c, c->scratch, sizeof(double) * (size_t)scratch_d, cap, "alloc adjoint scratch");
     if (rc) return rc;
-    const int64_t partial_d = sc.table ? table_adj_rows(sc) * sc.Lmax
-                                       : (sc.n_items + (sorted ? sorted_rows(sc) * sc.D : 0)) * (int64_t)ML;
+    const int64_t partial_d = sc.table ? table_adj_rows(sc) * sc.Lmax : sorted ? sorted_d : sc.n_items * (int64_t)ML;
     rc = ensure_buf(c, c->partial, sizeof(double) * (size_t)partial_d, cap, "alloc partial gradients");
     if (rc) return rc;
     rc = ensure_buf(c, c->stats, sizeof(uint64_t) * ST_WORDS, cap, "alloc stats");
@@ -1235,7 +1236,6 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
         return GWG_OK;
     }
     if (c->timing && !cap) HIP_CHECK(c, hipEventRecord(c->timer[GWG_KERNEL_ADJOINT].begin(), s), "timing event");
-    // sorted adjoint: one row per group of items, behind the items' own
     double* rows = (double*)c->partial.p + (sorted ? sc.n_items * (int64_t)ML : 0);
     if (entries && c->memo) {
         AdjStore st = c->adj;
@@ -1248,8 +1248,6 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
                                      st, (double*)c->scratch.p, s),
                   "memoized adjoint kernel");
     } else if (sorted) {
-        rc = ensure_buf(c, c->sort_tab, sizeof(int32_t) * (size_t)sorted_ints(sc), cap, "alloc entry classes");
-        if (rc) return rc;
         HIP_CHECK(c, launch_adj_sorted(sc, (int)grid_s, d_dL_dI, (unsigned long long*)c->stats.p, rows, c->adj,
                                        (uint32_t*)c->adj_sort.p, (int32_t*)c->sort_tab.p, (double*)c->scratch.p, s),
                   "sorted adjoint kernels");

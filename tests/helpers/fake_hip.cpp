@@ -19,7 +19,7 @@ std::map<char*, size_t> g_mem;
 size_t g_used = 0, g_total = (size_t)288 << 30, g_refuse_lo = 1, g_refuse_hi = 0;
 char* g_next = (char*)0x100000000000;
 bool g_capture = false;
-std::string g_log;
+std::string g_log, g_sizes;
 double g_clock = 0.0;                      // ms of the launches so far
 std::map<void*, double> g_event;
 double g_cost64 = 1.0, g_cost128 = 1.0, g_cost256 = 1.0;
@@ -34,7 +34,8 @@ size_t fake_used() { return g_used; }
 void fake_capture(int on) { g_capture = on != 0; }
 void fake_costs(double c64, double c128, double c256) { g_cost64 = c64; g_cost128 = c128; g_cost256 = c256; }
 const char* fake_log() { return g_log.c_str(); }
-void fake_clear() { g_log.clear(); }
+const char* fake_sizes() { return g_sizes.c_str(); }       // of every allocation asked for
+void fake_clear() { g_log.clear(); g_sizes.clear(); }
 
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -49,6 +50,7 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int)
 hipError_t hipMalloc(void** p, size_t n)
 {
     *p = nullptr;
+    g_sizes += std::to_string(n) + "\n";
     if (g_used + n > g_total || (n >= g_refuse_lo && n <= g_refuse_hi)) return hipErrorOutOfMemory;
     g_mem[g_next] = n;
     g_used += n;

@@ -44,7 +44,7 @@ class Host:
         self.gwg, self.inputs = gwg, inputs
         self.lib = gwg.load_library()
         self.fake = C.CDLL(None)
-        self.fake.fake_log.restype = C.c_char_p
+        self.fake.fake_log.restype = self.fake.fake_sizes.restype = C.c_char_p
         self.fake.fake_used.restype = C.c_size_t
         self.fake.fake_memory.argtypes, self.fake.fake_refuse.argtypes = [C.c_size_t], [C.c_size_t] * 2
         self.fake.fake_costs.argtypes = [C.c_double] * 3
@@ -88,6 +88,11 @@ class Host:
         t = self.gwg.Tuning(**kw)
         assert self.lib.gwg_set_tuning(self.h, C.byref(t)) == 0
 
+    def kept(self):
+        v = C.c_int32(0)
+        assert self.lib.gwg_forward_kept_entries(self.h, C.byref(v)) == 0
+        return v.value
+
     def error(self):
         return self.lib.gwg_last_error(self.h).decode()
 
@@ -104,6 +109,10 @@ class Host:
             else:
                 rows.append([f[0], int(f[1]), int(f[2]), dict(k.split("=") for k in f[3:])])
         return rows
+
+    def sizes(self):
+        """Allocations asked for since the log was last cleared, bytes."""
+        return [int(x) for x in self.fake.fake_sizes().split()]
 
     def kernels(self, name, clear=True):
         return [x for x in self.log(clear) if name in x[0]]

@@ -1,0 +1,47 @@
+"""Buffers that the sorted adjoint adds to the stored entries: where one of them
+cannot be allocated the backward traces the paths again, as where the entries
+themselves do not fit; no call fails for it."""
+import pytest
+
+from tests.host_only import run
+
+STEP = """
+sc = h.scene(fov_n=3, rays_per_point=500, n_layers=40)
+def step(refuse=None):
+    if refuse: h.fake.fake_refuse(refuse, refuse)
+    rc = [h.forward(sc, grad=True)]
+    kept, fwd = h.kept(), h.sizes()
+    h.log()
+    rc.append(h.backward())
+    bwd = h.sizes()
+    return rc, kept, fwd, bwd, [x[0] for x in h.log()]
+"""
+
+
+def _sizes(which):
+    out = run(STEP + """
+rc, kept, fwd, bwd, _ = step()
+assert rc == [0, 0] and kept == 1
+out['fwd'], out['bwd'] = fwd, bwd
+""")
+    if which == "order":                                     # 4 bytes an entry of 48
+        return next(n for n in out["fwd"] if n * 12 in out["fwd"])
+    rows = [n for n in out["bwd"] if n % (8 * 6 * 40) == 0]
+    return max(rows) if which == "rows" else next(n for n in out["bwd"] if n % (4 * 129) == 0)
+
+
+@pytest.mark.parametrize("which", ["order", "rows", "classes"])
+def test_step_without_room_for(which):
+    n = _sizes(which)
+    out = run(STEP + f"""
+rc, kept, _, _, names = step({n})
+out['rc'], out['kept'], out['error'] = rc, kept, h.error()
+out['sorted'] = sum('k_adj_sorted' in x for x in names)
+out['regen'] = sum('k_trace_bwd' in x for x in names)
+h.fake.fake_refuse(1, 0)                                     # room again: entries and their sort
+rc, kept, _, _, names = step()
+out['again'] = [rc, kept, sum('k_adj_sorted' in x for x in names)]
+""")
+    assert out["rc"] == [0, 0], out["error"]
+    assert out["kept"] == (0 if which == "order" else 1) and out["sorted"] == 0 and out["regen"] == 1
+    assert out["again"] == [[0, 0], 1, 1]
