@@ -1079,14 +1079,24 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
     const int per_cu = occupancy(c, kind_f, precision, wg, smem_f,
                                  [&]() { return fwd_blocks_per_cu(sc, adj_sweep, wg, smem_f); });
     const int64_t grid = std::min<int64_t>(sc.n_items, (int64_t)std::max(c->n_cu, 1) * per_cu);
-    rc = ensure_buf(c, c->fwd_scratch, sizeof(double) * (size_t)fwd_scratch_doubles(sc, grid, wg), cap, "alloc hit queues");
-    if (rc) return rc;
     if (adj_sweep) {
         rc = ensure_buf(c, c->fwd_tape, sizeof(double) * (size_t)(grid * wg * (int64_t)sc.Kmax * kTapeStride), cap,
                         "alloc forward tape");
         if (rc) return rc;
     }
     rc = ensure_buf(c, c->stats, sizeof(uint64_t) * ST_WORDS, cap, "alloc stats");
+    if (rc) return rc;
+    const int waves_f = wg / 64;
+    rc = ensure_buf(c, c->item_work, sizeof(int32_t) * (size_t)(sc.n_items * waves_f), cap, "alloc item work");
+    if (rc) return rc;
+    rc = ensure_buf(c, c->fwd_order, sizeof(int32_t) * (size_t)sc.n_items, cap, "alloc forward order");
+    if (rc) return rc;
+    // the hit queues, last: with less memory than they want smaller pools do
+    // (bins, counts and entries do not depend on the pool; memoized gradients
+    // only in the order in which their keys are summed)
+    auto queues_b = [&]() { return sizeof(double) * (size_t)fwd_scratch_doubles(sc, grid, wg); };
+    while (!cap && sc.pool > 1 && !room_for(c, c->fwd_scratch, queues_b(), cap)) sc.pool = (sc.pool + 1) / 2;
+    rc = ensure_buf(c, c->fwd_scratch, queues_b(), cap, "alloc hit queues");
     if (rc) return rc;
     HIP_CHECK(c, launch_fill_u64(out->q_bins, nbins, 0, s), "zero bins");
     HIP_CHECK(c, launch_fill_u32(out->counts, nbins, 0, s), "zero counts");
@@ -1100,11 +1110,6 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         // items are taken in decreasing order of the mirror hits that the last
         // forward of the same decomposition recorded (its first call: item
         // order), so the workgroups finish together; results do not depend on it
-        const int waves_f = wg / 64;
-        rc = ensure_buf(c, c->item_work, sizeof(int32_t) * (size_t)(sc.n_items * waves_f), cap, "alloc item work");
-        if (rc) return rc;
-        rc = ensure_buf(c, c->fwd_order, sizeof(int32_t) * (size_t)sc.n_items, cap, "alloc forward order");
-        if (rc) return rc;
         sc.fwd_order = nullptr;
         if (c->work_items == sc.n_items && c->work_waves == waves_f) {
             HIP_CHECK(c, launch_item_order((const int32_t*)c->item_work.p, waves_f, sc.n_items,

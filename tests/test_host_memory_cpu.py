@@ -45,3 +45,28 @@ out['again'] = [rc, kept, sum('k_adj_sorted' in x for x in names)]
     assert out["rc"] == [0, 0], out["error"]
     assert out["kept"] == (0 if which == "order" else 1) and out["sorted"] == 0 and out["regen"] == 1
     assert out["again"] == [[0, 0], 1, 1]
+
+
+@pytest.mark.parametrize("mode", ["memo", "table", "hit"])
+def test_forward_with_little_memory_for_hit_queues(mode):
+    """Pools of several rounds take several times the memory of one: with less
+    the forward takes smaller pools."""
+    out = run(f"""
+kw = dict(fov_n=21, rays_per_point=8192, n_layers=8)
+flag = dict(memo={mode == "memo"}, table={mode == "table"})
+h.tuning(table_nodes=64)
+assert h.forward(h.scene(**kw), **flag) == 0, h.error()
+k = h.kernels('k_trace_fwd', clear=False)[-1]
+n = max(h.sizes())                                           # the queues
+out['pool'] = int(k[3]['pool'])
+h2 = type(h)()
+h2.fake.fake_clear()
+h2.tuning(table_nodes=64)
+h2.fake.fake_refuse(n // out['pool'] + n // 16, 1 << 62)     # room for one round, not for two
+out['rc'] = h2.forward(h2.scene(**kw), **flag)
+out['error'] = h2.error()
+out['small'] = [int(x[3]['pool']) for x in h2.kernels('k_trace_fwd')]
+""")
+    assert out["pool"] >= 4
+    assert out["rc"] == 0, out["error"]
+    assert out["small"] == [1]
