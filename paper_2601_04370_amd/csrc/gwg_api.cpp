@@ -618,14 +618,19 @@ int build_scene(gwg_ctx* c, const gwg_slab* sl, const gwg_prma* pr, const gwg_ma
 // Waves of 64 rays a launch has (points are traced separately).
 int64_t ray_waves(const SceneDev& s) { return (int64_t)s.D * s.n_lsel * s.F * ((s.N + 63) / 64); }
 
+// A launch of at most two waves of rays a CU: tiles of one wave in workgroups of
+// two, so that the rays spread over the CUs (with more, tiles of a whole
+// workgroup; memoized, too, where each item solves its keys).  Tiles of 64 in
+// workgroups of 128, of 128 in 128, and of 256 in 256: 81 points x 300 rays (405
+// waves), 200 layers, gradient 565, 606 and 681 us a step; 5000 rays of one point
+// (79 waves), 8 layers, forward 108, 116 and 120 us; 27 points x 2048 rays (864
+// waves), 200 layers 817, 784 and 674 us, memoized 474, 372 and 337 us.
+bool spread_rays(const SceneDev& s, int n_cu) { return !s.memo && ray_waves(s) <= 2 * (int64_t)std::max(n_cu, 1); }
+
 int pick_fwd_wg(gwg_ctx* c, const SceneDev& s, bool lds_bins)
 {
     if (c->tune.block_threads) return c->tune.block_threads;
-    // A launch of at most one wave per SIMD: workgroups of one wave spread
-    // over the CUs and wait for no other wave's barriers.  (27 points x 2048
-    // rays, 200 layers, gradient: 0.76 ms a step against 1.11 ms at 256
-    // threads; 100,000 rays of one point, 1563 waves: 0.16 against 0.14 ms.)
-    if (ray_waves(s) <= 4 * (int64_t)std::max(c->n_cu, 1)) return 64;
+    if (spread_rays(s, c->n_cu) && fwd_scene_bytes(s, 128, lds_bins) <= 65536) return 128;
     for (int wg : { 256, 128, 64 })
         if (fwd_scene_bytes(s, wg, lds_bins) <= 65536) return wg;
     return 64;
@@ -641,7 +646,8 @@ int pick_bwd_wg(gwg_ctx* c, const SceneDev& s)
 
 // grad: an adjoint follows, which takes the forward's items; per_hit: the
 // forward solves every hit (its passes are long enough for their fit to count).
-void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu, bool grad, bool per_hit)
+// forward: its tiles may be of one wave (spread_rays).
+void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu, bool grad, bool per_hit, bool forward)
 {
     const int64_t points = (int64_t)s.D * s.n_lsel * s.F;
     int64_t rpt = rays_per_tile;
@@ -677,6 +683,7 @@ void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu, bool grad, 
         rounds = pick;
         rpt = std::max<int64_t>(rpt, (int64_t)wg * rounds);
         rpt = ((rpt + wg - 1) / wg) * wg;
+        if (forward && wg <= 128 && spread_rays(s, n_cu)) rpt = 64;
     }
     if (rpt > s.N) rpt = s.N;
     s.rays_per_tile = rpt;
@@ -956,7 +963,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
         wg = pick_fwd_wg(c, sc, lds_bins);
     }
     set_tiles(sc, c->tune.rays_per_block, wg, c->n_cu, (flags & GWG_FWD_GRAD) != 0,
-              (flags & (GWG_FWD_MEMO | GWG_FWD_TABLE)) == 0);
+              (flags & (GWG_FWD_MEMO | GWG_FWD_TABLE)) == 0, true);
     if (fwd_scene_bytes(sc, wg, lds_bins) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     if (sc.n_items > 0x7fffffff) return fail(c, GWG_E_INVAL, "too many work items; raise rays_per_block");
     const int64_t nbins = (int64_t)sc.D * sc.n_lsel * sc.F * B;
@@ -1175,7 +1182,7 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     if (sorted && !(room_for(c, c->sort_tab, sizeof(int32_t) * (size_t)sorted_ints(sc), cap) &&
                     room_for(c, c->partial, sizeof(double) * (size_t)sorted_d, cap)))
         entries = sorted = false;
-    if (!entries) set_tiles(sc, c->tune.bwd_rays_per_block, wg, c->n_cu, true, true);
+    if (!entries) set_tiles(sc, c->tune.bwd_rays_per_block, wg, c->n_cu, true, true, false);
     if (bwd_smem_bytes(sc, wg) > 65536) return fail(c, GWG_E_INVAL, "scene too large for one workgroup's LDS");
     // persistent grids: as many workgroups as fit on the device at once
     const size_t smem = bwd_smem_bytes(sc, wg);
@@ -1460,17 +1467,21 @@ int gwg_autotune(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, const g
         if (r != GWG_OK || !with_bwd) return r;
         return gwg_trace_backward(c, (const double*)c->tune_g.p, (double*)c->tune_grad.p, 1, nullptr, stream);
     };
-    // forward candidates: block size x ray tile; bins must not depend on them
+    // forward candidates: block size x ray tile, the automatic choice among
+    // them (shaped as the forward shapes it); bins must not depend on them
     std::vector<gwg_tuning> cands;
-    for (int wg : { 256, 128 }) {
-        if (fwd_scene_bytes(sc0, wg, lds_bins) > 65536) continue;
+    for (int wg : { 256, 128, 64 }) {
         SceneDev t = sc0;
-        set_tiles(t, 0, wg, c->n_cu, with_bwd, (flags & GWG_FWD_MEMO) == 0);
+        t.memo = (flags & GWG_FWD_MEMO) && t.dirs ? kFwdMemoKeys : 0;
+        if (t.memo && fwd_scene_bytes(t, wg, lds_bins) > 65536) t.memo = 0;
+        if (fwd_scene_bytes(t, wg, lds_bins) > 65536 || (wg == 64 && !cands.empty())) continue;
+        set_tiles(t, 0, wg, c->n_cu, with_bwd, (flags & GWG_FWD_MEMO) == 0, true);
+        const int64_t unit = std::min<int64_t>(wg, t.rays_per_tile);
         std::vector<int64_t> seen;
         for (int shift : { 0, -1, 1, -2, 2 }) {
             int64_t rpt = shift >= 0 ? t.rays_per_tile << shift : t.rays_per_tile >> -shift;
-            rpt = std::max<int64_t>(rpt, (int64_t)wg);
-            rpt = std::min<int64_t>(((rpt + wg - 1) / wg) * wg, sc0.N);
+            rpt = std::max<int64_t>(rpt, unit);
+            rpt = std::min<int64_t>(((rpt + unit - 1) / unit) * unit, sc0.N);
             if (std::find(seen.begin(), seen.end(), rpt) != seen.end()) continue;
             seen.push_back(rpt);
             gwg_tuning cand = saved;
