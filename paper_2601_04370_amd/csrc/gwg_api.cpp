@@ -1188,7 +1188,8 @@ int gwg_trace_backward(gwg_ctx* c, const double* d_dL_dI, double* d_grad, int64_
     const size_t smem = bwd_smem_bytes(sc, wg);
     const int64_t n_cu = std::max(c->n_cu, 1);
     const int64_t grid = std::min<int64_t>(
-        sc.n_items, n_cu * occupancy(c, sc.table ? KIND_BWD_REGEN_TAB : KIND_BWD_REGEN, sc.precision, wg, smem));
+        sc.n_items, n_cu * occupancy(c, sc.table ? KIND_BWD_REGEN_TAB : sc.slot_complex == 0u ? KIND_BWD_REGEN_LOSSLESS : KIND_BWD_REGEN,
+                                   sc.precision, wg, smem));
     const int64_t grid_e = entries && !c->memo && !sc.table && !sorted
         ? std::min<int64_t>(sc.n_items, n_cu * occupancy(c, KIND_ADJ_ENTRIES, sc.precision, wg, smem)) : 0;
     const int64_t grid_s = sorted

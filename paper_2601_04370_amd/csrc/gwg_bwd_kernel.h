@@ -52,54 +52,82 @@ __device__ inline void q_put(const Queue& q, int pos, double kappa, cd Gs, cd Gp
 
 // Adjoint thin-film solve of one mirror hit (one per lane): kappa, the
 // scaled cotangents and meta = mirror | front << 8 | reflected << 9.
-// KIND: the scene has no absorbing slot (ADJ_LOSSLESS), has one (ADJ_ABSORBING),
-// or either (ADJ_ANY): the entry kernels are compiled for one of them, so that
-// each keeps within the 64 KB instruction cache.
+// KIND: whether the scene has absorbing slots; the kernels are compiled for
+// either, so that each keeps within the 64 KB instruction cache.
 // chk: the lane's scratch (blocks of 8 doubles, stride cstride).
-enum { ADJ_ANY = 0, ADJ_LOSSLESS = 1, ADJ_ABSORBING = 2 };
-template <int KIND = ADJ_ANY>
-__device__ inline void adjoint_hit(const SceneDev& sc, const PointLds& pl, const double* s_thk,
+enum { ADJ_LOSSLESS = 1, ADJ_ABSORBING = 2 };
+template <int KIND>
+__device__ inline void adjoint_hit(int n_slots, uint32_t slot_complex, int Lmax, const PointLds& pl, const double* s_thk,
                                    const uint8_t* s_slot, const LaneSlots3& sl, double* gw, double kappa, cd Gs,
                                    cd Gp, int meta, double* chk, int64_t cstride)
 {
     const int m = meta & 255;
     const bool front = (meta >> 8) & 1, refl = (meta >> 9) & 1;
     bool hyp = false;                       // an evanescent lossless slot at this kappa
-    for (int s = 0; s < sc.n_slots; ++s) {
+    for (int s = 0; s < n_slots; ++s) {
         double P[NPF];
-        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], KIND != ADJ_LOSSLESS && ((sc.slot_complex >> s) & 1u), kappa, pl.k0, P);
+        slot_params(pl.slotN[2 * s], pl.slotN[2 * s + 1], KIND != ADJ_LOSSLESS && ((slot_complex >> s) & 1u), kappa, pl.k0, P);
         sl.put(s, P);
-        hyp |= !((sc.slot_complex >> s) & 1u) && P[0] < 0.0;
+        hyp |= !((slot_complex >> s) & 1u) && P[0] < 0.0;
     }
     const double z0 = pl.ng * pl.ng - kappa * kappa;
     const double q0 = sqrt(z0 > kTinyZ ? z0 : kTinyZ);
-    if (KIND == ADJ_LOSSLESS || (KIND == ADJ_ANY && sc.slot_complex == 0u)) {
+    if (KIND == ADJ_LOSSLESS) {
         // waves whose lanes all see circular layers take the sweep without
         // the hyperbolic case
         const bool circ = __ballot(hyp) == 0ull;
-        const int nblk = sc.Lmax / kSegUp + 1;
+        const int nblk = Lmax / kSegUp + 1;
         if (circ)
-            tmm_adjoint_lossless<false>(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, pl.k0, q0,
-                                        pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, nblk);
+            tmm_adjoint_lossless<false>(s_thk + m * Lmax, s_slot + m * Lmax, pl.nlay[m], front, sl, pl.k0, q0,
+                                        pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * Lmax, chk, cstride, nblk);
         else
-            tmm_adjoint_lossless<true>(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, pl.k0, q0,
-                                       pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk, cstride, nblk);
+            tmm_adjoint_lossless<true>(s_thk + m * Lmax, s_slot + m * Lmax, pl.nlay[m], front, sl, pl.k0, q0,
+                                       pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * Lmax, chk, cstride, nblk);
     }
-    else if (KIND != ADJ_LOSSLESS)
-        tmm_adjoint(s_thk + m * sc.Lmax, s_slot + m * sc.Lmax, pl.nlay[m], front, sl, sc.slot_complex,
-                    pl.k0, kappa * kappa, q0, pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * sc.Lmax, chk,
+    else
+        tmm_adjoint(s_thk + m * Lmax, s_slot + m * Lmax, pl.nlay[m], front, sl, slot_complex,
+                    pl.k0, kappa * kappa, q0, pl.ng * pl.ng / q0, refl, Gs, Gp, gw + m * Lmax, chk,
                     cstride);
 }
 
-// Adjoint thin-film solve of ring-queue entry `pos`.
+// What the regenerating kernel's thin-film routines read: LDS (PointLds, the
+// stacks, this lane's slot table, the wave's accumulator) and the scene's sizes.
+struct BwdCtx {
+    LdsPtr pl, thk, slot, sp, gw;
+    int Lmax, n_slots;
+    uint32_t cplx;               // absorbing slots
+    __device__ const PointLds& point() const { return *(const PointLds*)pl; }
+    __device__ LaneSlots3 slots() const
+    {
+        const PointLds& p = point();
+        return { (double*)sp, p.nsq, p.pxy };
+    }
+};
+
+// Adjoint thin-film solve of ring-queue entry `pos` (one per lane).  It and
+// bwd_solve are out of line, as the forward's solves are: inlined among the
+// walks their layer loops reloaded scalar registers from vector lanes (363
+// points x 8192 rays, traced again: 200 layers 17.6 -> 17.4 ms, 40 layers 7.2 ->
+// 6.2 ms, 201 layers with one of silver, 75 points x 4096 rays 6.0 -> 4.8 ms).
 template <int KIND>
-__device__ inline void adjoint_entry(const SceneDev& sc, const PointLds& pl, const double* s_thk,
-                                     const uint8_t* s_slot, const LaneSlots3& sl, double* gw, const Queue& q,
-                                     int pos, double* chk, int64_t cstride)
+__device__ __attribute__((noinline)) void bwd_adjoint(BwdCtx cx, Queue q, int pos, double* chk, int64_t cstride)
 {
     const int p = pos % q.cap;
-    adjoint_hit<KIND>(sc, pl, s_thk, s_slot, sl, gw, q.base[p], mk(q.base[1 * q.cap + p], q.base[2 * q.cap + p]),
+    adjoint_hit<KIND>(__builtin_amdgcn_readfirstlane(cx.n_slots), (uint32_t)__builtin_amdgcn_readfirstlane((int)cx.cplx),
+                      __builtin_amdgcn_readfirstlane(cx.Lmax), cx.point(), (const double*)cx.thk, (const uint8_t*)cx.slot,
+                      cx.slots(), (double*)cx.gw, q.base[p], mk(q.base[1 * q.cap + p], q.base[2 * q.cap + p]),
                       mk(q.base[3 * q.cap + p], q.base[4 * q.cap + p]), (int)q.base[5 * q.cap + p], chk, cstride);
+}
+
+// Solve the wave's `total` queued hits; off: as solve_hits.
+template <int MODE>
+__device__ __attribute__((noinline)) HitCounts bwd_solve(BwdCtx cx, HitQueue hq, int total, int off)
+{
+    const int Lmax = __builtin_amdgcn_readfirstlane(cx.Lmax);
+    return solve_hits<MODE>(__builtin_amdgcn_readfirstlane(cx.n_slots), (uint32_t)__builtin_amdgcn_readfirstlane((int)cx.cplx),
+                            cx.point(), ArrStacks{ (const double*)cx.thk, (const uint8_t*)cx.slot, Lmax,
+                                                   LaneSlots3::kPer * kSlotLanes * 8 },
+                            cx.slots(), hq, __builtin_amdgcn_readfirstlane(total), off);
 }
 
 // Pushes the entries of one ray onto the ring queue with the dL/dI factor applied.
@@ -136,7 +164,9 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
     const int lane = wave_lane();
     const int ML = sc.M * sc.Lmax;
     double* gw = s_grad + (int64_t)wave * ML;
-    const LaneSlots3 sl = { slot_lane_base(s_sp, sc.n_slots, LaneSlots3::kPer, tid), pl->nsq, pl->pxy };
+    const BwdCtx cx = { lds_ptr(pl), lds_ptr(s_thk), lds_ptr(s_slot),
+                        lds_ptr(slot_lane_base(s_sp, sc.n_slots, LaneSlots3::kPer, tid)), lds_ptr(gw), sc.Lmax, sc.n_slots,
+                        sc.slot_complex };
     const int64_t nthreads = (int64_t)gridDim.x * WG;
     const int64_t gtid = (int64_t)blockIdx.x * WG + tid;
     const int64_t gwave = (int64_t)blockIdx.x * n_waves + wave;
@@ -207,8 +237,9 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
                 int htotal;
                 const int hoff = wave_excl_scan(nh, &htotal);
                 __threadfence_block();
-                solve_hits<MODE>(sc, *pl, ArrStacks{ s_thk, s_slot, sc.Lmax, LaneSlots3::kPer * kSlotLanes * 8 }, sl,
-                                 hq, htotal, hoff, &c_fp64, &c_lay);
+                const HitCounts n = bwd_solve<MODE>(cx, hq, htotal, hoff);
+                c_fp64 += n.fp64;
+                c_lay += n.lay;
                 __threadfence_block();
             }
             if (active) {
@@ -241,7 +272,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
             __threadfence_block();
             // phase 2: drain full batches
             while (qcount >= 64) {
-                adjoint_entry<KIND>(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
+                bwd_adjoint<KIND>(cx, q, qhead + lane, chk, nthreads);
                 const int m = ((int)q.base[5 * q.cap + (qhead + lane) % q.cap]) & 255;
                 c_ahits += 1;
                 c_alay += (unsigned long long)pl->nlay[m];
@@ -251,7 +282,7 @@ __global__ void __launch_bounds__(128, 2) k_trace_bwd(SceneDev sc, const double*
         }
         if (qcount > 0) {
             if (lane < qcount) {
-                adjoint_entry<KIND>(sc, *pl, s_thk, s_slot, sl, gw, q, qhead + lane, chk, nthreads);
+                bwd_adjoint<KIND>(cx, q, qhead + lane, chk, nthreads);
                 const int m = ((int)q.base[5 * q.cap + (qhead + lane) % q.cap]) & 255;
                 c_ahits += 1;
                 c_alay += (unsigned long long)pl->nlay[m];
@@ -397,7 +428,7 @@ __global__ void __launch_bounds__(128, 2) k_adj_entries(SceneDev sc, const doubl
                     const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
                     const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
                     const int mm = (int)(meta & 1023);
-                    adjoint_hit<ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, chk, nthreads);
+                    adjoint_hit<ADJ_ABSORBING>(sc.n_slots, sc.slot_complex, sc.Lmax, *pl, s_thk, s_slot, sl, gw, kappa, Gs, Gp, mm, chk, nthreads);
                     c_ahits += 1;
                     c_alay += (unsigned long long)pl->nlay[mm & 255];
                 }

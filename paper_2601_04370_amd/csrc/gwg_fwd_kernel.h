@@ -65,7 +65,7 @@ __device__ inline Coef4 hit_solve(int n_slots, uint32_t cplx, const PointLds& pl
 // whose exclusive prefix sum of hit counts (off) is <= p: lanes without hits
 // share the next lane's offset and lose the search to it.  Returns its queue
 // slot.  Called by all lanes of the wave (shuffles).
-__device__ inline int dense_slot(int p, int off, int)
+__device__ inline int dense_slot(int p, int off)
 {
     int l = 0;
 #pragma unroll
@@ -76,29 +76,33 @@ __device__ inline int dense_slot(int p, int off, int)
     return hq_slot(l, p - __shfl(off, l, 64));
 }
 
+// This lane's solves: hits in double precision, layers.
+struct HitCounts { unsigned long long fp64, lay; };
+
 // Solve the wave's `total` queued hits in batches of 64 (one per lane);
 // off: this lane's exclusive prefix sum of hit counts.
 template <int MODE, class SL, class Stks>
-__device__ inline void solve_hits(const SceneDev& sc, const PointLds& pl, const Stks& stks,
-                                  const SL& sl, const HitQueue& hq, int total,
-                                  int off, unsigned long long* n_fp64, unsigned long long* n_lay)
+__device__ inline HitCounts solve_hits(int n_slots, uint32_t cplx, const PointLds& pl, const Stks& stks,
+                                       const SL& sl, const HitQueue& hq, int total, int off)
 {
     const int lane = wave_lane();
+    HitCounts n = { 0ull, 0ull };
     for (int b = 0; b < total; b += 64) {
         const int p = b + lane;
         const int pp = p < total ? p : total - 1;
-        const int q = dense_slot(pp, off, sc.Kmax);
+        const int q = dense_slot(pp, off);
         if (p < total) {
             const double kappa = hq.kappa(q);
             const int meta = hq.meta(q);
             const int m = meta & 255;
             bool u64 = false;
-            const Coef4 c = hit_solve<MODE>(sc.n_slots, sc.slot_complex, pl, stks, sl, m, (meta >> 8) & 1, kappa, &u64);
+            const Coef4 c = hit_solve<MODE>(n_slots, cplx, pl, stks, sl, m, (meta >> 8) & 1, kappa, &u64);
             hq.put_coef(q, c);
-            *n_fp64 += u64 ? 1ull : 0ull;
-            *n_lay += (unsigned long long)pl.nlay[m];
+            n.fp64 += u64 ? 1ull : 0ull;
+            n.lay += (unsigned long long)pl.nlay[m];
         }
     }
+    return n;
 }
 
 struct NoHit {

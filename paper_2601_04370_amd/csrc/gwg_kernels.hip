@@ -614,19 +614,20 @@ int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem)
     return blocks_per_cu(fwd_kernel(sc.precision, adj, sc.table != nullptr, sc.memo != 0, sc.dirs != nullptr), wg, smem);
 }
 
-template <bool TAB>
+template <bool TAB, int KIND>
 static int bwd_blocks_per_cu(int precision, int wg, size_t smem)
 {
-    if (precision == GWG_FP64) return blocks_per_cu(k_trace_bwd<GWG_FP64, TAB, ADJ_ANY>, wg, smem);
-    if (precision == GWG_FP32_MIXED) return blocks_per_cu(k_trace_bwd<GWG_FP32_MIXED, TAB, ADJ_ANY>, wg, smem);
-    return blocks_per_cu(k_trace_bwd<GWG_FP32, TAB, ADJ_ANY>, wg, smem);
+    if (precision == GWG_FP64) return blocks_per_cu(k_trace_bwd<GWG_FP64, TAB, KIND>, wg, smem);
+    if (precision == GWG_FP32_MIXED) return blocks_per_cu(k_trace_bwd<GWG_FP32_MIXED, TAB, KIND>, wg, smem);
+    return blocks_per_cu(k_trace_bwd<GWG_FP32, TAB, KIND>, wg, smem);
 }
 
 int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem)
 {
     switch (kind) {
-    case KIND_BWD_REGEN: return bwd_blocks_per_cu<false>(precision, wg, smem);
-    case KIND_BWD_REGEN_TAB: return bwd_blocks_per_cu<true>(precision, wg, smem);
+    case KIND_BWD_REGEN: return bwd_blocks_per_cu<false, ADJ_ABSORBING>(precision, wg, smem);
+    case KIND_BWD_REGEN_LOSSLESS: return bwd_blocks_per_cu<false, ADJ_LOSSLESS>(precision, wg, smem);
+    case KIND_BWD_REGEN_TAB: return bwd_blocks_per_cu<true, ADJ_LOSSLESS>(precision, wg, smem);
     case KIND_ADJ_SORTED:
         return blocks_per_cu(k_adj_sorted<true>, 64, smem);
     case KIND_ADJ_SORTED_ABS:
@@ -686,15 +687,12 @@ hipError_t launch_trace_bwd(const SceneDev& sc, int wg, int grid_blocks, const d
 {
     size_t sm = bwd_smem_bytes(sc, wg);
     dim3 grid((unsigned)grid_blocks), block(wg);
-    if (sc.table)
-        launch_bwd_mode<true, ADJ_ANY>(sc, grid, block, sm, dLdI, partial, scratch, sample_stride, regen, stats, s);
+    if (sc.table)                                            // no thin-film adjoints in it
+        launch_bwd_mode<true, ADJ_LOSSLESS>(sc, grid, block, sm, dLdI, partial, scratch, sample_stride, regen, stats, s);
     else if (sc.slot_complex == 0u)
-        // Without an absorbing layer: the kernel without the absorbing sweep's code
-        // (64 designs x 3751 points x 2000 rays, 10 to 250 layers, entries over their budget:
-        // adjoint 3.37 s against 3.42 s.)
         launch_bwd_mode<false, ADJ_LOSSLESS>(sc, grid, block, sm, dLdI, partial, scratch, sample_stride, regen, stats, s);
     else
-        launch_bwd_mode<false, ADJ_ANY>(sc, grid, block, sm, dLdI, partial, scratch, sample_stride, regen, stats, s);
+        launch_bwd_mode<false, ADJ_ABSORBING>(sc, grid, block, sm, dLdI, partial, scratch, sample_stride, regen, stats, s);
     return hipGetLastError();
 }
 

@@ -22,7 +22,7 @@ int64_t bwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);
 // KIND_FWD and up: forward kernels, KIND_FWD + gradient + 2 table + 4 memoized + 8 direction table
 enum { KIND_BWD_REGEN = 0, KIND_ADJ_ENTRIES = 1, KIND_ADJ_SORTED = 2, KIND_ADJ_MEMO = 3, KIND_ADJ_MEMO_LOSSLESS = 4,
        KIND_TABLE_ACCUM = 5, KIND_BWD_REGEN_TAB = 6, KIND_OMEGA = 7, KIND_FWD = 8,
-       KIND_KEY_ADJ = 64, KIND_KEY_ADJ_LOSSLESS = 65, KIND_ADJ_SORTED_ABS = 66 };
+       KIND_KEY_ADJ = 64, KIND_KEY_ADJ_LOSSLESS = 65, KIND_ADJ_SORTED_ABS = 66, KIND_BWD_REGEN_LOSSLESS = 67 };
 int fwd_blocks_per_cu(const SceneDev& sc, bool adj, int wg, size_t smem);
 int trace_blocks_per_cu(int kind, int precision, int wg, size_t smem);
 int64_t fwd_scratch_doubles(const SceneDev& sc, int64_t grid_blocks, int wg);

@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(64, 1) k_key_adj(SceneDev sc, AdjStore st, con
                     int mm;
                     key_hit(sc, dir_point, key_of[i >> 1], i & 1, &kappa, &mm);
                     const double* g = acc + 4 * i;
-                    adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, kappa, mk(g[0], g[1]),
+                    adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc.n_slots, sc.slot_complex, sc.Lmax, *pl, s_thk, s_slot, sl, gw, kappa, mk(g[0], g[1]),
                                                                          mk(g[2], g[3]), mm, chk, nthreads);
                     c_keys += 1;
                     c_lay += (unsigned long long)pl->nlay[mm & 255];
@@ -564,7 +564,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves, 2) k_adj_memo(SceneDev sc, co
                             const cd Gs = cscale(mk(en.gs_re, en.gs_im), gscale);
                             const cd Gp = cscale(mk(en.gp_re, en.gp_im), gscale);
                             const int mm = (int)(meta & 1023);
-                            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, en.kappa, Gs, Gp, mm, chk, nthreads);
+                            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc.n_slots, sc.slot_complex, sc.Lmax, *pl, s_thk, s_slot, sl, gw, en.kappa, Gs, Gp, mm, chk, nthreads);
                             c_keys += 1;
                             c_lay += (unsigned long long)pl->nlay[mm & 255];
                         }
@@ -578,7 +578,7 @@ __global__ void __launch_bounds__(64 * kMemoWaves, 2) k_adj_memo(SceneDev sc, co
                         const cd Gs = mk(m0.gsum[k], m0.gsum[kMemoKeys + k]);
                         const cd Gp = mk(m0.gsum[2 * kMemoKeys + k], m0.gsum[3 * kMemoKeys + k]);
                         const int mm = m0.kmeta[k];
-                        adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw,
+                        adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc.n_slots, sc.slot_complex, sc.Lmax, *pl, s_thk, s_slot, sl, gw,
                                               __longlong_as_double((long long)m0.kbits[k]), Gs, Gp, mm, chk, nthreads);
                         c_keys += 1;
                         c_lay += (unsigned long long)pl->nlay[mm & 255];

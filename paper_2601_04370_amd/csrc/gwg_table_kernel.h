@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(128, 2) k_table_adj(SceneDev sc, double* __res
             const long long* a = acc + (int64_t)j * 4;
             const cd Gs = mk((double)a[0] * inv, (double)a[1] * inv);
             const cd Gp = mk((double)a[2] * inv, (double)a[3] * inv);
-            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc, *pl, s_thk, s_slot, sl, gw, table_kappa(pl->ng, j, n), Gs, Gp, meta, chk, cstride);
+            adjoint_hit<LOSSLESS ? ADJ_LOSSLESS : ADJ_ABSORBING>(sc.n_slots, sc.slot_complex, sc.Lmax, *pl, s_thk, s_slot, sl, gw, table_kappa(pl->ng, j, n), Gs, Gp, meta, chk, cstride);
             c_keys += 1;
             c_lay += (unsigned long long)pl->nlay[m];
         };

@@ -19,11 +19,16 @@ std::map<char*, size_t> g_mem;
 size_t g_used = 0, g_total = (size_t)288 << 30, g_refuse_lo = 1, g_refuse_hi = 0;
 char* g_next = (char*)0x100000000000;
 bool g_capture = false;
-std::string g_log, g_sizes;
+std::string g_log, g_sizes, g_asked;
 double g_clock = 0.0;                      // ms of the launches so far
 std::map<void*, double> g_event;
 double g_cost64 = 1.0, g_cost128 = 1.0, g_cost256 = 1.0;
 struct Call { dim3 grid, block; size_t smem; hipStream_t stream; } g_call;
+const char* kernel_name(const void* f)
+{
+    Dl_info di;
+    return dladdr(f, &di) && di.dli_sname ? di.dli_sname : "?";
+}
 }  // namespace
 
 extern "C" {
@@ -34,6 +39,7 @@ size_t fake_used() { return g_used; }
 void fake_capture(int on) { g_capture = on != 0; }
 void fake_costs(double c64, double c128, double c256) { g_cost64 = c64; g_cost128 = c128; g_cost256 = c256; }
 const char* fake_log() { return g_log.c_str(); }
+const char* fake_asked() { return g_asked.c_str(); }       // kernels whose occupancy was asked for
 const char* fake_sizes() { return g_sizes.c_str(); }       // of every allocation asked for
 void fake_clear() { g_log.clear(); g_sizes.clear(); }
 
@@ -90,7 +96,12 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b)
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = g_next; return hipSuccess; }
-hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int wg, size_t) { *n = 512 / wg; return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int wg, size_t)
+{
+    g_asked += std::string(kernel_name(f)) + "\n";
+    *n = 512 / wg;
+    return hipSuccess;
+}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sm, hipStream_t s) { g_call = { g, b, sm, s }; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* sm, hipStream_t* s)
 {
@@ -99,8 +110,7 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* sm, hipStream_t* 
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sm, hipStream_t)
 {
-    Dl_info di;
-    const char* name = dladdr(f, &di) && di.dli_sname ? di.dli_sname : "?";
+    const char* name = kernel_name(f);
     char line[768];
     std::snprintf(line, sizeof(line), "%s %u %u", name, g.x * g.y * g.z, b.x);
     g_log += line;

@@ -44,7 +44,7 @@ class Host:
         self.gwg, self.inputs = gwg, inputs
         self.lib = gwg.load_library()
         self.fake = C.CDLL(None)
-        self.fake.fake_log.restype = self.fake.fake_sizes.restype = C.c_char_p
+        self.fake.fake_log.restype = self.fake.fake_sizes.restype = self.fake.fake_asked.restype = C.c_char_p
         self.fake.fake_used.restype = C.c_size_t
         self.fake.fake_memory.argtypes, self.fake.fake_refuse.argtypes = [C.c_size_t], [C.c_size_t] * 2
         self.fake.fake_costs.argtypes = [C.c_double] * 3
@@ -113,6 +113,10 @@ class Host:
     def sizes(self):
         """Allocations asked for since the log was last cleared, bytes."""
         return [int(x) for x in self.fake.fake_sizes().split()]
+
+    def asked(self):
+        """Kernels whose occupancy was asked for."""
+        return self.fake.fake_asked().decode().split()
 
     def kernels(self, name, clear=True):
         return [x for x in self.log(clear) if name in x[0]]
