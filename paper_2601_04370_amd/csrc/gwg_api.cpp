@@ -1031,7 +1031,7 @@ int gwg_trace_forward(gwg_ctx* c, const gwg_slab* slab, const gwg_prma* prma, co
             // sorted adjoint's waves then have entries of one kind, where a
             // few of every region would make them sweep for the others.
             const int64_t ck_per = c->tune.ck_entries_per_ray == 0 ? kCkEntriesPerRay : c->tune.ck_entries_per_ray;
-            if (precision == GWG_FP64 && !(flags & GWG_FWD_MEMO) && sc.slot_complex == 0u && ck_per > 0) {
+            if (precision == GWG_FP64 && !(flags & GWG_FWD_MEMO) && !table && sc.slot_complex == 0u && ck_per > 0) {
                 const int64_t rays_w = (sc.rays_per_tile + wg - 1) / wg * 64;
                 const int64_t ck_cap = std::min<int64_t>(cap_w, rays_w * ck_per);
                 double budget = (double)c->adj_ck.bytes;

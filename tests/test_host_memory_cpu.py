@@ -70,3 +70,23 @@ out['small'] = [int(x[3]['pool']) for x in h2.kernels('k_trace_fwd')]
     assert out["pool"] >= 4
     assert out["rc"] == 0, out["error"]
     assert out["small"] == [1]
+
+
+@pytest.mark.parametrize("mode", ["memo", "table"])
+def test_keyed_forwards_reserve_no_segment_matrices(mode):
+    """Only the per-hit solves store them (25 GB for 1323 points x 8192 rays of 200 layers)."""
+    out = run(f"""
+sc = h.scene(fov_n=3, rays_per_point=512, n_layers=40)
+h.tuning(table_nodes=16, rays_per_block=256)
+assert h.forward(sc, grad=True) == 0
+out['hit'] = h.sizes()
+g = type(h)()
+g.fake.fake_clear()
+g.tuning(table_nodes=16, rays_per_block=256)
+assert g.forward(sc, grad=True, memo={mode == "memo"}, table={mode == "table"}) == 0
+out['keyed'] = g.sizes()
+""")
+    entries = 12 * next(n for n in out["hit"] if n * 12 in out["hit"])      # 8 a ray, 48 bytes
+    matrices = entries * 4 * 2 * 64 // (8 * 48)                             # of 4 entries a ray, 2 blocks of 64 bytes
+    assert matrices in out["hit"] and entries in out["keyed"]
+    assert matrices not in out["keyed"]
