@@ -119,6 +119,12 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sm
         std::snprintf(line, sizeof(line), " items=%lld rays=%lld pool=%d memo=%d dirs=%p", (long long)s->n_items,
                       (long long)s->rays_per_tile, s->pool, s->memo, (const void*)s->dirs);
         g_log += line;
+        if (std::strstr(name, "k_trace_fwd")) {
+            const gwg::AdjStore* a = (const gwg::AdjStore*)args[8];
+            std::snprintf(line, sizeof(line), " regions=%lld ck_regions=%lld ck_nb=%d ck_evan=%d",
+                          (long long)(s->n_items * a->waves), (long long)a->ck_regions, a->ck_nb, a->ck_evan);
+            g_log += line;
+        }
         if (std::strstr(name, "k_trace_fwd")) g_clock += b.x == 64 ? g_cost64 : b.x == 128 ? g_cost128 : g_cost256;
     }
     g_log += "\n";
