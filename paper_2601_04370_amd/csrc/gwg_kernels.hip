@@ -879,20 +879,23 @@ static hipError_t launch_tmm_mode(const double* thk, const uint8_t* slot, int L,
     return hipGetLastError();
 }
 
-// Whether queries are solved by kind.  A launch whose waves all run at once
-// (two workgroups a CU) is as long as its longest wave, and sorting adds to it
-// (100000 queries of 200 layers: double precision 73 us in order and 77 by
-// kind, mixed 111 and 114).  Beyond that mixed precision gains always (200000
-// queries of 8, 40 and 200 layers: 33, 64 and 219 us in order, 26, 42 and 118
-// by kind); double precision on lossless stacks of more than a few layers (8,
-// 40 and 200: 24.0, 43.8 and 134 us in order, 25.1, 41.4 and 118 by kind).
-// Silver's complex path hides the hyperbolic case (300000 queries of 201
-// layers: 225 and 234 us), and single precision hardly pays for it (115 and
-// 129 us).
+// Whether queries are solved by kind.  Mixed precision always: in order, one
+// query near the critical angle makes its wave run both solves (uniform
+// angles, in order and by kind: 2000 queries of 200 layers 143 and 96 us,
+// 100000 of 400 308 and 239 us, of 2000 1500 and 1156 us; where a fifth of the
+// queries are near-critical, 100000 of 200 layers 111 and 114 us, 200000 of 8,
+// 40 and 200 layers 33, 64 and 219 us and 26, 42 and 118 us).  Double precision
+// on lossless stacks of more than a few layers (200000 queries of 8, 40 and
+// 200: 24.0, 43.8 and 134 us in order, 25.1, 41.4 and 118 by kind), unless the
+// waves all run at once, two workgroups a CU: such a launch is as long as its
+// longest wave, and sorting adds to it (100000 of 200 layers 73 us in order
+// and 77 by kind).  Silver's complex path hides the hyperbolic case (300000
+// queries of 201 layers: 225 and 234 us), and single precision hardly pays for
+// it (115 and 129 us).
 static bool tmm_sorted(int precision, int L, uint32_t cplx, int64_t nq, int n_cu)
 {
-    if (nq <= 2 * 256 * (int64_t)n_cu) return false;
-    return precision == GWG_FP32_MIXED || (precision == GWG_FP64 && cplx == 0u && L >= 32);
+    if (precision == GWG_FP32_MIXED) return true;
+    return precision == GWG_FP64 && cplx == 0u && L >= 32 && nq > 2 * 256 * (int64_t)n_cu;
 }
 
 hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, int L,
@@ -905,8 +908,9 @@ hipError_t launch_tmm_rt(int precision, const double* thk, const uint8_t* slot, 
     int chunk = 0;
     if (tmm_sorted(precision, L, rows.cplx, nq, n_cu)) {
         // as many queries a workgroup as fill the GPU once (the longer its
-        // list, the fewer its mixed batches), if their list fits in LDS
-        const int64_t want = (nq + 2 * n_cu - 1) / (2 * n_cu);
+        // list, the fewer its mixed batches) and at least one a lane, if
+        // their list fits in LDS
+        const int64_t want = std::max<int64_t>(wg, (nq + 2 * n_cu - 1) / (2 * n_cu));
         chunk = (int)std::min<int64_t>(kTmmChunk, (want + 63) / 64 * 64);
         if (sm + sizeof(uint16_t) * chunk + 64 > 65536) chunk = 0;
         sm += sizeof(uint16_t) * chunk;

@@ -69,6 +69,17 @@ class Host:
         return self.lib.gwg_trace_forward(self.h, C.byref(s), C.byref(p), C.byref(m), C.byref(st), C.byref(r), 1, 0,
                                           precision, flags, C.byref(eb), None, 1, None, None)
 
+    def tmm(self, n_layers, silver, n, precision=0):
+        import numpy as np
+        g = self.gwg
+        lam = np.array([450.0, 550.0, 650.0])
+        n_re = np.tile([1.52, 1.46, 2.35, 0.12], (3, 1))
+        n_im = np.tile([0.0, 0.0, 0.0, 3.3 if silver else 0.0], (3, 1))
+        mat = (1 + np.arange(n_layers) % (3 if silver else 2)).astype(np.uint8)
+        st = g.Stack(n_layers, self.ptr, g._np_ptr(mat, g._u8p), 0, 0)
+        mt = g.Materials(*n_re.shape, *(g._np_ptr(x, g._dp) for x in (lam, n_re, n_im)))
+        return self.lib.gwg_tmm_rt(self.h, C.byref(st), C.byref(mt), n, self.ptr, self.ptr, precision, self.ptr, None)
+
     def backward(self, stride=1):
         return self.lib.gwg_trace_backward(self.h, self.ptr, self.ptr, stride, None, None)
 

@@ -2,7 +2,8 @@
 (header: asynchronous), its results are those of one call per wavelength bit
 for bit, whether the tables travel with the launch (up to 31 wavelengths of
 long stacks) or are copied, and whether queries are solved in order or by kind
-(launches of more queries than run at once: 131072 lanes of 256 CUs)."""
+(mixed precision; lossless stacks in double precision where the launch has
+more queries than run at once: 131072 lanes of 256 CUs)."""
 import time
 
 import numpy as np
