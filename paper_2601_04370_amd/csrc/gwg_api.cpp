@@ -661,26 +661,36 @@ void set_tiles(SceneDev& s, int64_t rays_per_tile, int wg, int n_cu, bool grad, 
         const int64_t target = cu * (s.memo ? 16 : 32);
         const int64_t tiles = points >= target ? 1 : (target + points - 1) / points;
         rpt = (s.N + tiles - 1) / tiles;
-        // 4 rays per lane make fuller solve batches and field passes, but
-        // not at the price of idle CUs: fewer while the launch has under 4
-        // items per CU (8 with an adjoint, which runs 8 waves a CU and two
-        // to an item; 2 memoized, whose items solve their keys each).  75
-        // points x 8192 rays, 200 layers, gradient: 2.94 ms a step at one
-        // ray per lane, 4.95 at four; memoized 1.74 and 1.31 ms.  100,000
-        // rays of one point, 8 layers, forward: 0.14 and 0.30 ms; 1,000,000
-        // rays 0.83 and 0.75 ms.
-        const int64_t fill = cu * (s.memo ? 2 : grad ? 8 : 4) * (wg / 64);
-        int64_t rounds = std::min<int64_t>(4, std::max<int64_t>(1, ray_waves(s) / fill));
-        // per hit, of 1 to that many the one whose items fill whole passes of two
-        // workgroups per CU best (1,000,000 rays of one point: 1302 items
-        // of three rounds take 0.84 ms, 977 of four 0.75)
-        int64_t best = -1, pick = rounds;
-        for (int64_t r = rounds; per_hit && r >= 1; --r) {
-            const int64_t items = points * ((s.N + wg * r - 1) / (wg * r));
-            const int64_t cost = (items + 2 * cu - 1) / (2 * cu) * r;
-            if (best < 0 || cost < best) { best = cost; pick = r; }
+        int64_t rounds = 1;
+        if (per_hit) {
+            // Rounds of 64 rays a wave, one to four: more make fuller solve
+            // batches, fewer a shorter tail and a fuller GPU.  The fewest
+            // rounds by passes x (rounds + 0.4) + 0.7 rounds (the tail), a
+            // pass being two workgroups of four waves a CU, at least one;
+            // items are drawn, so passes need not be whole.  Over 230 launches
+            // of 1.6e5 to 4e6 rays, 8 to 250 layers, both precisions, with and
+            // without a gradient, this is 3.3 % slower than the best of the
+            // four on average and 23 % at worst; whole passes x rounds alone
+            // 6.2 and 28 %, always two rounds 4.8 and 39 %.  1,000,000 rays of
+            // one point, 8 layers, 1 to 4 rounds: 0.83, 0.77, 0.85, 0.76 ms;
+            // 9 points x 116,500 rays, 250 layers, mixed precision: 6.01, 5.59,
+            // 6.54, 5.98 ms.
+            const int64_t slots = 2 * cu * (256 / wg);
+            int64_t best = -1;
+            for (int64_t r = 1; r <= 4; ++r) {
+                const int64_t full = std::min<int64_t>(r, (s.N + wg - 1) / wg);
+                const int64_t items = points * ((s.N + wg * r - 1) / (wg * r));
+                const int64_t cost = std::max<int64_t>(items, slots) * (10 * full + 4) + 7 * slots * full;
+                if (best < 0 || cost <= best) { best = cost; rounds = r; }
+            }
+        } else {
+            // Keyed items walk, and solve their keys each: up to four rounds
+            // while that leaves 4 items per CU (8 with a gradient, 2 memoized).
+            // 75 points x 8192 rays, 200 layers, memoized, gradient: 1.74 ms
+            // a step at one ray per lane and 1.31 ms at four.
+            const int64_t fill = cu * (s.memo ? 2 : grad ? 8 : 4) * (wg / 64);
+            rounds = std::min<int64_t>(4, std::max<int64_t>(1, ray_waves(s) / fill));
         }
-        rounds = pick;
         rpt = std::max<int64_t>(rpt, (int64_t)wg * rounds);
         rpt = ((rpt + wg - 1) / wg) * wg;
         if (forward && wg <= 128 && spread_rays(s, n_cu)) rpt = 64;
